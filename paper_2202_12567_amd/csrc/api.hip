@@ -617,7 +617,7 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
     bool any_global = false;
     for (int g = 1; g < 8; g += 2) any_global = any_global || !plan->groups[g].empty();
     bytes[R_GSYS] = any_global ? (size_t)S * GADM_SYS_BYTES : 0;
-    bytes[R_GE2] = (size_t)e2b * 8;
+    bytes[R_GE2] = (size_t)e2b * 8 * (plan->als ? ALS_E2_SLOTS : 1);
     bytes[R_COLW_PREFIX] = oc * 8;
     bytes[R_BITMAP] = obm * 4;
     bytes[R_BITMAPT] = obmt * 4;
@@ -898,8 +898,10 @@ int vplmc_render(vplmc_ctx *ctx, const vplmc_plan *plan, const vplmc_points *poi
     float *scale = region<float>(ws, plan, VPLMC_R_SLICE_SCALE);
     if ((rc = ph.mark(VPLMC_PH_ADM))) return rc;
     if (plan->als)
-        rc = launch_als(st, *plan, desc, ids, *params, row_ptr, csr_col, csr_val, col_ptr, csc_row, csc_val, X, Y,
-                        scale, stats);
+        rc = launch_als(st, *plan, desc, ids, ids + S, region<char>(ws, plan, R_GSYS), region<double>(ws, plan, R_GE2),
+                        *params, row_ptr, csr_col, csr_val, col_ptr, csc_row, csc_val, X,
+                        region<float>(ws, plan, R_XNEXT), Y, scale, region<int32_t>(ws, plan, R_XP),
+                        region<int32_t>(ws, plan, R_YP), stats);
     else
         rc = launch_adm(st, &ctx->adm, *plan, ctx->n_cu, desc, ids, ids + S, region<char>(ws, plan, R_GSYS),
                         region<double>(ws, plan, R_GE2), region<int32_t>(ws, plan, R_QUEUE), *params,
@@ -1262,8 +1264,10 @@ int vplmc_stage_adm(vplmc_ctx *ctx, const vplmc_plan *plan, const vplmc_params *
     float *Y = region<float>(ws, plan, VPLMC_R_Y);
     float *scale = region<float>(ws, plan, VPLMC_R_SLICE_SCALE);
     if (plan->als)
-        rc = launch_als(st, *plan, desc, ids, *params, row_ptr, csr_col, csr_val, col_ptr, csc_row, csc_val, X, Y,
-                        scale, stats);
+        rc = launch_als(st, *plan, desc, ids, ids + plan->n_slices, region<char>(ws, plan, R_GSYS), region<double>(ws, plan, R_GE2),
+                        *params, row_ptr, csr_col, csr_val, col_ptr, csc_row, csc_val, X,
+                        region<float>(ws, plan, R_XNEXT), Y, scale, region<int32_t>(ws, plan, R_XP),
+                        region<int32_t>(ws, plan, R_YP), stats);
     else
         rc = launch_adm(st, &ctx->adm, *plan, ctx->n_cu, desc, ids, ids + plan->n_slices, region<char>(ws, plan, R_GSYS),
                         region<double>(ws, plan, R_GE2), region<int32_t>(ws, plan, R_QUEUE), *params,

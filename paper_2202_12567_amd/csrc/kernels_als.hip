@@ -13,14 +13,36 @@
 // rank stay 0 (their Gram block is lam max(1, n) I and their right-hand side
 // 0).
 //
-// One workgroup per slice, X and Y in global memory (each slice's factors
-// stay in the caches of its CU).  One wavefront per row (then per column):
-// the wavefront stages a block of the row's samples' Y vectors in its LDS
-// area, each lane accumulates its share of the q x q Gram (FP32) and lanes
-// below q the right-hand side; the system is solved in FP64 by a
-// right-looking Cholesky in the wavefront's LDS area.  Rows and columns are
-// owned by fixed wavefronts and summed in a fixed order, so results are
-// bit-reproducible.
+// Two launches per iteration over all slices of a rank bucket (k_als_rows,
+// k_als_cols), after an init launch and before a final one, so that a frame of
+// a few dozen slices fills the chip and the launch boundaries order the
+// half-steps.  A 16-lane row of a wavefront (32 lanes at rank 32) owns one
+// system, lane r holding row r of its Gram: a factor vector is one coalesced
+// load of the tile, and each lane multiplies its own component by every
+// component, broadcast by DPP.  The Gram is summed in FP32 in sample order;
+// each lane then turns its row to FP64 and the tile solves by Gauss-Jordan
+// elimination (symmetric positive definite, so no pivoting), the pivot row
+// broadcast by DPP as well, so the system never leaves the registers.  The
+// loads run two blocks of samples ahead of the arithmetic (index, then the
+// vectors it names).  The init launch orders a slice's rows and columns by
+// decreasing sample count: the systems of a wavefront are then of similar
+// length, and the longest start first.
+// The residual of the iterate that enters an iteration is formed by the row
+// launch from the Y vectors it loads anyway; its sums per workgroup land in
+// slots, which every workgroup of the column launch adds in slot order for
+// the stop test.  The row launch writes the second X buffer, so a slice that
+// stops keeps the X its residual was measured on.  The factors are
+// bit-reproducible (every system is summed in sample order).
+//
+// Bound by the latency of the gathers on the longest columns and by the
+// elimination's dependent FP64 chain.  Measured on one MI355X, 48 slices of
+// 200-900 rows, 300 columns, rank 16, 6.5% sampled, 100 iterations: 467 ms
+// with one 512-thread workgroup per slice and the systems in LDS (Cholesky by
+// one wavefront per row), 13.0 ms now; Grams on the matrix unit (a
+// wavefront per four systems, summed in another order) took 16 ms in FP32 and
+// 26 ms in FP64.
+
+#include <utility>
 
 #include "vplmc_internal.h"
 
@@ -28,15 +50,10 @@ namespace vplmc {
 namespace {
 
 constexpr int WAVE = 64;
-constexpr int ALS_THREADS = 512;
+constexpr int ALS_THREADS = 256;      // of the row and column launches
 constexpr int ALS_NW = ALS_THREADS / WAVE;
-constexpr int ALS_B = 4;          // samples staged per round
-
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+constexpr int ALS_INIT_THREADS = 512;
+constexpr int ALS_BINS = 1024;        // sample counts told apart by the ordering
 
 __device__ __forceinline__ double wave_sum_d(double v) {
 #pragma unroll
@@ -44,271 +61,495 @@ __device__ __forceinline__ double wave_sum_d(double v) {
     return v;
 }
 
-// Solves A x = b for nrhs right-hand sides (b[r * Q + k]) in place, A the
-// Q x Q SPD matrix in the wavefront's LDS area (full matrix written; the lower
-// triangle is factored).
-template <int Q>
-__device__ void wave_chol_solve(double *A, double *b, int nrhs, int lane) {
-    for (int j = 0; j < Q; ++j) {
-        if (lane == 0) A[j * Q + j] = sqrt(A[j * Q + j]);
-        wave_lds_sync();
-        const double d = A[j * Q + j];
-        for (int i = j + 1 + lane; i < Q; i += WAVE) A[i * Q + j] /= d;
-        wave_lds_sync();
-        for (int e = lane; e < Q * Q; e += WAVE) {
-            const int i = e / Q, k = e % Q;
-            if (k > j && i >= k) A[i * Q + k] -= A[i * Q + j] * A[k * Q + j];
-        }
-        wave_lds_sync();
-    }
-    if (lane < nrhs) {
-        double *x = b + lane * Q;
-        for (int i = 0; i < Q; ++i) {
-            double s = x[i];
-            for (int l = 0; l < i; ++l) s -= A[i * Q + l] * x[l];
-            x[i] = s / A[i * Q + i];
-        }
-        for (int i = Q - 1; i >= 0; --i) {
-            double s = x[i];
-            for (int l = i + 1; l < Q; ++l) s -= A[l * Q + i] * x[l];
-            x[i] = s / A[i * Q + i];
-        }
-    }
-    wave_lds_sync();
-}
-
-template <int Q>
-struct AlsWave {
-    double A[Q * Q];
-    double b[3 * Q];
-    float stage[ALS_B * 3 * Q];
-};
-
 // sum over the block of one double per thread, in a fixed order
+template <int NW>
 __device__ __forceinline__ double block_sum_d(double v, double *red) {
     const int t = threadIdx.x, lane = t % WAVE, w = t / WAVE;
     v = wave_sum_d(v);
     if (lane == 0) red[w] = v;
     __syncthreads();
     double s = 0.0;
-    for (int k = 0; k < ALS_NW; ++k) s += red[k];
+    for (int k = 0; k < NW; ++k) s += red[k];
     __syncthreads();
     return s;
 }
 
+// how a rank is laid out on a wavefront
 template <int Q>
-__global__ __launch_bounds__(ALS_THREADS) void k_als(
-    const SliceDesc *__restrict__ desc, const int32_t *__restrict__ slice_list, uint64_t seed, int32_t max_iter,
-    int32_t mode, float tol, float lam, const int32_t *__restrict__ row_ptr_all,
-    const int32_t *__restrict__ csr_col_all, const float *__restrict__ csr_val_all,
-    const int32_t *__restrict__ col_ptr_all, const int32_t *__restrict__ csc_row_all,
-    const float *__restrict__ csc_val_all, float *X_all, float *Y_all, float *scale_all, int32_t *stats_all) {
-    constexpr int EPL = (Q * Q + WAVE - 1) / WAVE;     // Gram entries per lane
-    __shared__ AlsWave<Q> wv[ALS_NW];
-    __shared__ double red[ALS_NW];
-    const int s = __builtin_amdgcn_readfirstlane(slice_list[blockIdx.x]);
-    const SliceDesc d = desc[s];
-    const int m = d.m, n = d.n, qr = d.qr;
-    const int t = threadIdx.x, lane = t % WAVE;
-    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);
-    AlsWave<Q> &my = wv[w];
-    const int32_t *row_ptr = row_ptr_all + d.off_row;
-    const int32_t *col_ptr = col_ptr_all + d.off_colptr;
-    const int32_t *csr_col = csr_col_all + d.off_omega;
-    const float *csr_val = csr_val_all + 3 * d.off_omega;
-    const int32_t *csc_row = csc_row_all + d.off_omega;
-    const float *csc_val = csc_val_all + 3 * d.off_omega;
-    float *X = X_all + d.off_x;
-    float *Y = Y_all + d.off_y;
-    int32_t *st = stats_all + 4 * s;
-    const int nnz = row_ptr[m];
+struct AlsShape {
+    static constexpr int T = Q <= 16 ? 16 : 32;         // lanes of a system
+    static constexpr int SYS = WAVE / T;                // systems per wavefront
+    static constexpr int GRP = SYS * ALS_NW;            // systems per workgroup
+    // workgroups per row block and per column block of the plan
+    static constexpr int RSUB = GADM_RB / GRP, CSUB = GADM_CB / GRP;
+};
 
-    // ---- scale s0 = mean sampled value; ||P_Omega M|| of M / s0 ----
+// per-slice state between the launches
+struct AlsState {
+    int32_t done, iters, resid, zero;    // resid: FP32 bits; zero: every sample is 0
+    double norm_m, s0;                   // ||P_Omega M|| / s0, mean sampled value
+};
+
+struct AlsArgs {
+    const SliceDesc *desc;
+    const int32_t *ids;                  // the group's slices
+    const int32_t *rowp, *colp;          // count + 1: prefixes of the slices' row and column blocks
+    int32_t count;
+    uint64_t seed;
+    int32_t max_iter, mode;
+    float tol, lam;
+    const int32_t *row_ptr_all, *csr_col_all;
+    const float *csr_val_all;
+    const int32_t *col_ptr_all, *csc_row_all;
+    const float *csc_val_all;
+    float *X_all, *Xn_all, *Y_all, *scale_all;
+    int32_t *rord_all, *cord_all;        // per slice at off_x, off_y: its rows and columns by decreasing count
+    int32_t *stats_all;
+    char *gsys;
+    double *e2;                          // RSUB slots per row block of the group
+};
+
+__device__ __forceinline__ AlsState *state_of(char *base, int s) {
+    return reinterpret_cast<AlsState *>(base + (size_t)s * GADM_SYS_BYTES);
+}
+
+// the slice position k with pre[k] <= b < pre[k + 1]
+__device__ __forceinline__ int block_slice(const int32_t *__restrict__ pre, int count, int b) {
+    int lo = 0, hi = count;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (pre[mid] <= b) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// the items 0 .. n - 1 of a CSR / CSC pointer by decreasing count (counts past
+// ALS_BINS - 1 alike; the order among equals does not matter).  All threads call.
+__device__ void order_by_count(const int32_t *__restrict__ ptr, int n, int32_t *__restrict__ order, int32_t *bins) {
+    const int t = threadIdx.x;
+    auto bin = [&](int i) { return ALS_BINS - 1 - min(ptr[i + 1] - ptr[i], ALS_BINS - 1); };
+    for (int e = t; e < ALS_BINS; e += ALS_INIT_THREADS) bins[e] = 0;
+    __syncthreads();
+    for (int i = t; i < n; i += ALS_INIT_THREADS) atomicAdd(bins + bin(i), 1);
+    __syncthreads();
+    if (t < WAVE) {                       // exclusive prefix on one wavefront
+        constexpr int PER = ALS_BINS / WAVE;
+        int sum = 0;
+        for (int e = 0; e < PER; ++e) sum += bins[t * PER + e];
+        int incl = sum;
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const int u = __shfl_up(incl, o, WAVE);
+            if (t >= o) incl += u;
+        }
+        int base = incl - sum;
+        for (int e = 0; e < PER; ++e) {
+            const int c = bins[t * PER + e];
+            bins[t * PER + e] = base;
+            base += c;
+        }
+    }
+    __syncthreads();
+    for (int i = t; i < n; i += ALS_INIT_THREADS) order[atomicAdd(bins + bin(i), 1)] = i;
+    __syncthreads();
+}
+
+// scale s0 = mean sampled value, ||P_Omega M|| of M / s0, initial factors as the ADM's
+template <int Q>
+__global__ __launch_bounds__(ALS_INIT_THREADS) void k_als_init(AlsArgs a) {
+    __shared__ double red[ALS_INIT_THREADS / WAVE];
+    __shared__ int32_t bins[ALS_BINS];
+    const int s = __builtin_amdgcn_readfirstlane(a.ids[blockIdx.x]);
+    const SliceDesc d = a.desc[s];
+    const int m = d.m, n = d.n, qr = d.qr, t = threadIdx.x;
+    const float *csr_val = a.csr_val_all + 3 * d.off_omega;
+    float *X = a.X_all + d.off_x;
+    float *Y = a.Y_all + d.off_y;
+    AlsState *st = state_of(a.gsys, s);
+    const int nnz = a.row_ptr_all[d.off_row + m];
     double sum = 0.0, sumsq = 0.0;
-    for (int p = t; p < 3 * nnz; p += ALS_THREADS) {
+    for (int p = t; p < 3 * nnz; p += ALS_INIT_THREADS) {
         const double v = (double)csr_val[p];
         sum += v;
         sumsq += v * v;
     }
-    sum = block_sum_d(sum, red);
-    sumsq = block_sum_d(sumsq, red);
-    if (nnz == 0 || !(sumsq > 0.0)) {
-        for (int e = t; e < m * Q; e += ALS_THREADS) X[e] = 0.f;
-        for (int e = t; e < 3 * n * Q; e += ALS_THREADS) Y[e] = 0.f;
-        if (t == 0) {
-            scale_all[s] = 0.f;
-            st[0] = 0;
-            st[1] |= VPLMC_SLICE_ALL_ZERO;
-            st[2] = __float_as_int(0.f);
-        }
-        return;
+    sum = block_sum_d<ALS_INIT_THREADS / WAVE>(sum, red);
+    sumsq = block_sum_d<ALS_INIT_THREADS / WAVE>(sumsq, red);
+    const bool zero = nnz == 0 || !(sumsq > 0.0);
+    const double s0 = zero ? 0.0 : sum / (3.0 * (double)nnz);
+    if (t == 0) {
+        st->done = zero ? 1 : 0;
+        st->iters = zero ? 0 : a.max_iter;
+        st->resid = 0;
+        st->zero = zero ? 1 : 0;
+        st->norm_m = zero ? 0.0 : sqrt(sumsq) / s0;
+        st->s0 = s0;
+        a.scale_all[s] = (float)s0;
     }
-    const double s0 = sum / (3.0 * (double)nnz);
-    const float inv_s0 = (float)(1.0 / s0);
-    const double normM = sqrt(sumsq) / s0;
-    if (t == 0) scale_all[s] = (float)s0;
-
-    // ---- initial factors, as the ADM's ----
+    order_by_count(a.row_ptr_all + d.off_row, m, a.rord_all + d.off_x, bins);
+    order_by_count(a.col_ptr_all + d.off_colptr, n, a.cord_all + d.off_y, bins);
     const float cq = (float)(2.0 / sqrt((double)qr));
-    const bool given = (mode & 2) != 0;
-    for (int e = t; e < m * Q; e += ALS_THREADS) {
+    const bool given = (a.mode & 2) != 0;
+    for (int e = t; e < m * Q; e += ALS_INIT_THREADS) {
         const int i = e / Q, k = e % Q;
-        const U64x4 r = philox(seed, (uint64_t)s, (uint64_t)i, (uint64_t)k, TAG_INITX, 0);
-        X[e] = k < qr ? (given ? X[e] : __fmul_rn((float)(r.a >> 40) * 0x1p-24f, cq)) : 0.f;
+        float v = 0.f;
+        if (!zero && k < qr)
+            v = given ? X[e]
+                      : __fmul_rn((float)(philox(a.seed, (uint64_t)s, (uint64_t)i, (uint64_t)k, TAG_INITX, 0).a >> 40) *
+                                      0x1p-24f,
+                                  cq);
+        X[e] = v;
     }
-    for (int e = t; e < 3 * n * Q; e += ALS_THREADS) {
+    for (int e = t; e < 3 * n * Q; e += ALS_INIT_THREADS) {
         const int j = e / (3 * Q), c = (e / Q) % 3, k = e % Q;
-        const uint64_t col = (uint64_t)c * (uint64_t)n + (uint64_t)j;
-        const U64x4 r = philox(seed, (uint64_t)s, (uint64_t)k, col, TAG_INITY, 0);
-        Y[e] = k < qr ? (given ? Y[e] : __fmul_rn((float)(r.a >> 40) * 0x1p-24f, cq)) : 0.f;
+        float v = 0.f;
+        if (!zero && k < qr) {
+            const uint64_t col = (uint64_t)c * (uint64_t)n + (uint64_t)j;
+            v = given ? Y[e]
+                      : __fmul_rn((float)(philox(a.seed, (uint64_t)s, (uint64_t)k, col, TAG_INITY, 0).a >> 40) *
+                                      0x1p-24f,
+                                  cq);
+        }
+        Y[e] = v;
     }
-    __threadfence_block();
-    __syncthreads();
+}
 
-    int iters = max_iter;
-    double err = 0.0;
-    for (int it = 0; it < max_iter; ++it) {
-        // ---- relative residual on Omega: one wavefront per row, lanes over its samples ----
-        double r2 = 0.0;
-        for (int i = w; i < m; i += ALS_NW) {
-            const float *xi = X + (size_t)i * Q;
-            for (int p = row_ptr[i] + lane; p < row_ptr[i + 1]; p += WAVE) {
-                const float *yj = Y + (size_t)csr_col[p] * 3 * Q;
-                float d0 = 0.f, d1 = 0.f, d2 = 0.f;
+// sum over the lanes of each tile, the same bits in all of them
+template <int T>
+__device__ __forceinline__ float tile_sum(float v) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));   // quad_perm [1 0 3 2]
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));   // quad_perm [2 3 0 1]
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));  // row_half_mirror
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, true));  // row_mirror
+    if constexpr (T == 32) v += __shfl_xor(v, 16, WAVE);
+    return v;
+}
+
+// lane J's value of each 16-lane row (T = 16: DPP row_newbcast) or 32-lane half
+template <int T, int J>
+__device__ __forceinline__ double tile_bcast(double v) {
+    if constexpr (T == 16) {
+        const long long b = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x150 + J, 0xF, 0xF, true);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + J, 0xF, 0xF, true);
+        return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+    } else {
+        return __shfl(v, J, 32);
+    }
+}
+
+template <int J>
+__device__ __forceinline__ float row_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + J, 0xF, 0xF, true));
+}
+
+template <int J>
+__device__ __forceinline__ int row_bcast(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0x150 + J, 0xF, 0xF, true);
+}
+// f(0), ..., f(U - 1) with constant arguments (a DPP lane number is one)
+template <int U, typename F, int... I>
+__device__ __forceinline__ void block_u_(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int U, typename F>
+__device__ __forceinline__ void block_u(F &&f) {
+    block_u_<U>(f, std::make_integer_sequence<int, U>{});
+}
+
+// one component of a vector per lane of a tile -> its 16-component blocks,
+// each held alike by every 16-lane row of the tile
+template <int T>
+__device__ __forceinline__ void blocks_of(float v, int r, float (&blk)[T / 16]) {
+    if constexpr (T == 16) {
+        blk[0] = v;
+    } else {
+        const float o = __shfl_xor(v, 16, WAVE);
+        blk[0] = r < 16 ? v : o;
+        blk[1] = r < 16 ? o : v;
+    }
+}
+
+// G[k] += f f_k (columns), or with the three channels of a sample
+// G[k] += (f1 f1_k + f0 f0_k) + f2 f2_k, rounded in that order
+template <int Q, int T, int K>
+__device__ __forceinline__ void gram_add(float (&G)[Q], float f, const float (&b)[T / 16]) {
+    if constexpr (K < Q) {
+        G[K] = fmaf(f, row_bcast<K % 16>(b[K / 16]), G[K]);
+        gram_add<Q, T, K + 1>(G, f, b);
+    }
+}
+template <int Q, int T, int K>
+__device__ __forceinline__ void gram_add3(float (&G)[Q], const float (&f)[3], const float (&b)[3][T / 16]) {
+    if constexpr (K < Q) {
+        const float p = fmaf(f[0], row_bcast<K % 16>(b[0][K / 16]), __fmul_rn(f[1], row_bcast<K % 16>(b[1][K / 16])));
+        G[K] = __fadd_rn(G[K], fmaf(f[2], row_bcast<K % 16>(b[2][K / 16]), p));
+        gram_add3<Q, T, K + 1>(G, f, b);
+    }
+}
+
+// step J of the elimination: row J is the pivot row, every other row of the
+// tile loses its component J (components below J are not needed any more)
+template <int Q, int T, int NR, int J>
+__device__ __forceinline__ void gj_steps(double (&A)[Q], double (&b)[NR], double &dinv, int r) {
+    if constexpr (J < Q) {
+        const double inv = 1.0 / tile_bcast<T, J>(A[J]);
+        const double f = r == J ? 0.0 : A[J] * inv;
+        dinv = r == J ? inv : dinv;
 #pragma unroll
-                for (int k = 0; k < Q; ++k) {
-                    const float x = xi[k];
-                    d0 = fmaf(x, yj[k], d0);
-                    d1 = fmaf(x, yj[Q + k], d1);
-                    d2 = fmaf(x, yj[2 * Q + k], d2);
-                }
-                const float e0 = csr_val[3 * p] * inv_s0 - d0, e1 = csr_val[3 * p + 1] * inv_s0 - d1;
-                const float e2 = csr_val[3 * p + 2] * inv_s0 - d2;
-                r2 += (double)e0 * e0 + (double)e1 * e1 + (double)e2 * e2;
+        for (int k = J + 1; k < Q; ++k) A[k] = fma(-f, tile_bcast<T, J>(A[k]), A[k]);
+#pragma unroll
+        for (int c = 0; c < NR; ++c) b[c] = fma(-f, tile_bcast<T, J>(b[c]), b[c]);
+        gj_steps<Q, T, NR, J + 1>(A, b, dinv, r);
+    }
+}
+
+// (G + shift I)^-1 b of the systems of a wavefront, lane r of a tile holding
+// row r of its system's G and component r of the right-hand sides
+template <int Q, int NR>
+__device__ __forceinline__ void tile_solve(const float (&G)[Q], double shift, double (&b)[NR], int r) {
+    using S = AlsShape<Q>;
+    double A[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) A[k] = (double)G[k];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) A[k] += r == k ? shift : 0.0;
+    double dinv = 0.0;
+    gj_steps<Q, S::T, NR, 0>(A, b, dinv, r);
+#pragma unroll
+    for (int c = 0; c < NR; ++c) b[c] *= dinv;
+}
+
+// Row half-step: GRP rows of one slice per workgroup.
+template <int Q>
+__global__ __launch_bounds__(ALS_THREADS) void k_als_rows(AlsArgs a, int it) {
+    using S = AlsShape<Q>;
+    constexpr int U = 8;                             // samples of a block
+    __shared__ double red[ALS_NW];
+    const int blk = blockIdx.x / S::RSUB, sub = blockIdx.x % S::RSUB;
+    const int kk = block_slice(a.rowp, a.count, blk);
+    const int s = __builtin_amdgcn_readfirstlane(a.ids[kk]);
+    const AlsState *st = state_of(a.gsys, s);
+    if (st->done) return;
+    const SliceDesc d = a.desc[s];
+    const int t = threadIdx.x, lane = t % WAVE, r = lane % S::T, g = lane / S::T;
+    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);
+    const int at = (blk - a.rowp[kk]) * GADM_RB + sub * S::GRP + w * S::SYS + g;   // the tile's place in the order
+    const float inv_s0 = (float)(1.0 / st->s0);
+    const int32_t *row_ptr = a.row_ptr_all + d.off_row;
+    const int32_t *csr_col = a.csr_col_all + d.off_omega;
+    const float *csr_val = a.csr_val_all + 3 * d.off_omega;
+    const float *X = ((it & 1) ? a.Xn_all : a.X_all) + d.off_x;
+    float *Xn = ((it & 1) ? a.X_all : a.Xn_all) + d.off_x;
+    const float *Y = a.Y_all + d.off_y;
+    const bool in = at < d.m, comp = r < Q;
+    const int i = in ? a.rord_all[d.off_x + at] : 0;
+    const int p0 = in ? row_ptr[i] : 0, cnt = in ? row_ptr[i + 1] - p0 : 0;
+    int most = cnt;                                  // longest of the wavefront's systems
+#pragma unroll
+    for (int o = S::T; o < WAVE; o <<= 1) most = max(most, __shfl_xor(most, o, WAVE));
+    most = __builtin_amdgcn_readfirstlane(most);
+    const float x = in && comp ? X[(size_t)i * Q + r] : 0.f;
+    float G[Q], rhs = 0.f;
+#pragma unroll
+    for (int k = 0; k < Q; ++k) G[k] = 0.f;
+    double e2 = 0.0;
+    // lane l of a 16-lane row holds the index and the values of sample l % U
+    // of a block; past the end a lane reads the slice's first sample (every
+    // slice in this launch has one) and its vectors are taken as 0
+    int jn;
+    float y[U][3], vn[3], vc[3];
+    const int su = lane % U;
+    auto load_index = [&](int e0) {
+        const int p = e0 + su < cnt ? p0 + e0 + su : 0;
+        jn = csr_col[p];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) vn[c] = csr_val[3 * (size_t)p + c];
+    };
+    auto load_block = [&]() {                        // the samples whose indices are in jn
+        block_u<U>([&](auto u) {
+            const float *yj = Y + (size_t)row_bcast<u.value>(jn) * 3 * Q + (comp ? r : 0);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) y[u.value][c] = yj[c * Q];
+        });
+    };
+    load_index(0);
+    load_block();
+    for (int e0 = 0; e0 < most; e0 += U) {
+        float yb[U][3];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) yb[u][c] = e0 + u < cnt && comp ? y[u][c] : 0.f;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) vc[c] = e0 + su < cnt ? vn[c] * inv_s0 : 0.f;
+        if (e0 + U < most) {
+            load_index(e0 + U);
+            load_block();
+        }
+        block_u<U>([&](auto uc) {
+            constexpr int u = uc.value;
+            float b[3][S::T / 16], mb[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                blocks_of<S::T>(yb[u][c], r, b[c]);
+                mb[c] = row_bcast<u>(vc[c]);
+            }
+            gram_add3<Q, S::T, 0>(G, yb[u], b);
+            rhs = __fadd_rn(rhs, fmaf(mb[2], yb[u][2], fmaf(mb[0], yb[u][0], __fmul_rn(mb[1], yb[u][1]))));
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {            // 0 past the end
+                const float e = mb[c] - tile_sum<S::T>(x * yb[u][c]);
+                e2 = fma((double)e, (double)e, e2);
+            }
+        });
+    }
+    double b[1] = {(double)rhs};
+    tile_solve<Q, 1>(G, in ? (double)a.lam * (double)max(1, 3 * cnt) : 1.0, b, r);
+    if (in && comp) Xn[(size_t)i * Q + r] = r < d.qr ? (float)b[0] : 0.f;
+    e2 = block_sum_d<ALS_NW>(r == 0 ? e2 : 0.0, red);
+    if (t == 0) a.e2[blockIdx.x] = e2;
+}
+
+// Column half-step: GRP columns of one slice per workgroup, their three
+// channels sharing a system; first the stop test on the residual slots.
+template <int Q>
+__global__ __launch_bounds__(ALS_THREADS) void k_als_cols(AlsArgs a, int it) {
+    using S = AlsShape<Q>;
+    constexpr int U = 16;                            // samples of a block
+    __shared__ double red[ALS_NW];
+    __shared__ int done_s;
+    const int blk = blockIdx.x / S::CSUB, sub = blockIdx.x % S::CSUB;
+    const int kk = block_slice(a.colp, a.count, blk);
+    const int s = __builtin_amdgcn_readfirstlane(a.ids[kk]);
+    AlsState *st = state_of(a.gsys, s);
+    const SliceDesc d = a.desc[s];
+    const int first_at = (blk - a.colp[kk]) * GADM_CB + sub * S::GRP;
+    if (first_at >= d.n) return;
+    // a slice that stops in this launch is marked by its first workgroup; the
+    // others find the same sum, so it does not matter which they see first
+    const int t = threadIdx.x, lane = t % WAVE, r = lane % S::T, g = lane / S::T;
+    if (t == 0) done_s = __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (done_s) return;
+    if (!(a.mode & 1) || first_at == 0) {
+        double e2 = 0.0;
+        for (int u = a.rowp[kk] * S::RSUB + t; u < a.rowp[kk + 1] * S::RSUB; u += ALS_THREADS) e2 += a.e2[u];
+        e2 = block_sum_d<ALS_NW>(e2, red);
+        const double err = sqrt(e2) / st->norm_m;
+        const bool stop = !(a.mode & 1) && err < (double)a.tol;
+        if (first_at == 0 && t == 0) {
+            st->resid = __float_as_int((float)err);
+            if (stop) {
+                st->iters = it;
+                __hip_atomic_store(&st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
-        r2 = block_sum_d(r2, red);
-        err = sqrt(r2) / normM;
-        if (!(mode & 1) && err < (double)tol) {
-            iters = it;
-            break;
+        if (stop) return;
+    }
+    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);
+    const int at = first_at + w * S::SYS + g;
+    const float inv_s0 = (float)(1.0 / st->s0);
+    const int32_t *col_ptr = a.col_ptr_all + d.off_colptr;
+    const int32_t *csc_row = a.csc_row_all + d.off_omega;
+    const float *csc_val = a.csc_val_all + 3 * d.off_omega;
+    const float *Xn = ((it & 1) ? a.X_all : a.Xn_all) + d.off_x;
+    float *Y = a.Y_all + d.off_y;
+    const bool in = at < d.n, comp = r < Q;
+    const int j = in ? a.cord_all[d.off_y + at] : 0;
+    const int p0 = in ? col_ptr[j] : 0, cnt = in ? col_ptr[j + 1] - p0 : 0;
+    int most = cnt;
+#pragma unroll
+    for (int o = S::T; o < WAVE; o <<= 1) most = max(most, __shfl_xor(most, o, WAVE));
+    most = __builtin_amdgcn_readfirstlane(most);
+    float G[Q], rhs[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < Q; ++k) G[k] = 0.f;
+    int jn;                                          // as in the row launch
+    float x[U], vn[3], vc[3];
+    const int su = lane % U;
+    auto load_index = [&](int e0) {
+        const int p = e0 + su < cnt ? p0 + e0 + su : 0;
+        jn = csc_row[p];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) vn[c] = csc_val[3 * (size_t)p + c];
+    };
+    auto load_block = [&]() {
+        block_u<U>([&](auto u) { x[u.value] = Xn[(size_t)row_bcast<u.value>(jn) * Q + (comp ? r : 0)]; });
+    };
+    load_index(0);
+    load_block();
+    for (int e0 = 0; e0 < most; e0 += U) {
+        float xb[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) xb[u] = e0 + u < cnt && comp ? x[u] : 0.f;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) vc[c] = e0 + su < cnt ? vn[c] * inv_s0 : 0.f;
+        if (e0 + U < most) {
+            load_index(e0 + U);
+            load_block();
         }
-        // ---- rows: x_i from the row's samples ----
-        for (int i = w; i < m; i += ALS_NW) {
-            float g[EPL];
+        block_u<U>([&](auto uc) {
+            constexpr int u = uc.value;
+            float b[S::T / 16];
+            blocks_of<S::T>(xb[u], r, b);
+            gram_add<Q, S::T, 0>(G, xb[u], b);
 #pragma unroll
-            for (int u = 0; u < EPL; ++u) g[u] = 0.f;
-            float rhs = 0.f;
-            const int p0 = row_ptr[i], p1 = row_ptr[i + 1];
-            for (int pb = p0; pb < p1; pb += ALS_B) {
-                const int nb = min(ALS_B, p1 - pb);
-                for (int e = lane; e < nb * 3 * Q; e += WAVE) {
-                    const int b = e / (3 * Q), o = e % (3 * Q);
-                    my.stage[e] = Y[(size_t)csr_col[pb + b] * 3 * Q + o];
-                }
-                wave_lds_sync();
-                for (int b = 0; b < nb; ++b) {
-                    const float *ys = my.stage + b * 3 * Q;
+            for (int c = 0; c < 3; ++c) rhs[c] = fmaf(xb[u], row_bcast<u>(vc[c]), rhs[c]);
+        });
+    }
+    double b[3] = {(double)rhs[0], (double)rhs[1], (double)rhs[2]};
+    tile_solve<Q, 3>(G, in ? (double)a.lam * (double)max(1, cnt) : 1.0, b, r);
+    if (in && comp) {
 #pragma unroll
-                    for (int u = 0; u < EPL; ++u) {
-                        const int e = lane + u * WAVE;
-                        if (e < Q * Q) {
-                            const int a = e / Q, c = e % Q;
-                            g[u] += ys[a] * ys[c] + ys[Q + a] * ys[Q + c] + ys[2 * Q + a] * ys[2 * Q + c];
-                        }
-                    }
-                    if (lane < Q) {
-                        const float *v = csr_val + 3 * (pb + b);
-                        rhs += (v[0] * inv_s0) * ys[lane] + (v[1] * inv_s0) * ys[Q + lane] +
-                               (v[2] * inv_s0) * ys[2 * Q + lane];
-                    }
-                }
-                wave_lds_sync();
-            }
-            const double shift = (double)lam * (double)max(1, 3 * (p1 - p0));
-#pragma unroll
-            for (int u = 0; u < EPL; ++u) {
-                const int e = lane + u * WAVE;
-                if (e < Q * Q) my.A[e] = (double)g[u] + (e / Q == e % Q ? shift : 0.0);
-            }
-            if (lane < Q) my.b[lane] = (double)rhs;
-            wave_lds_sync();
-            wave_chol_solve<Q>(my.A, my.b, 1, lane);
-            if (lane < Q) X[(size_t)i * Q + lane] = lane < qr ? (float)my.b[lane] : 0.f;
-            wave_lds_sync();
-        }
-        __threadfence_block();
-        __syncthreads();
-        // ---- columns: y_{c, j} for the three channels of column j ----
-        for (int j = w; j < n; j += ALS_NW) {
-            float g[EPL];
-#pragma unroll
-            for (int u = 0; u < EPL; ++u) g[u] = 0.f;
-            float r0 = 0.f, r1 = 0.f, r2c = 0.f;
-            const int p0 = col_ptr[j], p1 = col_ptr[j + 1];
-            for (int pb = p0; pb < p1; pb += ALS_B) {
-                const int nb = min(ALS_B, p1 - pb);
-                for (int e = lane; e < nb * Q; e += WAVE) {
-                    const int b = e / Q, o = e % Q;
-                    my.stage[e] = X[(size_t)csc_row[pb + b] * Q + o];
-                }
-                wave_lds_sync();
-                for (int b = 0; b < nb; ++b) {
-                    const float *xs = my.stage + b * Q;
-#pragma unroll
-                    for (int u = 0; u < EPL; ++u) {
-                        const int e = lane + u * WAVE;
-                        if (e < Q * Q) g[u] += xs[e / Q] * xs[e % Q];
-                    }
-                    if (lane < Q) {
-                        const float *v = csc_val + 3 * (pb + b);
-                        const float x = xs[lane];
-                        r0 += (v[0] * inv_s0) * x;
-                        r1 += (v[1] * inv_s0) * x;
-                        r2c += (v[2] * inv_s0) * x;
-                    }
-                }
-                wave_lds_sync();
-            }
-            const double shift = (double)lam * (double)max(1, p1 - p0);
-#pragma unroll
-            for (int u = 0; u < EPL; ++u) {
-                const int e = lane + u * WAVE;
-                if (e < Q * Q) my.A[e] = (double)g[u] + (e / Q == e % Q ? shift : 0.0);
-            }
-            if (lane < Q) {
-                my.b[lane] = (double)r0;
-                my.b[Q + lane] = (double)r1;
-                my.b[2 * Q + lane] = (double)r2c;
-            }
-            wave_lds_sync();
-            wave_chol_solve<Q>(my.A, my.b, 3, lane);
-            if (lane < Q) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    Y[(size_t)j * 3 * Q + c * Q + lane] = lane < qr ? (float)my.b[c * Q + lane] : 0.f;
-            }
-            wave_lds_sync();
-        }
-        __threadfence_block();
-        __syncthreads();
+        for (int c = 0; c < 3; ++c) Y[(size_t)j * 3 * Q + c * Q + r] = r < d.qr ? (float)b[c] : 0.f;
+    }
+}
+
+// the final X into the X region, statistics
+template <int Q>
+__global__ __launch_bounds__(ALS_THREADS) void k_als_final(AlsArgs a) {
+    const int s = __builtin_amdgcn_readfirstlane(a.ids[blockIdx.x]);
+    const AlsState *st = state_of(a.gsys, s);
+    const SliceDesc d = a.desc[s];
+    const int t = threadIdx.x;
+    if (st->iters & 1) {
+        const float *src = a.Xn_all + d.off_x;
+        float *dst = a.X_all + d.off_x;
+        for (int e = t; e < d.m * Q; e += ALS_THREADS) dst[e] = src[e];
     }
     if (t == 0) {
-        st[0] = iters;
-        if (!(mode & 1) && iters >= max_iter) st[1] |= VPLMC_SLICE_NOT_CONVERGED;
-        st[2] = __float_as_int((float)err);
+        int32_t *o = a.stats_all + 4 * s;
+        o[0] = st->iters;
+        if (st->zero)
+            o[1] |= VPLMC_SLICE_ALL_ZERO;
+        else if (!(a.mode & 1) && st->iters >= a.max_iter)
+            o[1] |= VPLMC_SLICE_NOT_CONVERGED;
+        o[2] = st->resid;
     }
 }
 
 template <int Q>
-int launch_als_q(hipStream_t st, size_t count, const int32_t *ids, const SliceDesc *desc, const vplmc_params &prm,
-                 const int32_t *row_ptr, const int32_t *csr_col, const float *csr_val, const int32_t *col_ptr,
-                 const int32_t *csc_row, const float *csc_val, float *X, float *Y, float *scale, int32_t *stats) {
+int launch_als_q(hipStream_t st, const AlsArgs &args, const vplmc_plan &plan, int grp, const int32_t *gblk_dev,
+                 double *e2) {
+    using S = AlsShape<Q>;
+    const size_t count = plan.groups[grp].size();
     if (count == 0) return VPLMC_OK;
-    const int32_t mode = ((prm.flags & VPLMC_FIXED_ITERS) ? 1 : 0) | ((prm.flags & VPLMC_GIVEN_INIT) ? 2 : 0);
-    hipLaunchKernelGGL(k_als<Q>, dim3((unsigned)count), dim3(ALS_THREADS), 0, st, desc, ids, prm.seed, prm.max_iter,
-                       mode, prm.tol, prm.lam, row_ptr, csr_col, csr_val, col_ptr, csc_row, csc_val, X, Y, scale,
-                       stats);
+    AlsArgs a = args;
+    a.count = (int32_t)count;
+    a.rowp = gblk_dev + plan.gblk_off[grp];
+    a.colp = a.rowp + count + 1;
+    a.e2 = e2 + ALS_E2_SLOTS * plan.ge2_base[grp];
+    static_assert(S::RSUB <= ALS_E2_SLOTS, "residual slots of a row block");
+    const unsigned nr = (unsigned)(plan.g_rows[grp] * S::RSUB), nc = (unsigned)(plan.g_cols[grp] * S::CSUB);
+    hipLaunchKernelGGL(k_als_init<Q>, dim3((unsigned)count), dim3(ALS_INIT_THREADS), 0, st, a);
+    VPLMC_HIP(hipGetLastError());
+    for (int it = 0; it < a.max_iter; ++it) {
+        hipLaunchKernelGGL(k_als_rows<Q>, dim3(nr), dim3(ALS_THREADS), 0, st, a, it);
+        VPLMC_HIP(hipGetLastError());
+        hipLaunchKernelGGL(k_als_cols<Q>, dim3(nc), dim3(ALS_THREADS), 0, st, a, it);
+        VPLMC_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_als_final<Q>, dim3((unsigned)count), dim3(ALS_THREADS), 0, st, a);
     VPLMC_HIP(hipGetLastError());
     return VPLMC_OK;
 }
@@ -316,17 +557,40 @@ int launch_als_q(hipStream_t st, size_t count, const int32_t *ids, const SliceDe
 }  // namespace
 
 int launch_als(hipStream_t st, const vplmc_plan &plan, const SliceDesc *desc, const int32_t *ids_dev,
-               const vplmc_params &prm, const int32_t *row_ptr, const int32_t *csr_col, const float *csr_val,
-               const int32_t *col_ptr, const int32_t *csc_row, const float *csc_val, float *X, float *Y, float *scale,
+               const int32_t *gblk_dev, char *gsys, double *e2, const vplmc_params &prm, const int32_t *row_ptr,
+               const int32_t *csr_col, const float *csr_val, const int32_t *col_ptr, const int32_t *csc_row,
+               const float *csc_val, float *X, float *Xn, float *Y, float *scale, int32_t *row_order, int32_t *col_order,
                int32_t *stats) {
     // with ALS every slice is in its rank bucket's global-memory group (2 b + 1)
     size_t base[9] = {0};
     for (int g = 0; g < 8; ++g) base[g + 1] = base[g] + plan.groups[g].size();
+    AlsArgs a;
+    a.desc = desc;
+    a.seed = prm.seed;
+    a.max_iter = prm.max_iter;
+    a.mode = ((prm.flags & VPLMC_FIXED_ITERS) ? 1 : 0) | ((prm.flags & VPLMC_GIVEN_INIT) ? 2 : 0);
+    a.tol = prm.tol;
+    a.lam = prm.lam;
+    a.row_ptr_all = row_ptr;
+    a.csr_col_all = csr_col;
+    a.csr_val_all = csr_val;
+    a.col_ptr_all = col_ptr;
+    a.csc_row_all = csc_row;
+    a.csc_val_all = csc_val;
+    a.X_all = X;
+    a.Xn_all = Xn;
+    a.Y_all = Y;
+    a.scale_all = scale;
+    a.rord_all = row_order;
+    a.cord_all = col_order;
+    a.stats_all = stats;
+    a.gsys = gsys;
     int rc = VPLMC_OK;
-#define VPLMC_ALS_BUCKET(B, Q)                                                                                   \
-    if (!rc)                                                                                                     \
-        rc = launch_als_q<Q>(st, plan.groups[2 * B + 1].size(), ids_dev + base[2 * B + 1], desc, prm, row_ptr,   \
-                             csr_col, csr_val, col_ptr, csc_row, csc_val, X, Y, scale, stats);
+#define VPLMC_ALS_BUCKET(B, Q)                                                      \
+    if (!rc) {                                                                      \
+        a.ids = ids_dev + base[2 * B + 1];                                          \
+        rc = launch_als_q<Q>(st, a, plan, 2 * B + 1, gblk_dev, e2);                 \
+    }
     VPLMC_ALS_BUCKET(3, 32)
     VPLMC_ALS_BUCKET(2, 16)
     VPLMC_ALS_BUCKET(1, 8)

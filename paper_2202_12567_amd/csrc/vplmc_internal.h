@@ -292,6 +292,7 @@ namespace vplmc {
 // bytes of a slice's system state (F and Inv in FP64, their FP32 copies, flags)
 constexpr int GADM_RB = 64;
 constexpr int GADM_CB = 256;
+constexpr int ALS_E2_SLOTS = 8;   // masked ALS: squared-residual slots per row block
 constexpr size_t GADM_SYS_BYTES = 2 * 32 * 32 * 8 + 2 * 32 * 32 * 4 + 256;
 // LDS budget of the LDS-resident ADM kernel (gfx950: 160 KiB per workgroup)
 constexpr size_t LDS_BYTES = 160 * 1024;
@@ -376,8 +377,9 @@ int launch_gadm_group(hipStream_t st, int q, const vplmc_plan &plan, int grp, co
                       const int32_t *col_ptr, const int32_t *csc_row, const float *csc_val, float *X, float *Xn,
                       float *Xp, float *Lam, float *Y, float *Yp, float *Pi, float *scale, int32_t *stats);
 int launch_als(hipStream_t st, const vplmc_plan &plan, const SliceDesc *desc, const int32_t *ids_dev,
-               const vplmc_params &prm, const int32_t *row_ptr, const int32_t *csr_col, const float *csr_val,
-               const int32_t *col_ptr, const int32_t *csc_row, const float *csc_val, float *X, float *Y, float *scale,
+               const int32_t *gblk_dev, char *gsys, double *e2, const vplmc_params &prm, const int32_t *row_ptr,
+               const int32_t *csr_col, const float *csr_val, const int32_t *col_ptr, const int32_t *csc_row,
+               const float *csc_val, float *X, float *Xn, float *Y, float *scale, int32_t *row_order, int32_t *col_order,
                int32_t *stats);
 int launch_reduce(hipStream_t st, const vplmc_plan &plan, const SliceDesc *desc, const int32_t *pt_ids,
                   const float *X, const float *Y, const float *scale, int32_t n_points, float *radiance);
