@@ -1429,7 +1429,7 @@ int vplmc_mlp_grad(vplmc_ctx *ctx, const float *params, int64_t rows, const floa
     int rc = mlp_scratch(rows, scratch, scratch_bytes, &y, &dy, &cache, &g);
     if (rc) return rc;
     VPLMC_HIP(hipSetDevice(ctx->device));
-    return launch_mlp_grad(ctx->stream, params, rows, features, dy_in, grad, y, cache);
+    return launch_mlp_grad(ctx->stream, params, rows, features, dy_in, grad, cache);
 }
 
 int vplmc_mlp_adam(vplmc_ctx *ctx, float *params, const float *grad, float *m, float *v, int32_t step, float lr) {

@@ -352,7 +352,7 @@ int launch_mlp_train_step(hipStream_t st, float *params, float *m, float *v, int
                           const float *features, const float *pstar, int32_t n_groups, const int32_t *group_off,
                           float *y, float *dy, float *grad, float *loss, float *cache);
 int launch_mlp_grad(hipStream_t st, const float *params, int64_t rows, const float *features, const float *dy,
-                    float *grad, float *y, float *cache);
+                    float *grad, float *cache);
 int launch_mlp_adam(hipStream_t st, float *params, const float *grad, float *m, float *v, int32_t step, float lr);
 int launch_targets(hipStream_t st, const vplmc_plan &plan, const SliceDesc *desc, const Bvh &bvh,
                    const vplmc_points &pts, const float *lights, int32_t n_lights, const int32_t *pt_ids,
