@@ -438,7 +438,7 @@ int vplmc_eval_pairs(vplmc_ctx *ctx, const vplmc_points *points, const vplmc_lig
 /* Brute-force column sum over every light (the paper's reference images,
  * Sec. 6): out double[n_out][3] for points point_ids[0 .. n_out) (or points
  * 0 .. n_out-1 if point_ids is NULL).  FP32 entries, FP64 sums; partial sums
- * over chunks of 2048 lights are combined with FP64 atomics, so the last
+ * over chunks of lights are combined with FP64 atomics, so the last
  * bits may vary between runs. */
 int vplmc_brute_force(vplmc_ctx *ctx, const vplmc_points *points, const vplmc_lights *lights,
                       int32_t n_out, const int32_t *point_ids, const vplmc_params *params,

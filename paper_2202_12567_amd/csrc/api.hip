@@ -1381,7 +1381,7 @@ int vplmc_brute_force(vplmc_ctx *ctx, const vplmc_points *points, const vplmc_li
     int rc = check_params(params);
     if (rc) return rc;
     VPLMC_HIP(hipSetDevice(ctx->device));
-    return launch_brute_force(ctx->stream, ctx->bvh, *points, *lights, n_out, point_ids, *params, out);
+    return launch_brute_force(ctx->stream, ctx->bvh, *points, *lights, n_out, point_ids, *params, ctx->n_cu, out);
 }
 
 int vplmc_set_proposal(vplmc_ctx *ctx, const float *params) {

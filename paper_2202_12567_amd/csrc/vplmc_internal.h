@@ -393,5 +393,5 @@ int launch_full_matrix(hipStream_t st, const Bvh &bvh, const vplmc_points &pts, 
 int launch_eval_pairs(hipStream_t st, const Bvh &bvh, const vplmc_points &pts, const vplmc_lights &l,
                       int64_t n, const int32_t *pid, const int32_t *lid, const vplmc_params &prm, float *out);
 int launch_brute_force(hipStream_t st, const Bvh &bvh, const vplmc_points &pts, const vplmc_lights &l,
-                       int32_t n_out, const int32_t *pid, const vplmc_params &prm, double *out);
+                       int32_t n_out, const int32_t *pid, const vplmc_params &prm, int n_cu, double *out);
 }  // namespace vplmc
