@@ -257,12 +257,30 @@ int vplmc_set_occluders(vplmc_ctx *ctx, int32_t n, const float *cx, const float 
     ctx->bvh = Bvh{};
     if (n == 0) return VPLMC_OK;
     const size_t nb = align256(nodes.size() * sizeof(BvhNode));
-    const size_t sb = sph.size() * sizeof(float);
+    const size_t sb = align256(sph.size() * sizeof(float));
+    // boxes of the groups, padded beyond any rounding of a sphere's own box
+    const int32_t n_groups = (n + BVH_GROUP - 1) / BVH_GROUP;
+    std::vector<float> groups(8 * (size_t)n_groups, 0.f);
+    for (int32_t g = 0; g < n_groups; ++g)
+        for (int k = 0; k < 3; ++k) {
+            double lo = INFINITY, hi = -INFINITY;
+            for (int32_t e = g * BVH_GROUP; e < std::min(n, (g + 1) * BVH_GROUP); ++e) {
+                const double c = sph[4 * (size_t)e + k], rad = sph[4 * (size_t)e + 3];
+                lo = std::min(lo, c - rad - 1e-5 * (fabs(c) + rad));
+                hi = std::max(hi, c + rad + 1e-5 * (fabs(c) + rad));
+            }
+            groups[8 * (size_t)g + k] = (float)lo;
+            groups[8 * (size_t)g + 4 + k] = (float)hi;
+        }
+    const size_t gb = groups.size() * sizeof(float);
     void *mem = nullptr;
-    if (hipMalloc(&mem, nb + sb) != hipSuccess) return set_error(VPLMC_ENOMEM, "BVH allocation failed");
+    if (hipMalloc(&mem, nb + sb + gb) != hipSuccess) return set_error(VPLMC_ENOMEM, "BVH allocation failed");
     ctx->bvh_mem = mem;
     VPLMC_HIP(hipMemcpy(mem, nodes.data(), nodes.size() * sizeof(BvhNode), hipMemcpyHostToDevice));
-    VPLMC_HIP(hipMemcpy(static_cast<char *>(mem) + nb, sph.data(), sb, hipMemcpyHostToDevice));
+    VPLMC_HIP(hipMemcpy(static_cast<char *>(mem) + nb, sph.data(), sph.size() * sizeof(float), hipMemcpyHostToDevice));
+    VPLMC_HIP(hipMemcpy(static_cast<char *>(mem) + nb + sb, groups.data(), gb, hipMemcpyHostToDevice));
+    ctx->bvh.groups = reinterpret_cast<const float4 *>(static_cast<char *>(mem) + nb + sb);
+    ctx->bvh.n_groups = n_groups;
     ctx->bvh.nodes = static_cast<const BvhNode *>(mem);
     ctx->bvh.spheres = reinterpret_cast<const float4 *>(static_cast<char *>(mem) + nb);
     ctx->bvh.n_nodes = (int32_t)nodes.size();
@@ -342,7 +360,12 @@ int vplmc_sbvh_build(int32_t n, const float *v, int32_t max_nodes, float *box, i
 // arithmetic): validates that every node but the root is the child of
 // exactly one later split node, and lays out left, right, parent, height,
 // smallest leaf, the split nodes ordered by (height, id) and the level offsets.
-static int build_tree(const vplmc_coarsen *co, std::vector<int32_t> &tree, int32_t &height_max) {
+//
+// Top of the tree: a split node is opened when the draws
+// expected below it are at least COARSEN_TOP_DRAWS rows' worth; front holds the
+// unopened nodes below opened ones, above the opened ones.
+static int build_tree(const vplmc_coarsen *co, double mean_rows, std::vector<int32_t> &tree, int32_t &height_max,
+                      int32_t &n_front) {
     const int ng = co->n_leaves, ns = ng - 1, NC = 2 * ng - 1;
     if (ns > 0 && (!co->left || !co->right)) return set_error(VPLMC_EINVAL, "tree arrays must be non-NULL");
     std::vector<int32_t> parent(NC, -1), height(NC, 0), min_leaf(NC);
@@ -365,6 +388,37 @@ static int build_tree(const vplmc_coarsen *co, std::vector<int32_t> &tree, int32
     for (int h = 1; h <= height_max; ++h) level_off[h] += level_off[h - 1];
     std::vector<int32_t> fill(level_off.begin(), level_off.end());
     for (int k = 0; k < ns; ++k) order[fill[height[ng + k] - 1]++] = ng + k;
+    // leaves in depth-first order (left before right): the leaves under every node are consecutive
+    // with their depths
+    std::vector<int32_t> dfs, dfs_depth;
+    std::vector<std::pair<int32_t, int32_t>> stack(1, {NC - 1, 0});
+    while (!stack.empty()) {
+        const auto [f, dep] = stack.back();
+        stack.pop_back();
+        if (f < ng) {
+            dfs.push_back(f);
+            dfs_depth.push_back(dep);
+        } else {
+            stack.push_back({co->right[f - ng], dep + 1});
+            stack.push_back({co->left[f - ng], dep + 1});
+        }
+    }
+    std::vector<int32_t> below(NC, 1), tidx(NC, -1), front(1, NC - 1), above;
+    for (int k = 0; k < ns; ++k) below[ng + k] = below[co->left[k]] + below[co->right[k]];
+    for (size_t at = 0; at < front.size();) {
+        const int f = front[at];
+        if (f >= ng && (int)front.size() < COARSEN_TOP_MAX &&
+            (double)co->pixels * below[f] >= COARSEN_TOP_DRAWS * mean_rows * ng) {
+            above.push_back(f);
+            front[at] = co->left[f - ng];
+            front.push_back(co->right[f - ng]);
+        } else {
+            ++at;
+        }
+    }
+    n_front = (int32_t)front.size();
+    for (int k = 0; k < n_front; ++k) tidx[front[k]] = k;
+    for (size_t k = 0; k < above.size(); ++k) tidx[above[k]] = n_front + (int32_t)k;
     tree.clear();
     tree.insert(tree.end(), co->left, co->left + ns);
     tree.insert(tree.end(), co->right, co->right + ns);
@@ -373,6 +427,11 @@ static int build_tree(const vplmc_coarsen *co, std::vector<int32_t> &tree, int32
     tree.insert(tree.end(), min_leaf.begin(), min_leaf.end());
     tree.insert(tree.end(), order.begin(), order.end());
     tree.insert(tree.end(), level_off.begin(), level_off.end());
+    tree.insert(tree.end(), dfs.begin(), dfs.end());
+    tree.insert(tree.end(), dfs_depth.begin(), dfs_depth.end());
+    tree.insert(tree.end(), tidx.begin(), tidx.end());
+    tree.insert(tree.end(), front.begin(), front.end());
+    tree.insert(tree.end(), above.begin(), above.end());
     return VPLMC_OK;
 }
 
@@ -388,6 +447,11 @@ static CoarsenTree tree_view(const vplmc_plan *plan, const int32_t *dev) {
     t.min_leaf = dev + 2 * ns + 2 * NC;
     t.order = dev + 2 * ns + 3 * NC;
     t.level_off = dev + 3 * ns + 3 * NC;
+    t.dfs = t.level_off + t.height_max + 1;
+    t.depth = t.dfs + ng;
+    t.tidx = t.depth + ng;
+    t.front = t.tidx + NC;
+    t.n_front = plan->n_front;
     return t;
 }
 
@@ -420,7 +484,8 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
         plan->n_lights = 2 * co->n_leaves - 1;
         plan->pixels = co->pixels;
         plan->bound = co->bound;
-        if ((rc = build_tree(co, plan->tree, plan->height_max))) {
+        const double mean_rows = n_slices > 0 ? std::max(1.0, (double)pt_offsets[n_slices] / n_slices) : 1.0;
+        if ((rc = build_tree(co, mean_rows, plan->tree, plan->height_max, plan->n_front))) {
             delete plan;
             return rc;
         }
@@ -585,13 +650,30 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
         bytes[VPLMC_R_NODE_MEMBERS] = NC * 4;
         bytes[R_TREE] = plan->tree.size() * 4;
         bytes[R_NODE_KD] = 2 * ns * 4;
-        bytes[R_LEAF_KPRE] = (ng + 1) * 8;
+        bytes[R_LEAF_KPRE] = 2 * (ng + 1) * 8;
         bytes[R_NODE_COST] = S * ns * 4;
         bytes[R_NODE_EFF] = S * ns * 4;
         bytes[R_NODE_MERGED] = S * ns;
         bytes[R_NODE_TOP] = S * NC * 4;
         bytes[R_LEAF_COL] = S * ng * 4;
         bytes[R_ZETA] = S * (int64_t)co->pixels * 2;
+        if (plan->n_front > 1) {
+            // runs of slices whose table of top lights fits the budget (a slice has at most 65,535 rows: 268 MB)
+            const int64_t cap = COARSEN_TOP_BYTES / (16 * plan->n_front);
+            int64_t most = 0, first = 0;
+            plan->top_runs.assign(1, 0);
+            for (int s = 0; s < n_slices; ++s) {
+                const int64_t end = plan->desc[s].off_row - s + plan->desc[s].m;   // rows up to and with slice s
+                if (end - first > cap && s > plan->top_runs.back()) {
+                    plan->top_runs.push_back(s);
+                    first = plan->desc[s].off_row - s;
+                }
+                most = std::max(most, end - first);
+            }
+            plan->top_runs.push_back(n_slices);
+            bytes[R_TOP_MAP] = 2 * (int64_t)plan->n_front * 4;
+            bytes[R_TOP] = most * plan->n_front * 16;
+        }
     }
     bytes[VPLMC_R_LIGHTS] = 9 * NC * 4;
     bytes[VPLMC_R_REP] = NC * 4;
@@ -811,9 +893,12 @@ int vplmc_render(vplmc_ctx *ctx, const vplmc_plan *plan, const vplmc_points *poi
         cs.dropped = kd + ns;
         int64_t *kpre = region<int64_t>(ws, plan, R_LEAF_KPRE);
         cs.kpre = kpre;
+        cs.dpre = kpre + ng + 1;
+        cs.top_map = region<int32_t>(ws, plan, R_TOP_MAP);
+        cs.top_val = region<float4>(ws, plan, R_TOP);
         cs.zeta = region<uint16_t>(ws, plan, R_ZETA);
-        if ((rc = launch_leaf_draws(st, ng, lights, plan->pixels, region<int32_t>(ws, plan, VPLMC_R_LEAF_DRAWS),
-                                    kpre)))
+        if ((rc = launch_leaf_draws(st, tr, kd, lights, plan->pixels, region<int32_t>(ws, plan, VPLMC_R_LEAF_DRAWS), kpre,
+                                    region<int32_t>(ws, plan, R_TOP_MAP))))
             return rc;
         if ((rc = ph.mark(VPLMC_PH_COARSEN))) return rc;
         if ((rc = launch_fill_u32(st, reinterpret_cast<uint32_t *>(cs.eps), (size_t)S * ns, 0u))) return rc;

@@ -84,10 +84,21 @@ __global__ __launch_bounds__(CT) void k_node_table(CoarsenTree tr, const int32_t
     }
 }
 
-// k_x = floor(K Q_x / sum Q) over the leaves, and its exclusive prefix
-// (kpre[n_g] = the draws per slice before the cap at m').
-__global__ __launch_bounds__(CT) void k_leaf_draws(int32_t ng, const float *__restrict__ lights, int64_t K,
-                                                   int32_t *quota, int64_t *kpre) {
+// k_x = floor(K Q_x / sum Q) over the leaves, and its exclusive prefix in leaf
+// order (kpre[0 .. n_g]; kpre[n_g] = the draws per slice before the cap at m')
+// and in depth-first order (the n_g + 1 values after it).  Also, per node of
+// the top of the tree, the front node whose light it has (the kept children
+// down to one).
+__global__ __launch_bounds__(CT) void k_leaf_draws(CoarsenTree tr, const int32_t *__restrict__ kept,
+                                                   const float *__restrict__ lights, int64_t K, int32_t *quota,
+                                                   int64_t *kpre, int32_t *__restrict__ top_map) {
+    const int ng = tr.n_leaves;
+    if (tr.n_front > 1)
+        for (int k = threadIdx.x; k < 2 * tr.n_front - 1; k += CT) {
+            int f = tr.front[k];
+            while (tr.tidx[f] >= tr.n_front) f = kept[f - ng];
+            top_map[k] = tr.tidx[f];
+        }
     __shared__ double dmax[CT / WAVE];
     __shared__ unsigned long long qsum[CT / WAVE];
     __shared__ uint32_t sm[CT / WAVE];
@@ -118,24 +129,32 @@ __global__ __launch_bounds__(CT) void k_leaf_draws(int32_t ng, const float *__re
     __syncthreads();
     unsigned long long Q = 0;
     for (int k = 0; k < CT / WAVE; ++k) Q += qsum[k];
-    for (int x0 = 0; x0 < ng; x0 += CT) {
-        const int x = x0 + t;
-        uint32_t kx = 0;
-        if (x < ng) {
-            const uint64_t qx = quantise(total_t(lights[6 * N + x], lights[7 * N + x], lights[8 * N + x]), tmax);
-            kx = (uint32_t)(((uint64_t)K * qx) / (uint64_t)Q);
-            quota[x] = (int32_t)kx;
+    for (int x = t; x < ng; x += CT) {
+        const uint64_t qx = quantise(total_t(lights[6 * N + x], lights[7 * N + x], lights[8 * N + x]), tmax);
+        quota[x] = (int32_t)(((uint64_t)K * qx) / (uint64_t)Q);
+    }
+    __threadfence_block();
+    __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {
+        int64_t *pre = kpre + pass * (ng + 1);
+        for (int x0 = 0; x0 < ng; x0 += CT) {
+            const int x = x0 + t;
+            // a chunk of CT quotas sums to at most K < 2^31
+            const uint32_t kx = x < ng ? (uint32_t)quota[pass ? tr.dfs[x] : x] : 0u;
+            uint32_t tot;
+            const uint32_t ex = block_excl_scan(kx, &tot, sm);
+            const unsigned long long c = carry_s;
+            if (x < ng) pre[x] = (int64_t)(c + ex);
+            __syncthreads();
+            if (t == 0) carry_s = c + tot;
+            __syncthreads();
         }
-        // a chunk of CT quotas sums to at most K < 2^31
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan(kx, &tot, sm);
-        const unsigned long long c = carry_s;
-        if (x < ng) kpre[x] = (int64_t)(c + ex);
-        __syncthreads();
-        if (t == 0) carry_s = c + tot;
+        if (t == 0) {
+            pre[ng] = (int64_t)carry_s;
+            carry_s = 0;
+        }
         __syncthreads();
     }
-    if (t == 0) kpre[ng] = (int64_t)carry_s;
 }
 
 // merge key of split node f: eff bits, height, id (eff >= 0, so its bits order as the value)
@@ -382,8 +401,9 @@ int launch_node_table(hipStream_t st, const CoarsenTree &tr, const int32_t *cut_
     return VPLMC_OK;
 }
 
-int launch_leaf_draws(hipStream_t st, int32_t ng, const float *lights, int64_t K, int32_t *quota, int64_t *kpre) {
-    hipLaunchKernelGGL(k_leaf_draws, dim3(1), dim3(CT), 0, st, ng, lights, K, quota, kpre);
+int launch_leaf_draws(hipStream_t st, const CoarsenTree &tr, const int32_t *kept, const float *lights, int64_t K,
+                      int32_t *quota, int64_t *kpre, int32_t *top_map) {
+    hipLaunchKernelGGL(k_leaf_draws, dim3(1), dim3(CT), 0, st, tr, kept, lights, K, quota, kpre, top_map);
     VPLMC_HIP(hipGetLastError());
     return VPLMC_OK;
 }

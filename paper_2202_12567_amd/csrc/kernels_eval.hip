@@ -154,6 +154,152 @@ __device__ __forceinline__ bool shade(const Bvh &bvh, const PointData &q, const 
     return shade_in(BvhGlobal<KIND>{bvh}, bvh.n_nodes, q, L, r_min2, eps, o0, o1, o2);
 }
 
+// LDS written by some lanes of a wavefront and then read by others
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// minimum over the wavefront, uniform
+__device__ __forceinline__ float wave_min(float v) {
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true)));
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true)));
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true)));
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, true)));
+    const int b = __float_as_int(v);
+    return fminf(fminf(__int_as_float(__builtin_amdgcn_readlane(b, 0)), __int_as_float(__builtin_amdgcn_readlane(b, 16))),
+                 fminf(__int_as_float(__builtin_amdgcn_readlane(b, 32)), __int_as_float(__builtin_amdgcn_readlane(b, 48))));
+}
+
+// Shadow segments of a whole wavefront against the spheres near their common
+// shaft.  The segments of lanes with `want` run from o, inside the box A of
+// their origins, to y, inside the box B of their ends; at parameter t every
+// one of them is inside the box between A and B at t, so a sphere can only be
+// met if its box overlaps that moving box for some t in [0, 1], six linear
+// conditions on t.  The lanes test a box each: the groups of BVH_GROUP
+// consecutive (hence close) spheres, 64 at a time, then the spheres of the
+// groups that pass, two groups at a time; the spheres that pass are listed in
+// LDS, and every lane tests its own segment against the list exactly as a BVH
+// leaf does.  All boxes are padded beyond FP32 rounding, so the list holds
+// every sphere that any of the segments meets and the answer is that of the
+// traversal.  It pays where the segments of a wavefront are alike: rows of one
+// slice against one light or the lights below one tree node.  Returns 1
+// (occluded), 0 (not), or -1 for every lane if the list overflows.  All 64
+// lanes call.
+constexpr int SHAFT_CAP = 128;
+__device__ int occluded_shaft(const Bvh &b, float4 *list, bool want, P3 o, P3 y) {
+    const int lane = threadIdx.x & 63;
+    if (b.n_groups == 0 || __ballot(want) == 0) return 0;
+    const float of[3] = {o.x, o.y, o.z}, yf[3] = {y.x, y.y, y.z};
+    float alo[3], ahi[3], ilo[3], ihi[3], slo[3], shi[3];   // lines of the lower and upper box sides: start, 1 / slope, sign
+    float blo[3], bhi[3], big = 0.f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        alo[k] = wave_min(want ? of[k] : INFINITY);
+        ahi[k] = -wave_min(want ? -of[k] : INFINITY);
+        blo[k] = wave_min(want ? yf[k] : INFINITY);
+        bhi[k] = -wave_min(want ? -yf[k] : INFINITY);
+        big = fmaxf(fmaxf(big, fmaxf(fabsf(alo[k]), fabsf(ahi[k]))), fmaxf(fabsf(blo[k]), fabsf(bhi[k])));
+    }
+    const float pad = 1e-5f * big;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const float dl = blo[k] - alo[k], dh = bhi[k] - ahi[k];
+        alo[k] -= pad;
+        ahi[k] += pad;
+        ilo[k] = 1.0f / (fabsf(dl) > 1e-20f ? dl : copysignf(1e-20f, dl));
+        ihi[k] = 1.0f / (fabsf(dh) > 1e-20f ? dh : copysignf(1e-20f, dh));
+        slo[k] = ilo[k] > 0.f ? -INFINITY : INFINITY;
+        shi[k] = ihi[k] > 0.f ? -INFINITY : INFINITY;
+    }
+    // does the box [lo, hi] overlap the moving box at some t in [0, 1]:
+    // alo + t dl <= hi and ahi + t dh >= lo on every axis
+    auto meets = [&](const float (&lo)[3], const float (&hi)[3]) {
+        float t0 = -1e-5f, t1 = 1.0f + 1e-5f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float u = (hi[k] - alo[k]) * ilo[k];        // upper bound of t on a rising side, lower on a falling one
+            t1 = fminf(t1, fmaxf(u, slo[k]));
+            t0 = fmaxf(t0, fminf(u, slo[k]));
+            const float v = (lo[k] - ahi[k]) * ihi[k];
+            t0 = fmaxf(t0, fminf(v, -shi[k]));
+            t1 = fminf(t1, fmaxf(v, -shi[k]));
+        }
+        return t0 <= t1 + 1e-5f;
+    };
+    int count = 0;
+    for (int g0 = 0; g0 < b.n_groups; g0 += 64) {
+        bool in = false;
+        if (g0 + lane < b.n_groups) {
+            const float4 l4 = b.groups[2 * (g0 + lane)], h4 = b.groups[2 * (g0 + lane) + 1];
+            const float lo[3] = {l4.x, l4.y, l4.z}, hi[3] = {h4.x, h4.y, h4.z};
+            in = meets(lo, hi);
+        }
+        unsigned long long mask = __ballot(in);
+        while (mask) {
+            const int ga = g0 + __ffsll(mask) - 1;
+            mask &= mask - 1;
+            const int gb = mask ? g0 + __ffsll(mask) - 1 : -1;
+            mask = mask ? mask & (mask - 1) : 0;
+            const int e = (lane < 32 ? ga : gb) * BVH_GROUP + lane % 32;
+            bool hit = false;
+            float4 sp = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (e >= 0 && e < b.n_spheres) {
+                sp = b.spheres[e];
+                const float rr = fmaf(1e-6f, fabsf(sp.x) + fabsf(sp.y) + fabsf(sp.z), 1.00001f * sp.w);
+                const float lo[3] = {sp.x - rr, sp.y - rr, sp.z - rr}, hi[3] = {sp.x + rr, sp.y + rr, sp.z + rr};
+                hit = meets(lo, hi);
+            }
+            const unsigned long long hits = __ballot(hit);
+            const int at = count + __popcll(hits & ((1ull << lane) - 1));
+            if (hit && at < SHAFT_CAP) list[at] = sp;
+            count += __popcll(hits);
+        }
+    }
+    if (count > SHAFT_CAP) return -1;
+    wave_lds_sync();
+    const P3 D = sub(y, o);
+    const float inv_dd = 1.0f / dot(D, D);
+    bool occ = false;
+    for (int k0 = 0; k0 < count; k0 += 8) {
+        for (int k = k0; k < min(count, k0 + 8); ++k) {
+            const float4 sp4 = list[k];
+            const P3 oc = {sp4.x - o.x, sp4.y - o.y, sp4.z - o.z};
+            const float t = fminf(fmaxf(dot(oc, D) * inv_dd, 0.0f), 1.0f);
+            const P3 p = {oc.x - t * D.x, oc.y - t * D.y, oc.z - t * D.z};
+            occ = occ || dot(p, p) < sp4.w * sp4.w;
+        }
+        if (__ballot(want && !occ) == 0) break;
+    }
+    wave_lds_sync();             // the next list overwrites this one
+    return want && occ ? 1 : 0;
+}
+
+// shade_in for a whole wavefront (all 64 lanes call; lanes without `on` get zeros)
+template <int KIND, typename S>
+__device__ __forceinline__ bool shade_wave(const Bvh &bvh, const S *staged, float4 *list, bool on, const PointData &q,
+                                           const Light &L, float r_min2, float eps, float &o0, float &o1, float &o2) {
+    if constexpr (KIND == 0) {
+        o0 = o1 = o2 = 0.f;
+        bool ray = false;
+        if (on) ray = entry_unoccluded(q, L, r_min2, o0, o1, o2);
+        const P3 o = {fmaf(eps, q.n.x, q.x.x), fmaf(eps, q.n.y, q.x.y), fmaf(eps, q.n.z, q.x.z)};
+        int occ = occluded_shaft(bvh, list, ray, o, L.y);
+        if (occ < 0) occ = ray && occluded_in(BvhGlobal<KIND>{bvh}, bvh.n_nodes, o, sub(L.y, o)) ? 1 : 0;
+        if (occ) o0 = o1 = o2 = 0.f;
+        return ray;
+    } else {
+        bool ray = false;
+        o0 = o1 = o2 = 0.f;
+        if (on) {
+            if (staged) ray = shade_in(*staged, bvh.n_nodes, q, L, r_min2, eps, o0, o1, o2);
+            else ray = shade<KIND>(bvh, q, L, r_min2, eps, o0, o1, o2);
+        }
+        return ray;
+    }
+}
+
 // adds a per-thread count into a device total: one atomic per wavefront
 __device__ __forceinline__ void add_count(unsigned long long *total, uint32_t v) {
 #pragma unroll
@@ -240,8 +386,9 @@ __global__ __launch_bounds__(256) void k_eval_omega(Bvh bvh, vplmc_points pts, c
 }
 
 // Merge errors of the per-slice light coarsening (Sec. 4).  One thread per
-// row draw (slice s, draw r; r < kpre[n_g]): the draw belongs to leaf x
-// (kpre[x] <= r < kpre[x + 1]) and is its k-th, k = r - kpre[x] < m'; its row
+// row draw (slice s, draw r; r < dpre[n_g]), draws in depth-first order of their
+// leaves x (dpre, the prefix of the draw counts in that order), so that the
+// lanes of a wavefront lie below one small subtree; draw k < m' of leaf x: its row
 // is the k-th image of leaf x's keyed permutation of [0, m') (4-round
 // Feistel, round function Philox(key = (seed, s), ctr = (R, round, TAG_ZETA,
 // x)) & mask, cycle-walked).  Walking from x to the root, the thread carries
@@ -266,12 +413,64 @@ __device__ __forceinline__ uint64_t feistel_zeta(uint64_t v, uint64_t seed, uint
 }
 
 
-// six wavefronts per SIMD (80 VGPRs): the walk's latency needs the occupancy;
-// at 83 VGPRs (five) the kernel ran 14% slower on the 1080p frame
+// The top of the tree, where the draws below a node outnumber the slice's rows
+// and the walk would evaluate the same (row, light) many times: every row of a
+// run of slices against the lights of the front nodes, once each.  Lanes are
+// consecutive rows of a slice against one light, so their shadow rays are alike.
+constexpr int TOP_LIGHTS = 8;    // front nodes per thread
 template <bool STAGED, int KIND>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_coarsen_eps(Bvh bvh, vplmc_points pts, const float *__restrict__ lights,
-                                                     const SliceDesc *__restrict__ desc, int64_t total, int64_t K,
-                                                     const int32_t *__restrict__ pt_ids, CoarsenTree tr,
+__global__ __launch_bounds__(256) void k_coarsen_top(Bvh bvh, vplmc_points pts, const float *__restrict__ lights,
+                                                     const SliceDesc *__restrict__ desc, int32_t s_first, int32_t s_end,
+                                                     int64_t row_first, int64_t rows, const int32_t *__restrict__ pt_ids,
+                                                     CoarsenTree tr, CoarsenSlices cs, float r_min2, float eps) {
+    extern __shared__ float4 stage[];
+    if (STAGED) {
+        const int nn = 2 * bvh.n_nodes, ns = bvh.n_spheres;
+        const float4 *nodes4 = reinterpret_cast<const float4 *>(bvh.nodes);
+        for (int k = threadIdx.x; k < nn + ns; k += blockDim.x) stage[k] = k < nn ? nodes4[k] : bvh.spheres[k - nn];
+        __syncthreads();
+    }
+    const BvhStaged<KIND> staged{stage, bvh.n_nodes};
+    __shared__ float4 lists[KIND == 0 ? 256 / 64 * SHAFT_CAP : 1];
+    float4 *list = lists + (KIND == 0 ? threadIdx.x / 64 * SHAFT_CAP : 0);
+    const int64_t R0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const bool act = R0 < rows;
+    const int64_t R = act ? R0 : rows - 1;
+    int lo = s_first, hi = s_end;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (desc[mid].off_row - mid - row_first <= R) lo = mid; else hi = mid;
+    }
+    const SliceDesc d = desc[lo];
+    const int64_t base = d.off_row - lo - row_first;
+    const int i = (int)(R - base);
+    const PointData q = load_point(pts, pt_ids[d.pt_off + i]);
+    float4 *out = cs.top_val + base * tr.n_front + i;
+    const size_t N = (size_t)(2 * tr.n_leaves - 1);
+    const int k1 = min(tr.n_front, (int)(blockIdx.y + 1) * TOP_LIGHTS);
+    for (int k = blockIdx.y * TOP_LIGHTS; k < k1; ++k) {
+        float o0, o1, o2;
+        const bool ray = shade_wave<KIND>(bvh, STAGED ? &staged : nullptr, list, act, q,
+                                          node_light(lights, N, tr.front[k], true), r_min2, eps, o0, o1, o2);
+        if (act) out[(int64_t)k * d.m] = make_float4(o0, o1, o2, ray ? 1.f : 0.f);
+    }
+}
+
+// All lanes of a wavefront are on one tree level at a time (deeper leaves start
+// earlier), so they meet the same node's light as soon as they are below it;
+// their shadow rays share a candidate list (occluded_shaft).  Lights of the top
+// of the tree come from k_coarsen_top's table.  Bound by VALU work (0.81 busy):
+// shading a third, shadow tests a third, the draws' permutation a ninth.
+// Measured on one MI355X, 1080p frame (3,069 slices, 32,768 draws, 16,384
+// leaves, 2,048 spheres): 154 ms with draws in leaf-id order, 135 depth-first,
+// 114 + 7.4 with the top of the tree evaluated once per row, 49.7 + 2.9 with
+// the shared candidate lists.  Measured and not kept: a wavefront walking the
+// BVH together with scalar loads (162), leaf tests postponed until few lanes
+// still walk (145-174), four wavefronts per SIMD (52.3; five and six alike).
+template <bool STAGED, int KIND>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_coarsen_eps(Bvh bvh, vplmc_points pts, const float *__restrict__ lights,
+                                                     const SliceDesc *__restrict__ desc, int32_t s_first, int64_t row_first,
+                                                     int64_t total, int64_t K, const int32_t *__restrict__ pt_ids, CoarsenTree tr,
                                                      CoarsenSlices cs, uint64_t seed, float r_min2, float eps,
                                                      unsigned long long *__restrict__ counts) {
     extern __shared__ float4 stage[];
@@ -287,50 +486,74 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     const int64_t kt = cs.kpre[ng];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     uint32_t n_eval = 0, n_ray = 0;
-    for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < total; g += stride) {
-        const int s = (int)(g / K);
-        const int64_t r = g - (int64_t)s * K;
-        if (r >= kt) continue;
+    const int lane = threadIdx.x & 63;
+    __shared__ float4 lists[KIND == 0 ? 256 / 64 * SHAFT_CAP : 1];
+    float4 *list = lists + (KIND == 0 ? threadIdx.x / 64 * SHAFT_CAP : 0);
+    for (int64_t base = blockIdx.x * (int64_t)blockDim.x + (threadIdx.x - lane); base < total; base += stride) {
+        const int64_t g = base + lane < total ? base + lane : total - 1;
+        const int sl = (int)(g / K), s = s_first + sl;
+        const int64_t r = g - (int64_t)sl * K;
         const SliceDesc d = desc[s];
+        // draw r of the slice in depth-first leaf order
         int lo = 0, hi = ng;
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
-            if (cs.kpre[mid] <= r) lo = mid; else hi = mid;
+            if (cs.dpre[mid] <= r) lo = mid; else hi = mid;
         }
-        const int x = lo;
-        const int64_t k = r - cs.kpre[x];
-        if (k >= d.m) continue;
+        const int x = tr.dfs[lo];
+        const int64_t k = r - cs.dpre[lo];
+        const bool act = base + lane < total && r < kt && k < d.m;
         // row of the draw
         const uint64_t m = (uint64_t)d.m;
-        int b = m > 1 ? 64 - __clzll((long long)(m - 1)) : 0;
-        b = b < 2 ? 2 : b;
-        const int h = (b + 1) / 2;
-        uint64_t e = feistel_zeta((uint64_t)k, seed, (uint64_t)s, (uint64_t)x, h);
-        while (e >= m) e = feistel_zeta(e, seed, (uint64_t)s, (uint64_t)x, h);
-        const int i = (int)e;
-        cs.zeta[g] = (uint16_t)i;
+        int i = 0;
+        if (act) {
+            int b = m > 1 ? 64 - __clzll((long long)(m - 1)) : 0;
+            b = b < 2 ? 2 : b;
+            const int h = (b + 1) / 2;
+            uint64_t e = feistel_zeta((uint64_t)k, seed, (uint64_t)s, (uint64_t)x, h);
+            while (e >= m) e = feistel_zeta(e, seed, (uint64_t)s, (uint64_t)x, h);
+            i = (int)e;
+            cs.zeta[(int64_t)s * K + cs.kpre[x] + k] = (uint16_t)i;
+        }
         const PointData q = load_point(pts, pt_ids[d.pt_off + i]);
-        float c0, c1, c2;
-        bool ray;
-        if (STAGED)
-            ray = shade_in(staged, bvh.n_nodes, q, node_light(lights, N, x, true), r_min2, eps, c0, c1, c2);
-        else
-            ray = shade<KIND>(bvh, q, node_light(lights, N, x, true), r_min2, eps, c0, c1, c2);
-        n_eval += 1;
-        n_ray += ray ? 1u : 0u;
+        // levels from the deepest leaf of the wavefront up, all lanes on one
+        // level: lanes below one node evaluate the same light
+        const int dep = act ? tr.depth[lo] : -1;
+        int level = dep;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) level = max(level, __shfl_xor(level, o, 64));
+        const float4 *top = cs.top_val + (d.off_row - s - row_first) * tr.n_front + i;   // the row's entry of front node k: top[k m]
         float *node_eps = cs.eps + (size_t)s * (ng - 1);
+        float c0 = 0.f, c1 = 0.f, c2 = 0.f;
         int c = x;
-        for (int f = tr.parent[x]; f >= 0; c = f, f = tr.parent[f]) {
+        for (level = __builtin_amdgcn_readfirstlane(level); level >= 0; --level) {
+            const bool on = level <= dep;
+            // the lane's leaf itself, then the other child of each ancestor
+            const bool first = level == dep, up = on && !first;
+            const int f = up ? tr.parent[c] : ng;
             const int kk = f - ng;
-            const int a = cs.kept[kk], bb = cs.dropped[kk];
+            const int a = up ? cs.kept[kk] : x, bb = up ? cs.dropped[kk] : x;
             const int other = c == a ? bb : a;
             float o0, o1, o2;
-            if (STAGED)
-                ray = shade_in(staged, bvh.n_nodes, q, node_light(lights, N, other, true), r_min2, eps, o0, o1, o2);
-            else
-                ray = shade<KIND>(bvh, q, node_light(lights, N, other, true), r_min2, eps, o0, o1, o2);
+            const int ti = tr.n_front > 1 && on ? tr.tidx[other] : -1;
+            bool ray = shade_wave<KIND>(bvh, STAGED ? &staged : nullptr, list, on && ti < 0, q,
+                                        node_light(lights, N, other, true), r_min2, eps, o0, o1, o2);
+            if (ti >= 0) {                       // in the top of the tree: evaluated by k_coarsen_top
+                const float4 v = top[(int64_t)cs.top_map[ti] * d.m];
+                o0 = v.x;
+                o1 = v.y;
+                o2 = v.z;
+                ray = v.w != 0.f;
+            }
+            if (!on) continue;
             n_eval += 1;
             n_ray += ray ? 1u : 0u;
+            if (first) {
+                c0 = o0;
+                c1 = o1;
+                c2 = o2;
+                continue;
+            }
             const bool kept_path = c == a;
             const float a0 = kept_path ? c0 : o0, a1 = kept_path ? c1 : o1, a2 = kept_path ? c2 : o2;
             const float b0 = kept_path ? o0 : c0, b1 = kept_path ? o1 : c1, b2 = kept_path ? o2 : c2;
@@ -344,6 +567,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
             c0 = a0;
             c1 = a1;
             c2 = a2;
+            c = f;
         }
     }
     if (counts) {
@@ -574,35 +798,42 @@ int launch_eval_omega(hipStream_t st, const Bvh &bvh, const vplmc_points &pts, c
     return VPLMC_OK;
 }
 
+template <bool STAGED, int KIND>
+static int coarsen_eps(hipStream_t st, const vplmc_plan &plan, const Bvh &bvh, size_t staged, const vplmc_points &pts,
+                       const float *lights, const SliceDesc *desc, const int32_t *pt_ids, const CoarsenTree &tr,
+                       const CoarsenSlices &cs, const vplmc_params &prm, int n_cu, unsigned long long *counts) {
+    const int threads = 256;
+    const float r_min2 = prm.r_min * prm.r_min;
+    const size_t runs = plan.n_front > 1 ? plan.top_runs.size() - 1 : 1;
+    for (size_t k = 0; k < runs; ++k) {
+        const int32_t s0 = plan.n_front > 1 ? plan.top_runs[k] : 0, s1 = plan.n_front > 1 ? plan.top_runs[k + 1] : plan.n_slices;
+        const int64_t row0 = plan.desc[s0].off_row - s0;
+        if (plan.n_front > 1) {
+            const int64_t rows = plan.desc[s1 - 1].off_row - (s1 - 1) + plan.desc[s1 - 1].m - row0;
+            hipLaunchKernelGGL((k_coarsen_top<STAGED, KIND>),
+                               dim3(blocks_for(rows, threads), (unsigned)((plan.n_front + TOP_LIGHTS - 1) / TOP_LIGHTS)),
+                               dim3(threads), staged, st, bvh, pts, lights, desc, s0, s1, row0, rows, pt_ids, tr, cs,
+                               r_min2, prm.ray_eps);
+            VPLMC_HIP(hipGetLastError());
+        }
+        const int64_t total = (int64_t)(s1 - s0) * plan.pixels;
+        const int64_t blocks = std::min<int64_t>(blocks_for(total, threads), (int64_t)EVAL_GRID_PER_CU * n_cu);
+        hipLaunchKernelGGL((k_coarsen_eps<STAGED, KIND>), dim3((unsigned)blocks), dim3(threads), staged, st, bvh, pts,
+                           lights, desc, s0, row0, total, (int64_t)plan.pixels, pt_ids, tr, cs, prm.seed, r_min2,
+                           prm.ray_eps, counts);
+        VPLMC_HIP(hipGetLastError());
+    }
+    return VPLMC_OK;
+}
+
 int launch_coarsen_eps(hipStream_t st, const vplmc_plan &plan, const Bvh &bvh, const vplmc_points &pts,
                        const float *lights, const SliceDesc *desc, const int32_t *pt_ids, const CoarsenTree &tr,
                        const CoarsenSlices &cs, const vplmc_params &prm, int n_cu, unsigned long long *counts) {
-    const int64_t total = (int64_t)plan.n_slices * plan.pixels;
-    if (total <= 0) return VPLMC_OK;
-    const int threads = 256;
-    const int64_t blocks = std::min<int64_t>(blocks_for(total, threads), (int64_t)EVAL_GRID_PER_CU * n_cu);
+    if (plan.n_slices <= 0 || plan.pixels <= 0) return VPLMC_OK;
     const size_t staged = ((size_t)2 * bvh.n_nodes + bvh.n_spheres) * sizeof(float4);
-    if (bvh.n_nodes > 0 && staged <= (size_t)EVAL_LDS_BYTES) {
-        if (bvh.kind == 1)
-            hipLaunchKernelGGL((k_coarsen_eps<true, 1>), dim3((unsigned)blocks), dim3(threads), staged, st, bvh, pts, lights,
-                               desc, total, (int64_t)plan.pixels, pt_ids, tr, cs, prm.seed, prm.r_min * prm.r_min,
-                               prm.ray_eps, counts);
-        else
-            hipLaunchKernelGGL((k_coarsen_eps<true, 0>), dim3((unsigned)blocks), dim3(threads), staged, st, bvh, pts, lights,
-                               desc, total, (int64_t)plan.pixels, pt_ids, tr, cs, prm.seed, prm.r_min * prm.r_min,
-                               prm.ray_eps, counts);
-    } else {
-        if (bvh.kind == 1)
-            hipLaunchKernelGGL((k_coarsen_eps<false, 1>), dim3((unsigned)blocks), dim3(threads), 0, st, bvh, pts, lights,
-                               desc, total, (int64_t)plan.pixels, pt_ids, tr, cs, prm.seed, prm.r_min * prm.r_min,
-                               prm.ray_eps, counts);
-        else
-            hipLaunchKernelGGL((k_coarsen_eps<false, 0>), dim3((unsigned)blocks), dim3(threads), 0, st, bvh, pts, lights,
-                               desc, total, (int64_t)plan.pixels, pt_ids, tr, cs, prm.seed, prm.r_min * prm.r_min,
-                               prm.ray_eps, counts);
-    }
-    VPLMC_HIP(hipGetLastError());
-    return VPLMC_OK;
+    const bool stage = bvh.kind == 1 && bvh.n_nodes > 0 && staged <= (size_t)EVAL_LDS_BYTES;   // spheres: occluded_shaft
+    auto run = stage ? coarsen_eps<true, 1> : (bvh.kind == 1 ? coarsen_eps<false, 1> : coarsen_eps<false, 0>);
+    return run(st, plan, bvh, stage ? staged : 0, pts, lights, desc, pt_ids, tr, cs, prm, n_cu, counts);
 }
 
 int launch_full_matrix(hipStream_t st, const Bvh &bvh, const vplmc_points &pts, const float *lights,

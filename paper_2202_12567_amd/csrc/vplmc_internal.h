@@ -90,7 +90,11 @@ struct Bvh {
     int32_t n_nodes = 0;
     int32_t n_spheres = 0;             // float4 records after the nodes
     int32_t kind = 0;
+    // kind 0: boxes of every BVH_GROUP consecutive spheres, two float4 each (lo, hi)
+    const float4 *groups = nullptr;
+    int32_t n_groups = 0;
 };
+constexpr int BVH_GROUP = 32;
 constexpr int32_t BVH_MAX_TRIANGLES = 1 << 24;
 
 // host build: spheres -> nodes + reordered spheres
@@ -143,6 +147,14 @@ struct EllView {
     int32_t *split;    // per (slice, column): the columns of more than one part, first nsplit entries
     int32_t *nsplit;   // per slice
 };
+// Top of the coarsening tree: nodes with at least this many draws expected
+// below them per row of a slice are opened, at most COARSEN_TOP_MAX front nodes.
+// Below that the draws of a node rarely repeat a row, so evaluating every row
+// costs more than it saves: 1080p frame, walk + table 49.7 + 2.9 ms at 1,
+// 49.4 + 5.7 at 0.4, 51.0 + 11.5 at 0.2.
+constexpr double COARSEN_TOP_DRAWS = 1.0;
+constexpr int COARSEN_TOP_MAX = 256;
+constexpr int64_t COARSEN_TOP_BYTES = 512ll << 20;   // of a run's table
 constexpr int ELL_LMAX = 64;      // longest part
 // uniform mass of the proposal's training target, in units of the slice's mean
 // column standard deviation: p*_j ~ sigma_j + PROPOSAL_TARGET_MIX mean(sigma)
@@ -184,13 +196,15 @@ enum {
     R_QUEUE,         // int32[8]: work-queue counters of the completion launches
     R_TREE,          // int32: the coarsening tree (uploaded with the plan)
     R_NODE_KD,       // int32 per split node: kept child, then dropped child
-    R_LEAF_KPRE,     // int64 per leaf + 1: prefix of the draw counts
+    R_LEAF_KPRE,     // int64 per leaf + 1, twice: prefix of the draw counts, in leaf and in depth-first order
     R_NODE_COST,     // float per (slice, split node)
     R_NODE_EFF,      // float per (slice, split node)
     R_NODE_MERGED,   // uint8 per (slice, split node)
     R_NODE_TOP,      // int32 per (slice, node)
     R_LEAF_COL,      // int32 per (slice, leaf)
     R_ZETA,          // uint16 per (slice, draw slot)
+    R_TOP_MAP,       // int32 per node of the top of the tree
+    R_TOP,           // float4 per (slice of a run, front node, row)
     R_COUNTS,        // uint64[4]: shadow rays of the entries, coarsening evaluations and rays, -
     R_GSYS,          // GADM_SYS_BYTES per slice: q x q systems and state of the global-memory completion
     R_GE2,           // double per row block of the global-memory slices: squared residual sums
@@ -207,6 +221,13 @@ struct CoarsenTree {
     const int32_t *height = nullptr, *min_leaf = nullptr; // per node (leaves: 0, itself)
     const int32_t *order = nullptr;                       // split nodes by (height, id)
     const int32_t *level_off = nullptr;                   // height_max + 1: order[level_off[h-1] .. level_off[h]) have height h
+    const int32_t *dfs = nullptr;                         // n_leaves: the leaves in depth-first order
+    // top of the tree: front[0 .. n_front) are the unopened nodes; tidx of a
+    // node is its index in front, n_front + k for the k-th opened node (after
+    // front in memory), -1 below
+    int32_t n_front = 0;
+    const int32_t *tidx = nullptr, *front = nullptr;
+    const int32_t *depth = nullptr;                       // n_leaves: ancestors of the leaf at each depth-first position
 };
 
 // Per-frame and per-slice state of the coarsening.
@@ -217,6 +238,9 @@ struct CoarsenSlices {
     int32_t *leaf_col = nullptr;                             // per (slice, leaf): its column
     const int32_t *kept = nullptr, *dropped = nullptr;       // per split node
     const int64_t *kpre = nullptr;                           // n_leaves + 1: prefix of the draw counts
+    const int64_t *dpre = nullptr;                           // the same over the leaves in depth-first order
+    const int32_t *top_map = nullptr;                        // per tidx: the front node whose light it has
+    float4 *top_val = nullptr;                               // per (slice of a run, front node, row): unit-intensity entry, ray cast
     uint16_t *zeta = nullptr;                                // per (slice, draw slot): row of the draw
 };
 
@@ -263,6 +287,8 @@ struct vplmc_plan {
     bool coarse = false;
     bool als = false;              // completion by per-row masked ALS (VPLMC_ALS)
     int32_t n_leaves = 0, height_max = 0, pixels = 0;
+    int32_t n_front = 0;           // front nodes of the top of the tree (1: no table)
+    std::vector<int32_t> top_runs; // slice runs whose top-light tables share the region, as boundaries
     double bound = 0.0;
     std::vector<int32_t> tree;     // left, right, parent, height, min_leaf, order, level_off
     int32_t pass1_ppm = 0, pass2_ppm = 0;
@@ -314,7 +340,8 @@ int launch_cluster_table(hipStream_t st, const vplmc_lights &v, const vplmc_cut 
 // light coarsening (kernels_coarsen.hip, kernels_eval.hip)
 int launch_node_table(hipStream_t st, const CoarsenTree &tr, const int32_t *cut_offsets, uint64_t seed, int32_t *rep,
                       float *lights, float *bbox, int32_t *members, int32_t *kept, int32_t *dropped);
-int launch_leaf_draws(hipStream_t st, int32_t ng, const float *lights, int64_t K, int32_t *quota, int64_t *kpre);
+int launch_leaf_draws(hipStream_t st, const CoarsenTree &tr, const int32_t *kept, const float *lights, int64_t K,
+                      int32_t *quota, int64_t *kpre, int32_t *top_map);
 int launch_coarsen_eps(hipStream_t st, const vplmc_plan &plan, const Bvh &bvh, const vplmc_points &pts,
                        const float *lights, const SliceDesc *desc, const int32_t *pt_ids, const CoarsenTree &tr,
                        const CoarsenSlices &cs, const vplmc_params &prm, int n_cu, unsigned long long *counts);
