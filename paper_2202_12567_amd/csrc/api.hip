@@ -594,8 +594,11 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
     // global-memory completion: row and column blocks of every slice, as prefixes
     // per group (the launch grids), and the squared-residual slot of each row block
     plan->gblk.clear();
-    int64_t e2b = 0;
+    int64_t e2b = 0, gpart = 0;
     for (int g = 1; g < 8; g += 2) {
+        int64_t blocks = 0;
+        for (int32_t sl : plan->groups[g]) blocks += ((int64_t)plan->desc[sl].n + GADM_CB - 1) / GADM_CB;
+        plan->g_cb[g] = blocks < GADM_CB_FEW ? GADM_CB_SMALL : GADM_CB;
         plan->gblk_off[g] = (int64_t)plan->gblk.size();
         int64_t r = 0, c = 0;
         plan->gblk.push_back(0);
@@ -605,13 +608,16 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
         }
         plan->gblk.push_back(0);
         for (int32_t sl : plan->groups[g]) {
-            c += ((int64_t)plan->desc[sl].n + GADM_CB - 1) / GADM_CB;
+            c += ((int64_t)plan->desc[sl].n + plan->g_cb[g] - 1) / plan->g_cb[g];
             plan->gblk.push_back((int32_t)c);
         }
         plan->g_rows[g] = r;
         plan->g_cols[g] = c;
         plan->ge2_base[g] = e2b;
         e2b += r;
+        plan->gpart_base[g] = gpart;
+        const int64_t q = 4 << (g / 2);
+        if (!plan->als) gpart += (2 * r + c) * q * q;
     }
     plan->tot1 = o1;
     plan->tot2 = o2;
@@ -699,6 +705,7 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
     bool any_global = false;
     for (int g = 1; g < 8; g += 2) any_global = any_global || !plan->groups[g].empty();
     bytes[R_GSYS] = any_global ? (size_t)S * GADM_SYS_BYTES : 0;
+    bytes[R_GPART] = (size_t)gpart * 4;
     bytes[R_GE2] = (size_t)e2b * 8 * (plan->als ? ALS_E2_SLOTS : 1);
     bytes[R_COLW_PREFIX] = oc * 8;
     bytes[R_BITMAP] = obm * 4;
@@ -989,7 +996,7 @@ int vplmc_render(vplmc_ctx *ctx, const vplmc_plan *plan, const vplmc_points *poi
                         region<int32_t>(ws, plan, R_YP), stats);
     else
         rc = launch_adm(st, &ctx->adm, *plan, ctx->n_cu, desc, ids, ids + S, region<char>(ws, plan, R_GSYS),
-                        region<double>(ws, plan, R_GE2), region<int32_t>(ws, plan, R_QUEUE), *params,
+                        region<double>(ws, plan, R_GE2), region<float>(ws, plan, R_GPART), region<int32_t>(ws, plan, R_QUEUE), *params,
                         row_ptr, csr_col, csr_val, col_ptr, csc_row, csc_val, ell, X, region<float>(ws, plan, R_XNEXT),
                         region<float>(ws, plan, R_XP), region<float>(ws, plan, R_LAMBDA), Y,
                         region<float>(ws, plan, R_YP), region<float>(ws, plan, R_PI), region<float>(ws, plan, R_YT),
@@ -1355,7 +1362,7 @@ int vplmc_stage_adm(vplmc_ctx *ctx, const vplmc_plan *plan, const vplmc_params *
                         region<int32_t>(ws, plan, R_YP), stats);
     else
         rc = launch_adm(st, &ctx->adm, *plan, ctx->n_cu, desc, ids, ids + plan->n_slices, region<char>(ws, plan, R_GSYS),
-                        region<double>(ws, plan, R_GE2), region<int32_t>(ws, plan, R_QUEUE), *params,
+                        region<double>(ws, plan, R_GE2), region<float>(ws, plan, R_GPART), region<int32_t>(ws, plan, R_QUEUE), *params,
                         row_ptr, csr_col, csr_val, col_ptr, csc_row, csc_val, ell, X, region<float>(ws, plan, R_XNEXT),
                         region<float>(ws, plan, R_XP), region<float>(ws, plan, R_LAMBDA), Y,
                         region<float>(ws, plan, R_YP), region<float>(ws, plan, R_PI), region<float>(ws, plan, R_YT),

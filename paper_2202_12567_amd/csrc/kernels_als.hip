@@ -80,8 +80,8 @@ struct AlsShape {
     static constexpr int T = Q <= 16 ? 16 : 32;         // lanes of a system
     static constexpr int SYS = WAVE / T;                // systems per wavefront
     static constexpr int GRP = SYS * ALS_NW;            // systems per workgroup
-    // workgroups per row block and per column block of the plan
-    static constexpr int RSUB = GADM_RB / GRP, CSUB = GADM_CB / GRP;
+    // workgroups per row block of the plan (per column block: its columns / GRP)
+    static constexpr int RSUB = GADM_RB / GRP;
 };
 
 // per-slice state between the launches
@@ -107,6 +107,7 @@ struct AlsArgs {
     int32_t *stats_all;
     char *gsys;
     double *e2;                          // RSUB slots per row block of the group
+    int32_t cb;                          // columns per column block
 };
 
 __device__ __forceinline__ AlsState *state_of(char *base, int s) {
@@ -418,12 +419,12 @@ __global__ __launch_bounds__(ALS_THREADS) void k_als_cols(AlsArgs a, int it) {
     constexpr int U = 16;                            // samples of a block
     __shared__ double red[ALS_NW];
     __shared__ int done_s;
-    const int blk = blockIdx.x / S::CSUB, sub = blockIdx.x % S::CSUB;
+    const int csub = a.cb / S::GRP, blk = blockIdx.x / csub, sub = blockIdx.x % csub;
     const int kk = block_slice(a.colp, a.count, blk);
     const int s = __builtin_amdgcn_readfirstlane(a.ids[kk]);
     AlsState *st = state_of(a.gsys, s);
     const SliceDesc d = a.desc[s];
-    const int first_at = (blk - a.colp[kk]) * GADM_CB + sub * S::GRP;
+    const int first_at = (blk - a.colp[kk]) * a.cb + sub * S::GRP;
     if (first_at >= d.n) return;
     // a slice that stops in this launch is marked by its first workgroup; the
     // others find the same sum, so it does not matter which they see first
@@ -536,11 +537,12 @@ int launch_als_q(hipStream_t st, const AlsArgs &args, const vplmc_plan &plan, in
     if (count == 0) return VPLMC_OK;
     AlsArgs a = args;
     a.count = (int32_t)count;
+    a.cb = plan.g_cb[grp];
     a.rowp = gblk_dev + plan.gblk_off[grp];
     a.colp = a.rowp + count + 1;
     a.e2 = e2 + ALS_E2_SLOTS * plan.ge2_base[grp];
     static_assert(S::RSUB <= ALS_E2_SLOTS, "residual slots of a row block");
-    const unsigned nr = (unsigned)(plan.g_rows[grp] * S::RSUB), nc = (unsigned)(plan.g_cols[grp] * S::CSUB);
+    const unsigned nr = (unsigned)(plan.g_rows[grp] * S::RSUB), nc = (unsigned)(plan.g_cols[grp] * (a.cb / S::GRP));
     hipLaunchKernelGGL(k_als_init<Q>, dim3((unsigned)count), dim3(ALS_INIT_THREADS), 0, st, a);
     VPLMC_HIP(hipGetLastError());
     for (int it = 0; it < a.max_iter; ++it) {
