@@ -40,16 +40,23 @@ namespace {
 // part of a column (at most ELL_LMAX samples; the parts of a 64-lane group
 // have nearly equal lengths) and every load of a wavefront covers 64
 // consecutive entries.
-//   phase A, lane = part of column j: Y_j (3q floats) in registers, X_i from LDS;
-//     the residual r is stored in the ELL copy and the q components of
-//     sum_c r_c Y_j^c, times 2^S and rounded, are added into row i of a
-//     fixed-point R Y^T accumulator with integer LDS atomics (LDS float
-//     atomics serialise per lane on this chip).  Integer sums do not depend
-//     on the order of the additions.  Word q of each row sums a ceil-rounded
-//     bound of the row's L1 residual sum; the scale 2^S keeps every row sum
-//     below 2^31 given that bound and |Y|max, and the phase runs again with
-//     a smaller scale whenever an estimate taken from the previous iterate
+//   phase A, 4 lanes = part of column j, a lane = one of its samples: X_i from
+//     LDS, both products with Y_j (X_i . Y_j and sum_c r_c Y_j^c) on 4 x 4 x 1
+//     FP32 matrix instructions, whose results lie in the sample's own lane and
+//     are those of an fma chain bit for bit; the residual r is stored in the ELL
+//     copy and the q components of sum_c r_c Y_j^c, times 2^S and rounded, are
+//     added into row i of a fixed-point R Y^T accumulator with integer LDS
+//     atomics (LDS float atomics serialise per lane on this chip).  Integer sums
+//     do not depend on the order of the additions.  Word q of each row sums a
+//     ceil-rounded bound of the row's L1 residual sum; the scale 2^S keeps every
+//     row sum below 2^31 given that bound and |Y|max, and the phase runs again
+//     with a smaller scale whenever an estimate taken from the previous iterate
 //     fails, so no sum overflows.
+//     Bound by VALU issue (57% of the kernel at rank 16), then LDS (46%, most of
+//     it the atomics' bank conflicts); with one lane per part and the products
+//     on the vector units VALU issue was 61% at 9% more time.  Samples of a step
+//     are loaded while the step before is processed, unconditionally (a load
+//     under a lane mask waits for everything in flight).
 //   X system, X update: Inv = (GY + a I)^-1 by FP64 Cholesky, T = R Y^T + a U - L,
 //     then X+ = X (GY Inv) + T Inv as FP32 16 x 16 x 4 MFMA products per 16
 //     rows (the FP64 factors rounded to FP32), with U, L and the Grams X+^T X+
@@ -67,6 +74,10 @@ namespace {
 // 128-bit reads of a wavefront over the banks.
 // Per-wavefront partial Grams are summed in a fixed order through the
 // slice's global scratch.  The run is reproducible bit for bit.
+// The wavefronts take the items of phases A (16 parts) and B (64 parts) from a
+// counter, longest first: a frame of 16 slices of 1,024 columns (17 groups for
+// 15 wavefronts) 8.8 -> 6.8 ms, 2,025 slices of 512 columns 196 -> 166 ms,
+// 64 slices of 2,048 columns 35.8 -> 32.8 ms, all with the phase A above.
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -75,6 +86,13 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // register v of lane l of the result holds D[4 (l / 16) + v][l % 16].
 __device__ __forceinline__ f4 mfma16(float a, float b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// v_mfma_f32_4x4x1_16b_f32: 16 products of a 4 x 1 by a 1 x 4 operand, one per
+// four lanes: lane 4 b + l holds A_b[l] and B_b[l], register v of lane 4 b + l
+// of the result D_b[v][l].  Writes every lane, whatever the lane mask.
+__device__ __forceinline__ f4 mfma4(float a, float b, f4 c) {
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
 }
 
 __device__ __forceinline__ float wave_max(float v) {
@@ -149,12 +167,18 @@ __device__ __forceinline__ float4 *xchunk_w(float *X, int i, int c) {
 
 // elements of the fixed-point to float pass (m q <= ADM_CVT_ELEMS)
 constexpr int ADM_CVT_ELEMS = 18 * 1024;
-// ELL entries a lane loads at once in phase A (one more block of them in
-// flight while a block is processed) and in phase B
-constexpr int ADM_DA = 2;
+// ELL entries a lane loads at once in phase B
 constexpr int ADM_DB = 8;
 // split-column sums a thread gathers before it stores them
 constexpr int ADM_CMB = 4;
+
+// the wavefront's next item of a phase: the counter starts behind the items
+// that the wavefronts begin with
+__device__ __forceinline__ int next_item(int32_t &taken, int lane) {
+    int k = 0;
+    if (lane == 0) k = atomicAdd(&taken, 1);
+    return __builtin_amdgcn_readfirstlane(k);
+}
 
 template <int Q, int THREADS>
 __device__ void adm_ell_slice(
@@ -169,6 +193,7 @@ __device__ void adm_ell_slice(
     extern __shared__ __align__(16) float dyn[];
     __shared__ AdmShared<Q> sh;
     __shared__ float redf[NW];
+    __shared__ int32_t taken_a, taken_b;              // items of phases A and B handed out
 
     const SliceDesc d = desc[s];
     const int m = d.m, n = d.n;
@@ -198,12 +223,11 @@ __device__ void adm_ell_slice(
     float *Pi = Pi_all + d.off_y;
     float *Yt = Yt_all + d.off_y;
     float *red = red_all + d.off_red;
-    double *e2part = e2part_all + 2 * d.off_part;   // per part: the two halves' sums
+    double *e2part = e2part_all + d.off_part;       // per part, in column order
     int32_t *st = stats_all + 4 * s;
     const int nnz = col_ptr[n];
     const int P = pbase[n];               // parts
     const int G = (P + 63) / 64;          // groups of 64 parts
-    const bool halves = G < NW - 1;       // phase A: two wavefronts per group
     const int R3 = 3 * n;
 
     // the slice's samples in the ELL copy: entries k < length of the part at
@@ -405,119 +429,117 @@ __device__ void adm_ell_slice(
         for (;;) {
             const float fxs = ldexpf(1.f, S), fxr = ldexpf(1.f, Sr);
             for (int e = t; e < m * (Q + 1); e += THREADS) RXI[e] = 0;
+            if (t == 0) {
+                taken_a = NW - 1;
+                taken_b = NW - 1;
+            }
             __syncthreads();
             float rsm = 0.f;
             // the last wavefront solves the X system (Inv, F for the X update),
-            // which needs only GY, while the others take the parts
-            if (wave == NW - 1) {
-                if (!xsys) {
-                    spd_solve_wave<Q, true>(sh, alpha, lane);
-                    xsys = true;
+            // which needs only GY, while the others take the parts; then it
+            // takes items as they do
+            if (wave == NW - 1 && !xsys) spd_solve_wave<Q, true>(sh, alpha, lane);
+            xsys = true;
+            // An item is 16 parts of one group, 4 lanes per part; lane 4 b + u
+            // takes the entries 4 s + u of part b.  Both products of a part with
+            // its column's Y are 4 x 4 x 1 matrix instructions whose second operand
+            // and result belong to the lane's own entry.
+            const int bq = lane >> 2, uq = lane & 3;
+            const int items = (P + 15) >> 4;
+            for (int item = wave == NW - 1 ? next_item(taken_a, lane) : wave; item < items;
+                 item = next_item(taken_a, lane)) {
+                const int sp = 16 * item + bq;
+                const int2 pv = part[min(sp, P - 1)];
+                const int j = pv.x & 0xFFFF;
+                const int cnt = sp < P ? (pv.x >> 16) & 0x7F : 0;
+                // sorted by length: the item's first part is its longest
+                const int len = __builtin_amdgcn_readfirstlane(cnt);
+                const int steps = (len + 3) >> 2;
+                const int eb = grp[item >> 2] + 16 * (item & 3) + bq;
+                // Y_j as the first operand: of the residual, channel uq (one row of
+                // the product is unused), and of R Y^T, component 4 q + uq
+                const float *yj = Y + (size_t)j * 3 * Q;
+                float yr[Q], yt[3 * QV];
+#pragma unroll
+                for (int v = 0; v < QV; ++v) {
+                    const float4 a = reinterpret_cast<const float4 *>(yj + min(uq, 2) * Q)[v];
+                    yr[4 * v] = a.x;
+                    yr[4 * v + 1] = a.y;
+                    yr[4 * v + 2] = a.z;
+                    yr[4 * v + 3] = a.w;
                 }
-            } else {
-            // with fewer part groups than working wavefronts, two wavefronts
-            // share a group, the first taking entries [0, kh) of every part,
-            // the second [kh, length)
-            const int items = halves ? 2 * G : G;
-            for (int item = wave; item < items; item += NW - 1) {
-                const int g = halves ? item >> 1 : item, h = halves ? item & 1 : 0;
-                int j, cnt, pc, np;
-                part_of(g, j, cnt, pc, np);
-                const int base = grp[g];
-                const int len = (grp[g + 1] - base) >> 6;
-                const int kh = halves ? (len + 2 * ADM_DA - 1) / (2 * ADM_DA) * ADM_DA : len;
-                const int kb = h ? kh : 0, ke = h ? len : kh;
-                const int ce = cnt < ke ? cnt : ke;          // the lane's entries: [kb, ce)
+#pragma unroll
+                for (int v = 0; v < 3 * QV; ++v) yt[v] = yj[4 * v + uq];
                 double e2 = 0.0;
-                float y[3 * Q];
-                const float4 *y4 = reinterpret_cast<const float4 *>(Y + (size_t)j * 3 * Q);
+                // the lanes' entries of step k (a lane past its part's reads padding or
+                // again the longest part's last entry)
+                auto load_step = [&](int k, int &i, float &m0, float &m1, float &m2) {
+                    const int e = eb + 64 * min(4 * k + uq, len - 1);
+                    i = (int)erow[e];
+                    m0 = eval[3 * e];
+                    m1 = eval[3 * e + 1];
+                    m2 = eval[3 * e + 2];
+                };
+                auto do_step = [&](int k, int row, float m0, float m1, float m2) {
+                    const bool act = 4 * k + uq < cnt;
+                    const int i = act ? row : 0;
+                    f4 dd = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int v = 0; v < 3 * Q / 4; ++v) {
-                    const float4 a = ce > kb ? y4[v] : make_float4(0.f, 0.f, 0.f, 0.f);
-                    y[4 * v] = a.x;
-                    y[4 * v + 1] = a.y;
-                    y[4 * v + 2] = a.z;
-                    y[4 * v + 3] = a.w;
-                }
-                // entries k0 .. k0 + ADM_DA - 1 of the lane's part; the next block
-                // is loaded before this block's residuals are stored
-                auto load_block = [&](int k0, int *ib, float *mb0, float *mb1, float *mb2) {
+                    for (int v = 0; v < QV; ++v) {
+                        const float4 a4 = *xchunk<Q>(XA, i, v);
+                        dd = mfma4(yr[4 * v], a4.x, dd);
+                        dd = mfma4(yr[4 * v + 1], a4.y, dd);
+                        dd = mfma4(yr[4 * v + 2], a4.z, dd);
+                        dd = mfma4(yr[4 * v + 3], a4.w, dd);
+                    }
+                    const float r0 = fmaf(m0, inv_s0, -dd[0]), r1 = fmaf(m1, inv_s0, -dd[1]), r2 = fmaf(m2, inv_s0, -dd[2]);
+                    const float s0r = r0 * fxs, s1r = r1 * fxs, s2r = r2 * fxs;
+                    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+                    f4 cc[QV];
 #pragma unroll
-                    for (int u = 0; u < ADM_DA; ++u) {
-                        const bool act = k0 + u < ce;
-                        const int e = base + 64 * (k0 + u) + lane;
-                        ib[u] = act ? (int)erow[e] : -1;
-                        mb0[u] = act ? eval[3 * e] : 0.f;
-                        mb1[u] = act ? eval[3 * e + 1] : 0.f;
-                        mb2[u] = act ? eval[3 * e + 2] : 0.f;
+                    for (int v = 0; v < QV; ++v) cc[v] = mfma4(yt[2 * QV + v], s2r, zero);
+#pragma unroll
+                    for (int v = 0; v < QV; ++v) cc[v] = mfma4(yt[QV + v], s1r, cc[v]);
+#pragma unroll
+                    for (int v = 0; v < QV; ++v) cc[v] = mfma4(yt[v], s0r, cc[v]);
+                    if (act) {
+                        const int e = eb + 64 * (4 * k + uq);
+                        eres[3 * e] = r0;
+                        eres[3 * e + 1] = r1;
+                        eres[3 * e + 2] = r2;
+                        e2 += (double)(r0 * r0) + (double)(r1 * r1) + (double)(r2 * r2);
+                        const float rsa = fabsf(r0) + fabsf(r1) + fabsf(r2);
+                        rsm = fmaxf(rsm, rsa);
+                        int32_t *rx = RXI + i * (Q + 1);
+#pragma unroll
+                        for (int kk = 0; kk < Q; ++kk) atomicAdd(rx + kk, __float2int_rn(cc[kk >> 2][kk & 3]));
+                        atomicAdd(reinterpret_cast<uint32_t *>(rx + Q), __float2uint_ru(rsa * fxr));
                     }
                 };
-                int ib[ADM_DA];
-                float mb0[ADM_DA], mb1[ADM_DA], mb2[ADM_DA];
-                if (kb < ke) load_block(kb, ib, mb0, mb1, mb2);
-                for (int k0 = kb; k0 < ke; k0 += ADM_DA) {
-                    int ibn[ADM_DA];
-                    float mn0[ADM_DA], mn1[ADM_DA], mn2[ADM_DA];
-                    if (k0 + ADM_DA < ke) load_block(k0 + ADM_DA, ibn, mn0, mn1, mn2);
-#pragma unroll
-                    for (int u = 0; u < ADM_DA; ++u) {
-                        mb0[u] *= inv_s0;
-                        mb1[u] *= inv_s0;
-                        mb2[u] *= inv_s0;
-                    }
-#pragma unroll
-                    for (int u = 0; u < ADM_DA; ++u) {
-                        const int i = ib[u];
-                        if (i >= 0) {
-                            float x[Q];
-#pragma unroll
-                            for (int v = 0; v < QV; ++v) {
-                                const float4 a4 = *xchunk<Q>(XA, i, v);
-                                x[4 * v] = a4.x;
-                                x[4 * v + 1] = a4.y;
-                                x[4 * v + 2] = a4.z;
-                                x[4 * v + 3] = a4.w;
-                            }
-                            float d0 = 0.f, d1 = 0.f, d2 = 0.f;
-#pragma unroll
-                            for (int kk = 0; kk < Q; ++kk) {
-                                d0 = fmaf(x[kk], y[kk], d0);
-                                d1 = fmaf(x[kk], y[Q + kk], d1);
-                                d2 = fmaf(x[kk], y[2 * Q + kk], d2);
-                            }
-                            const float r0 = mb0[u] - d0, r1 = mb1[u] - d1, r2 = mb2[u] - d2;
-                            e2 += (double)(r0 * r0) + (double)(r1 * r1) + (double)(r2 * r2);
-                            const int e = base + 64 * (k0 + u) + lane;
-                            eres[3 * e] = r0;
-                            eres[3 * e + 1] = r1;
-                            eres[3 * e + 2] = r2;
-                            const float rsa = fabsf(r0) + fabsf(r1) + fabsf(r2);
-                            rsm = fmaxf(rsm, rsa);
-                            const float s0r = r0 * fxs, s1r = r1 * fxs, s2r = r2 * fxs;
-                            int32_t *row = RXI + i * (Q + 1);
-#pragma unroll
-                            for (int kk = 0; kk < Q; ++kk)
-                                atomicAdd(row + kk,
-                                          __float2int_rn(fmaf(s0r, y[kk], fmaf(s1r, y[Q + kk], s2r * y[2 * Q + kk]))));
-                            atomicAdd(reinterpret_cast<uint32_t *>(row + Q), __float2uint_ru(rsa * fxr));
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < ADM_DA; ++u) {
-                        ib[u] = ibn[u];
-                        mb0[u] = mn0[u];
-                        mb1[u] = mn1[u];
-                        mb2[u] = mn2[u];
+                // two steps in turn, one in flight while the other is processed
+                if (steps > 0) {
+                    int ia, ib;
+                    float ma0, ma1, ma2, mb0, mb1, mb2;
+                    load_step(0, ia, ma0, ma1, ma2);
+                    for (int k = 0;; k += 2) {
+                        load_step(k + 1, ib, mb0, mb1, mb2);
+                        do_step(k, ia, ma0, ma1, ma2);
+                        if (k + 1 >= steps) break;
+                        load_step(k + 2, ia, ma0, ma1, ma2);
+                        do_step(k + 1, ib, mb0, mb1, mb2);
+                        if (k + 2 >= steps) break;
                     }
                 }
-                if (64 * g + lane < P) e2part[2 * pc + h] = e2;
+                // the part's sum: its four lanes' in fixed pairs
+                e2 += __shfl_xor(e2, 1, WAVE);
+                e2 += __shfl_xor(e2, 2, WAVE);
+                if (uq == 0 && sp < P) e2part[pv.y] = e2;
             }
-            }
-            // sum of the parts' squared residuals in column order (and half order)
+            // sum of the parts' squared residuals in column order
             __threadfence_block();
             __syncthreads();
             double e2 = 0.0;
-            for (int u = t; u < P; u += THREADS) e2 += halves ? e2part[2 * u] + e2part[2 * u + 1] : e2part[2 * u];
+            for (int u = t; u < P; u += THREADS) e2 += e2part[u];
             uint32_t rsw = 0;
             for (int i = t; i < m; i += THREADS) rsw = max(rsw, reinterpret_cast<const uint32_t *>(RXI)[i * (Q + 1) + Q]);
             e2 = wave_sum_d(e2);
@@ -643,13 +665,12 @@ __device__ void adm_ell_slice(
         }
         // ---- phase B: T_j = X+^T R_j + b V_j - P_j (columns of several parts: partial sums) ----
         // the last wavefront meanwhile solves the Y system (Inv = (GX + b I)^-1,
-        // F[l][k] = (Inv C)[k][l]), which the Y update needs and phase B does not
+        // F[l][k] = (Inv C)[k][l]), which the Y update needs and phase B does
+        // not; then it takes groups as the others do
         t = fresh_tid();
         lane = t % WAVE;
-        if (wave == NW - 1)
-            spd_solve_wave<Q, false>(sh, beta, lane);
-        else
-        for (int g = wave; g < G; g += NW - 1) {
+        if (wave == NW - 1) spd_solve_wave<Q, false>(sh, beta, lane);
+        for (int g = wave == NW - 1 ? next_item(taken_b, lane) : wave; g < G; g = next_item(taken_b, lane)) {
             int j, cnt, pc, np;
             part_of(g, j, cnt, pc, np);
             const int base = grp[g];
@@ -657,35 +678,42 @@ __device__ void adm_ell_slice(
             float acc[3 * Q];
 #pragma unroll
             for (int kk = 0; kk < 3 * Q; ++kk) acc[kk] = 0.f;
-            // the part's entries are loaded ADM_DB at a time, all in flight together
-            for (int k0 = 0; k0 < len; k0 += ADM_DB) {
-                int ib[ADM_DB];
-                float rb0[ADM_DB], rb1[ADM_DB], rb2[ADM_DB];
+            // blocks of ADM_DB entries, all in flight together; a lane past its own
+            // entries reads padding, taken as residual 0 of row 0
+            auto load_block = [&](int k0, int *ib, float *rb0, float *rb1, float *rb2) {
+#pragma unroll
+                for (int u = 0; u < ADM_DB; ++u) {
+                    const int e = base + 64 * min(k0 + u, len - 1) + lane;
+                    ib[u] = (int)erow[e];
+                    rb0[u] = eres[3 * e];
+                    rb1[u] = eres[3 * e + 1];
+                    rb2[u] = eres[3 * e + 2];
+                }
+            };
+            auto do_block = [&](int k0, const int *ib, const float *rb0, const float *rb1, const float *rb2) {
 #pragma unroll
                 for (int u = 0; u < ADM_DB; ++u) {
                     const bool act = k0 + u < cnt;
-                    const int e = base + 64 * (k0 + u) + lane;
-                    ib[u] = act ? (int)erow[e] : -1;
-                    rb0[u] = act ? eres[3 * e] : 0.f;
-                    rb1[u] = act ? eres[3 * e + 1] : 0.f;
-                    rb2[u] = act ? eres[3 * e + 2] : 0.f;
-                }
+                    const int i = act ? ib[u] : 0;
+                    const float r0 = act ? rb0[u] : 0.f, r1 = act ? rb1[u] : 0.f, r2 = act ? rb2[u] : 0.f;
 #pragma unroll
-                for (int u = 0; u < ADM_DB; ++u) {
-                    if (ib[u] >= 0) {
+                    for (int v = 0; v < QV; ++v) {
+                        const float4 a = *xchunk<Q>(XA, i, v);
+                        const float xs[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
-                        for (int v = 0; v < QV; ++v) {
-                            const float4 a = *xchunk<Q>(XA, ib[u], v);
-                            const float xs[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-                            for (int w = 0; w < 4; ++w) {
-                                acc[4 * v + w] = fmaf(rb0[u], xs[w], acc[4 * v + w]);
-                                acc[Q + 4 * v + w] = fmaf(rb1[u], xs[w], acc[Q + 4 * v + w]);
-                                acc[2 * Q + 4 * v + w] = fmaf(rb2[u], xs[w], acc[2 * Q + 4 * v + w]);
-                            }
+                        for (int w = 0; w < 4; ++w) {
+                            acc[4 * v + w] = fmaf(r0, xs[w], acc[4 * v + w]);
+                            acc[Q + 4 * v + w] = fmaf(r1, xs[w], acc[Q + 4 * v + w]);
+                            acc[2 * Q + 4 * v + w] = fmaf(r2, xs[w], acc[2 * Q + 4 * v + w]);
                         }
                     }
                 }
+            };
+            for (int k0 = 0; k0 < len; k0 += ADM_DB) {
+                int ib[ADM_DB];
+                float rb0[ADM_DB], rb1[ADM_DB], rb2[ADM_DB];
+                load_block(k0, ib, rb0, rb1, rb2);
+                do_block(k0, ib, rb0, rb1, rb2);
             }
             if (64 * g + lane < P) {
                 if (np == 1) {
@@ -833,11 +861,19 @@ __device__ void adm_ell_slice(
                     *reinterpret_cast<float4 *>(Y + e) = make_float4(yo[0], yo[1], yo[2], yo[3]);
                 }
             };
-            for (int r0 = 16 * wave; r0 < R3; r0 += 16 * NW) {
-                float ya[QV], ta[QV];
-                float4 pa;
-                load_tile(r0, ya, ta, pa);
-                do_tile(r0, ya, ta, pa);
+            // two tiles in turn, one in flight while the other is processed
+            if (16 * wave < R3) {
+                float ya[QV], ta[QV], yb[QV], tb[QV];
+                float4 pa, pb;
+                load_tile(16 * wave, ya, ta, pa);
+                for (int r0 = 16 * wave;; r0 += 32 * NW) {
+                    load_tile(r0 + 16 * NW, yb, tb, pb);
+                    do_tile(r0, ya, ta, pa);
+                    if (r0 + 16 * NW >= R3) break;
+                    load_tile(r0 + 32 * NW, ya, ta, pa);
+                    do_tile(r0 + 16 * NW, yb, tb, pb);
+                    if (r0 + 32 * NW >= R3) break;
+                }
             }
             __threadfence_block();
             sum_partials<Q, NW>(gy, zero, red, sh.G, nullptr);

@@ -132,7 +132,7 @@ struct SliceDesc {
 // grp[g] + 64 k + l, so that one load instruction of a wavefront whose lane l
 // walks that part reads 64 consecutive entries and every lane of a group has
 // nearly the same number of samples.  Entries past a part's length are
-// padding and never read.  Parts are numbered in column order by
+// padding, loaded but never used.  Parts are numbered in column order by
 // pbase[j] + t.
 struct EllView {
     int2 *part;        // per (slice, sorted position): {j | len << 16 | (column of several parts) << 23,
