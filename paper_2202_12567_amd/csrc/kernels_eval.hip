@@ -188,20 +188,21 @@ __device__ __forceinline__ float wave_min(float v) {
 // (occluded), 0 (not), or -1 for every lane if the list overflows.  All 64
 // lanes call.
 constexpr int SHAFT_CAP = 128;
-__device__ int occluded_shaft(const Bvh &b, float4 *list, bool want, P3 o, P3 y) {
+// The tests of the groups are linear in their number; a traversal is not.  8,192
+// points against 4,096 lights and fine spheres, lists / traversal of the same
+// wavefronts: 1,024 groups 8.1 / 7.9 ms, 2,048 groups 10.2 / 10.1 ms.
+constexpr int SHAFT_MAX_GROUPS = 512;
+
+// the spheres near the shaft between the boxes A and B (wave-uniform) listed in
+// `list`; their number, which may exceed the SHAFT_CAP that are listed
+__device__ __forceinline__ int shaft_list(const Bvh &b, float4 *list, float (&alo)[3], float (&ahi)[3],
+                                          const float (&blo)[3], const float (&bhi)[3]) {
     const int lane = threadIdx.x & 63;
-    if (b.n_groups == 0 || __ballot(want) == 0) return 0;
-    const float of[3] = {o.x, o.y, o.z}, yf[3] = {y.x, y.y, y.z};
-    float alo[3], ahi[3], ilo[3], ihi[3], slo[3], shi[3];   // lines of the lower and upper box sides: start, 1 / slope, sign
-    float blo[3], bhi[3], big = 0.f;
+    float ilo[3], ihi[3], slo[3], shi[3];   // lines of the lower and upper box sides (from alo, ahi): 1 / slope, sign
+    float big = 0.f;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        alo[k] = wave_min(want ? of[k] : INFINITY);
-        ahi[k] = -wave_min(want ? -of[k] : INFINITY);
-        blo[k] = wave_min(want ? yf[k] : INFINITY);
-        bhi[k] = -wave_min(want ? -yf[k] : INFINITY);
+    for (int k = 0; k < 3; ++k)
         big = fmaxf(fmaxf(big, fmaxf(fabsf(alo[k]), fabsf(ahi[k]))), fmaxf(fabsf(blo[k]), fabsf(bhi[k])));
-    }
     const float pad = 1e-5f * big;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -257,7 +258,11 @@ __device__ int occluded_shaft(const Bvh &b, float4 *list, bool want, P3 o, P3 y)
             count += __popcll(hits);
         }
     }
-    if (count > SHAFT_CAP) return -1;
+    return count;
+}
+
+// is the lane's segment from o to y met by one of the first `count` listed spheres
+__device__ __forceinline__ bool list_occluded(const float4 *list, int count, bool want, P3 o, P3 y) {
     wave_lds_sync();
     const P3 D = sub(y, o);
     const float inv_dd = 1.0f / dot(D, D);
@@ -273,7 +278,23 @@ __device__ int occluded_shaft(const Bvh &b, float4 *list, bool want, P3 o, P3 y)
         if (__ballot(want && !occ) == 0) break;
     }
     wave_lds_sync();             // the next list overwrites this one
-    return want && occ ? 1 : 0;
+    return want && occ;
+}
+
+__device__ int occluded_shaft(const Bvh &b, float4 *list, bool want, P3 o, P3 y) {
+    if (b.n_groups == 0 || __ballot(want) == 0) return 0;
+    const float of[3] = {o.x, o.y, o.z}, yf[3] = {y.x, y.y, y.z};
+    float alo[3], ahi[3], blo[3], bhi[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        alo[k] = wave_min(want ? of[k] : INFINITY);
+        ahi[k] = -wave_min(want ? -of[k] : INFINITY);
+        blo[k] = wave_min(want ? yf[k] : INFINITY);
+        bhi[k] = -wave_min(want ? -yf[k] : INFINITY);
+    }
+    const int count = shaft_list(b, list, alo, ahi, blo, bhi);
+    if (count > SHAFT_CAP) return -1;
+    return list_occluded(list, count, want, o, y) ? 1 : 0;
 }
 
 // shade_in for a whole wavefront (all 64 lanes call; lanes without `on` get zeros)
@@ -285,7 +306,7 @@ __device__ __forceinline__ bool shade_wave(const Bvh &bvh, const S *staged, floa
         bool ray = false;
         if (on) ray = entry_unoccluded(q, L, r_min2, o0, o1, o2);
         const P3 o = {fmaf(eps, q.n.x, q.x.x), fmaf(eps, q.n.y, q.x.y), fmaf(eps, q.n.z, q.x.z)};
-        int occ = occluded_shaft(bvh, list, ray, o, L.y);
+        int occ = bvh.n_groups <= SHAFT_MAX_GROUPS ? occluded_shaft(bvh, list, ray, o, L.y) : -1;
         if (occ < 0) occ = ray && occluded_in(BvhGlobal<KIND>{bvh}, bvh.n_nodes, o, sub(L.y, o)) ? 1 : 0;
         if (occ) o0 = o1 = o2 = 0.f;
         return ray;
@@ -616,17 +637,15 @@ __global__ __launch_bounds__(256) void k_eval_pairs(Bvh bvh, vplmc_points pts, v
     out[3 * g + 2] = o2;
 }
 
-// Brute-force column sum: one thread per point and light chunk (grid.y),
+// Brute-force column sum against triangles: one thread per point and light chunk (grid.y),
 // lights staged through LDS; FP32 entries summed in FP64, chunk partial sums
 // added to the zeroed output with FP64 atomics.  Bound by the shadow rays'
 // traversal, whose latency needs wavefronts: the chunk (BF_MIN_CHUNK to
 // BF_CHUNK lights) is the largest that still gives BF_GRID_PER_CU workgroups
-// per CU.  8,192 points against 16,384 lights and 512 spheres on one MI355X:
-// 53.0 ms with chunks of 2,048 (one wavefront per SIMD), 14.8 ms so.
+// per CU.
 constexpr int BF_TILE = 256;
 constexpr int BF_CHUNK = 2048, BF_MIN_CHUNK = 64;
 constexpr int BF_GRID_PER_CU = 16;
-template <int KIND>
 __global__ __launch_bounds__(256) void k_brute_force(Bvh bvh, vplmc_points pts, vplmc_lights l, int32_t n_out,
                                                      const int32_t *__restrict__ pid, int32_t chunk, float r_min2,
                                                      float eps, double *__restrict__ out) {
@@ -658,7 +677,7 @@ __global__ __launch_bounds__(256) void k_brute_force(Bvh bvh, vplmc_points pts, 
                 const Light L = {{sl[0][k], sl[1][k], sl[2][k]}, {sl[3][k], sl[4][k], sl[5][k]}, sl[6][k], sl[7][k],
                                  sl[8][k]};
                 float o0, o1, o2;
-                shade<KIND>(bvh, q, L, r_min2, eps, o0, o1, o2);
+                shade<1>(bvh, q, L, r_min2, eps, o0, o1, o2);
                 a0 += (double)o0;
                 a1 += (double)o1;
                 a2 += (double)o2;
@@ -671,6 +690,172 @@ __global__ __launch_bounds__(256) void k_brute_force(Bvh bvh, vplmc_points pts, 
         atomicAdd(out + 3 * (size_t)g + 1, a1);
         atomicAdd(out + 3 * (size_t)g + 2, a2);
     }
+}
+
+// Brute-force column sum against spheres.  A workgroup takes a segment of BS_SEG
+// consecutive outputs, orders its points along a Morton curve over their two
+// longest axes (a bitonic sort in LDS, the same in every workgroup of the segment;
+// the order decides only which points share a wavefront), and its wavefronts each take 64 neighbours of that order and one
+// light after another, so that the 64 shadow segments lie in one narrow shaft
+// whose spheres are listed once (shaft_list).  With fewer runs of 64 points than
+// wavefronts, several wavefronts share a run and split its lights.  FP32 entries
+// summed in FP64, partial sums added to the zeroed output with FP64 atomics.
+// Bound by the latency of listing (a wavefront's list takes several dependent
+// loads), hence 8 wavefronts per SIMD although some registers spill: 5.3 ms
+// against 5.9 without.  8,192 points against 16,384 lights and 512 spheres 14.7 ->
+// 5.1 ms (with a traversal per ray, points in caller order), 64 points 1.47 ->
+// 0.44 ms, 16 spheres and 4,096 lights 0.84 -> 0.53 ms, 65,536 small spheres 15.4
+// -> 10.1 ms.  BS_GRID_PER_CU workgroups per CU even out the ends (4: 6.0 ms,
+// 16: as 8); each orders its segment again.
+constexpr int BS_SEG = 4096, BS_THREADS = 1024, BS_WAVES = BS_THREADS / 64;
+constexpr int BS_AXIS = 64;                  // Morton cells per axis
+constexpr int BS_GRID_PER_CU = 8;
+
+__device__ __forceinline__ uint32_t spread6(uint32_t x) {        // bit b of x to bit 2 b
+    x = (x | (x << 4)) & 0x30Fu;
+    x = (x | (x << 2)) & 0x333u;
+    return (x | (x << 1)) & 0x555u;
+}
+
+__global__ __launch_bounds__(BS_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_brute_spheres(
+    Bvh bvh, vplmc_points pts, vplmc_lights l, int32_t n_out, const int32_t *__restrict__ pid, int32_t chunk, float r_min2,
+    float eps, double *__restrict__ out) {
+    __shared__ float4 lists[BS_WAVES][SHAFT_CAP];
+    __shared__ uint32_t order[BS_SEG];       // Morton cell << 12 | output of the segment
+    __shared__ float ext[BS_WAVES][6];
+    constexpr int PER_SEG = BS_SEG / (64 * BS_WAVES);            // workgroups of a full segment
+    constexpr int PER_THREAD = BS_SEG / BS_THREADS;
+    static_assert(BS_SEG <= 4096 && BS_AXIS == 64, "12 bits each");
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int base = blockIdx.x / PER_SEG * BS_SEG;
+    const int len = min(BS_SEG, n_out - base);
+    const int run0 = blockIdx.x % PER_SEG * BS_WAVES;            // first run of 64 points
+    const int runs = min(BS_WAVES, (len + 63) / 64 - run0);
+    // positions, their box, the two longest axes
+    float x[PER_THREAD][3], lo[3], hi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) lo[a] = hi[a] = INFINITY;        // hi: minimum of the negated
+#pragma unroll
+    for (int u = 0; u < PER_THREAD; ++u) {
+        const int i = min(t + u * BS_THREADS, len - 1);
+        const int p = clamp_index(pid ? pid[base + i] : base + i, pts.m);
+        x[u][0] = pts.px[p];
+        x[u][1] = pts.py[p];
+        x[u][2] = pts.pz[p];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = fminf(lo[a], x[u][a]);
+            hi[a] = fminf(hi[a], -x[u][a]);
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = wave_min(lo[a]);
+        hi[a] = wave_min(hi[a]);
+        if (lane == 0) {
+            ext[w][a] = lo[a];
+            ext[w][3 + a] = hi[a];
+        }
+    }
+    __syncthreads();
+    float len3[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = hi[a] = INFINITY;
+        for (int v = 0; v < BS_WAVES; ++v) {
+            lo[a] = fminf(lo[a], ext[v][a]);
+            hi[a] = fminf(hi[a], ext[v][3 + a]);
+        }
+        len3[a] = -hi[a] - lo[a];
+    }
+    const int drop = len3[0] < len3[1] ? (len3[0] < len3[2] ? 0 : 2) : (len3[1] < len3[2] ? 1 : 2);
+#pragma unroll
+    for (int u = 0; u < PER_THREAD; ++u) {
+        uint32_t c[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {      // (not a number, as from an empty or infinite box: cell 0)
+            const float f = (x[u][a] - lo[a]) / len3[a] * (float)BS_AXIS;
+            c[a] = (uint32_t)fminf(fmaxf(f, 0.0f), (float)(BS_AXIS - 1));
+        }
+        const uint32_t key = spread6(drop == 0 ? c[1] : c[0]) | spread6(drop == 2 ? c[1] : c[2]) << 1;
+        const int i = t + u * BS_THREADS;
+        order[i] = i < len ? key << 12 | (uint32_t)i : 0xFFFFFFFFu;
+    }
+    __syncthreads();
+    for (int k = 2; k <= BS_SEG; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+#pragma unroll
+            for (int u = 0; u < PER_THREAD / 2; ++u) {
+                const int e = t + u * BS_THREADS;                // compare-exchange e of the step
+                const int i = (e & ~(j - 1)) << 1 | (e & (j - 1));
+                const uint32_t a = order[i], b = order[i | j];
+                if ((a > b) == ((i & k) == 0)) {
+                    order[i] = b;
+                    order[i | j] = a;
+                }
+            }
+            __syncthreads();
+        }
+    // the wavefront's run of points and its share of the chunk's lights
+    int slots = 1;
+    while (slots < runs) slots *= 2;
+    const int run = w & (slots - 1), split = BS_WAVES / slots, part = w / slots;
+    if (run >= runs) return;
+    const int i = (run0 + run) * 64 + lane;
+    const bool active = i < len;
+    const int g = base + (active ? (int)(order[i] & 4095u) : 0);
+    PointData q{};
+    if (active) q = load_point(pts, pid ? pid[g] : g);
+    const P3 o = {fmaf(eps, q.n.x, q.x.x), fmaf(eps, q.n.y, q.x.y), fmaf(eps, q.n.z, q.x.z)};
+    const float of[3] = {o.x, o.y, o.z};
+    float alo[3], ahi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        alo[a] = wave_min(active ? of[a] : INFINITY);
+        ahi[a] = -wave_min(active ? -of[a] : INFINITY);
+    }
+    // origins beyond any box, or too many groups: the traversal for every light
+    const bool boxed = fabsf(o.x) < 1e18f && fabsf(o.y) < 1e18f && fabsf(o.z) < 1e18f;
+    const bool shaft = bvh.n_groups <= SHAFT_MAX_GROUPS && __ballot(active && !boxed) == 0;
+    int over = 0;                          // lists that overflowed, less those that did not
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+    const int c1 = min(l.n, (int)(blockIdx.y + 1) * chunk);
+    for (int c = blockIdx.y * chunk + part; c < c1; c += split) {
+        const Light L = {{l.x[c], l.y[c], l.z[c]}, {l.nx[c], l.ny[c], l.nz[c]}, l.ir[c], l.ig[c], l.ib[c]};
+        float o0 = 0.f, o1 = 0.f, o2 = 0.f;
+        bool ray = false;
+        if (active) ray = entry_unoccluded(q, L, r_min2, o0, o1, o2);
+        if (__ballot(ray) == 0) continue;
+        bool occ = false;
+        int count = SHAFT_CAP + 1;
+        if (shaft && over <= 4) {
+            float blo[3] = {L.y.x, L.y.y, L.y.z}, bhi[3] = {L.y.x, L.y.y, L.y.z};
+            float al[3] = {alo[0], alo[1], alo[2]}, ah[3] = {ahi[0], ahi[1], ahi[2]};
+            count = bvh.n_groups ? shaft_list(bvh, lists[w], al, ah, blo, bhi) : 0;
+            over = count > SHAFT_CAP ? over + 1 : max(over - 1, 0);
+        }
+        if (count <= SHAFT_CAP)
+            occ = list_occluded(lists[w], count, ray, o, L.y);
+        else if (ray)
+            occ = occluded_in(BvhGlobal<0>{bvh}, bvh.n_nodes, o, sub(L.y, o));
+        if (ray && !occ) {
+            a0 += (double)o0;
+            a1 += (double)o1;
+            a2 += (double)o2;
+        }
+    }
+    if (active) {
+        atomicAdd(out + 3 * (size_t)g, a0);
+        atomicAdd(out + 3 * (size_t)g + 1, a1);
+        atomicAdd(out + 3 * (size_t)g + 2, a2);
+    }
+}
+
+// workgroups of a chunk of lights: whole segments, then the last one's runs
+int64_t bs_blocks(int32_t n_out) {
+    const int64_t per_seg = BS_SEG / (64 * BS_WAVES);
+    return n_out / BS_SEG * per_seg + (n_out % BS_SEG + 64 * BS_WAVES - 1) / (64 * BS_WAVES);
 }
 
 __global__ void k_zero_f64(double *p, size_t n) {
@@ -871,18 +1056,18 @@ int launch_brute_force(hipStream_t st, const Bvh &bvh, const vplmc_points &pts, 
     hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)std::min<size_t>((nz + 255) / 256, 65536)), dim3(256), 0, st, out, nz);
     VPLMC_HIP(hipGetLastError());
     if (l.n <= 0) return VPLMC_OK;
-    const int64_t blocks = blocks_for(n_out, 256);
+    const bool tri = bvh.kind == 1;
+    const int64_t blocks = tri ? blocks_for(n_out, 256) : bs_blocks(n_out);
+    const int64_t want = (int64_t)(tri ? BF_GRID_PER_CU : BS_GRID_PER_CU) * n_cu;
     int32_t chunk = BF_CHUNK;
     // (grid.y is at most 65,535)
-    while (chunk > BF_MIN_CHUNK && blocks * ((l.n + chunk - 1) / chunk) < (int64_t)BF_GRID_PER_CU * n_cu &&
-           l.n / (chunk / 2) < 65535)
-        chunk /= 2;
+    while (chunk > BF_MIN_CHUNK && blocks * ((l.n + chunk - 1) / chunk) < want && l.n / (chunk / 2) < 65535) chunk /= 2;
     const unsigned chunks = (unsigned)((l.n + (int64_t)chunk - 1) / chunk);
-    if (bvh.kind == 1)
-        hipLaunchKernelGGL((k_brute_force<1>), dim3(blocks_for(n_out, 256), chunks), dim3(256), 0, st, bvh, pts, l, n_out,
+    if (tri)
+        hipLaunchKernelGGL(k_brute_force, dim3((unsigned)blocks, chunks), dim3(256), 0, st, bvh, pts, l, n_out,
                            pid, chunk, prm.r_min * prm.r_min, prm.ray_eps, out);
     else
-        hipLaunchKernelGGL((k_brute_force<0>), dim3(blocks_for(n_out, 256), chunks), dim3(256), 0, st, bvh, pts, l, n_out,
+        hipLaunchKernelGGL(k_brute_spheres, dim3((unsigned)blocks, chunks), dim3(BS_THREADS), 0, st, bvh, pts, l, n_out,
                            pid, chunk, prm.r_min * prm.r_min, prm.ray_eps, out);
     VPLMC_HIP(hipGetLastError());
     return VPLMC_OK;
