@@ -318,10 +318,11 @@ int vplmc_render(vplmc_ctx *ctx, const vplmc_plan *plan, const vplmc_points *poi
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * frame as vplmc_render, with the workspace replaced by a static device array
- * of VPLMC_STATIC_WORKSPACE_BYTES that the library holds on every GPU it runs
- * on until the process ends.  Calls no allocating routine.  Returns
- * VPLMC_EINVAL if the plan's workspace (vplmc_workspace_size) exceeds that
- * size; small frames only (the tiny 64 x 64 configuration needs 46 MiB).
+ * of VPLMC_STATIC_WORKSPACE_BYTES (and 16 MiB for tables that only save time)
+ * that the library holds on every GPU it runs on until the process ends.
+ * Calls no allocating routine.  Returns VPLMC_EINVAL if the plan's workspace
+ * (vplmc_workspace_size, less such tables) exceeds that size; small frames
+ * only (the tiny 64 x 64 configuration needs 46 MiB).
  * All calls on one GPU share the array, which keeps the last frame's
  * contents (every buffer a frame reads is cleared or written by that frame
  * first): calls that overlap on one GPU, from any context or stream, race

@@ -38,7 +38,13 @@ namespace {
 // until the process ends.  Host code never uses the array's name as an
 // address (on the host it is only a stand-in for the device symbol): the
 // device address comes from hipGetSymbolAddress, once per device, below.
-__device__ __align__(256) unsigned char scratch[VPLMC_STATIC_WORKSPACE_BYTES];
+// Its limit on a frame leaves out the tables that only save time (core_total);
+// they have STATIC_TABLE_BYTES beside it, of which the Gram parts and the
+// depth-first tree never need more than a quarter of the frame's own size, and
+// the coarsening's top table is left out of a plan where it does not fit.
+constexpr size_t STATIC_TABLE_BYTES = 16u << 20;
+constexpr size_t STATIC_TOTAL_BYTES = VPLMC_STATIC_WORKSPACE_BYTES + STATIC_TABLE_BYTES;
+__device__ __align__(256) unsigned char scratch[STATIC_TOTAL_BYTES];
 
 constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
@@ -362,10 +368,10 @@ int vplmc_sbvh_build(int32_t n, const float *v, int32_t max_nodes, float *box, i
 // smallest leaf, the split nodes ordered by (height, id) and the level offsets.
 //
 // Top of the tree: a split node is opened when the draws
-// expected below it are at least COARSEN_TOP_DRAWS rows' worth; front holds the
-// unopened nodes below opened ones, above the opened ones.
-static int build_tree(const vplmc_coarsen *co, double mean_rows, std::vector<int32_t> &tree, int32_t &height_max,
-                      int32_t &n_front) {
+// expected below it are at least COARSEN_TOP_DRAWS rows' worth, up to top_max
+// front nodes; front holds the unopened nodes below opened ones, above the opened ones.
+static int build_tree(const vplmc_coarsen *co, double mean_rows, int top_max, std::vector<int32_t> &tree,
+                      int32_t &height_max, int32_t &n_front) {
     const int ng = co->n_leaves, ns = ng - 1, NC = 2 * ng - 1;
     if (ns > 0 && (!co->left || !co->right)) return set_error(VPLMC_EINVAL, "tree arrays must be non-NULL");
     std::vector<int32_t> parent(NC, -1), height(NC, 0), min_leaf(NC);
@@ -407,7 +413,7 @@ static int build_tree(const vplmc_coarsen *co, double mean_rows, std::vector<int
     for (int k = 0; k < ns; ++k) below[ng + k] = below[co->left[k]] + below[co->right[k]];
     for (size_t at = 0; at < front.size();) {
         const int f = front[at];
-        if (f >= ng && (int)front.size() < COARSEN_TOP_MAX &&
+        if (f >= ng && (int)front.size() < top_max &&
             (double)co->pixels * below[f] >= COARSEN_TOP_DRAWS * mean_rows * ng) {
             above.push_back(f);
             front[at] = co->left[f - ng];
@@ -478,14 +484,14 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
     plan->pass1_ppm = params->pass1_ppm;
     plan->pass2_ppm = params->pass2_ppm;
     plan->als = (params->flags & VPLMC_ALS) != 0;
+    const double mean_rows = n_slices > 0 ? std::max(1.0, (double)pt_offsets[n_slices] / n_slices) : 1.0;
     if (co) {
         plan->coarse = true;
         plan->n_leaves = co->n_leaves;
         plan->n_lights = 2 * co->n_leaves - 1;
         plan->pixels = co->pixels;
         plan->bound = co->bound;
-        const double mean_rows = n_slices > 0 ? std::max(1.0, (double)pt_offsets[n_slices] / n_slices) : 1.0;
-        if ((rc = build_tree(co, mean_rows, plan->tree, plan->height_max, plan->n_front))) {
+        if ((rc = build_tree(co, mean_rows, COARSEN_TOP_MAX, plan->tree, plan->height_max, plan->n_front))) {
             delete plan;
             return rc;
         }
@@ -739,13 +745,41 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
     bytes[R_COUNTS] = 4 * 8;
     bytes[VPLMC_R_FEATURES] = oc * MLP_IN * 4;
     bytes[VPLMC_R_LOGITS] = oc * 4;
-    size_t off = 0;
-    for (int r = 0; r < R_INTERNAL_END; ++r) {
-        L.off[r] = off;
-        L.bytes[r] = bytes[r];
-        off = align256(off + bytes[r]);
+    auto lay_out = [&] {
+        size_t off = 0;
+        for (int r = 0; r < R_INTERNAL_END; ++r) {
+            L.off[r] = off;
+            L.bytes[r] = bytes[r];
+            off = align256(off + bytes[r]);
+        }
+        L.total = off;
+    };
+    lay_out();
+    // the workspace without the tables that only save time: top table, Gram
+    // parts, depth-first half of the tree, ALS residual slots but one; and with
+    // the two residual sums per part that the completion once kept
+    size_t core[R_INTERNAL_END];
+    std::copy(bytes, bytes + R_INTERNAL_END, core);
+    core[R_TOP] = core[R_TOP_MAP] = core[R_GPART] = 0;
+    if (co) {
+        const int64_t ng = co->n_leaves, ns = ng - 1, nodes = 2 * ng - 1;
+        core[R_TREE] = (3 * ns + 3 * nodes + plan->height_max + 1) * 4;
+        core[R_LEAF_KPRE] = (ng + 1) * 8;
     }
-    L.total = off;
+    core[R_GE2] = (size_t)e2b * 8;
+    core[R_E2PART] = plan->tot_part * 16;
+    plan->core_total = 0;
+    for (int r = 0; r < R_INTERNAL_END; ++r) plan->core_total = align256(plan->core_total + core[r]);
+    // a frame that the static workspace takes does so with its tables, or without the top one
+    if (plan->core_total <= VPLMC_STATIC_WORKSPACE_BYTES && L.total > STATIC_TOTAL_BYTES && plan->n_front > 1) {
+        if ((rc = build_tree(co, mean_rows, 1, plan->tree, plan->height_max, plan->n_front))) {
+            delete plan;
+            return rc;
+        }
+        bytes[R_TREE] = plan->tree.size() * 4;
+        bytes[R_TOP_MAP] = bytes[R_TOP] = 0;
+        lay_out();
+    }
     // host staging copy of the descriptor table followed by the bucketed slice ids
     plan->upload.resize(bytes[R_DESC]);
     if (n_slices > 0) {
@@ -1013,16 +1047,16 @@ int vplmc_render_static(vplmc_ctx *ctx, const vplmc_plan *plan, const vplmc_poin
                         const vplmc_lights *vpls, const vplmc_cut *cut, const int32_t *pt_ids, const int32_t *cl_ids,
                         const vplmc_params *params, float *radiance) {
     if (!ctx || !plan) return set_error(VPLMC_EINVAL, "ctx and plan must be non-NULL");
-    if (plan->layout.total > VPLMC_STATIC_WORKSPACE_BYTES)
+    if (plan->core_total > VPLMC_STATIC_WORKSPACE_BYTES || plan->layout.total > STATIC_TOTAL_BYTES)
         return set_error(VPLMC_EINVAL, "frame needs a %zu-byte workspace, above the %zu-byte static workspace "
-                         "(use vplmc_render with a caller workspace)", plan->layout.total,
+                         "(use vplmc_render with a caller workspace)", plan->core_total,
                          (size_t)VPLMC_STATIC_WORKSPACE_BYTES);
     if (!ctx->scratch) return set_error(VPLMC_EHIP, "static workspace address unknown");
     // the same frame as vplmc_render, on the device array: every buffer the
     // frame reads before writing is cleared by its fill kernels, so the
     // previous call's contents do not matter
     return vplmc_render(ctx, plan, points, vpls, cut, pt_ids, cl_ids, params, ctx->scratch,
-                        (size_t)VPLMC_STATIC_WORKSPACE_BYTES, radiance);
+                        STATIC_TOTAL_BYTES, radiance);
 }
 
 static int check_tune(const vplmc_tune *t) {

@@ -303,6 +303,7 @@ struct vplmc_plan {
     int64_t tot1 = 0, tot2 = 0, tot_omega = 0, tot_col = 0, tot_row = 0, tot_x = 0, tot_y = 0;
     int64_t tot_bm = 0, tot_bmt = 0;
     int64_t tot_grp = 0, tot_ell = 0, n_ell = 0;   // ELL group table entries, ELL entries, ELL slices
+    size_t core_total = 0;                          // workspace bytes without the tables that only save time
     int64_t tot_part = 0;                           // part slots
     vplmc_tune tune = {0, 1024, 256, 0};             // launch shapes
     std::vector<int32_t> ids;                  // slice ids grouped by rank bucket
