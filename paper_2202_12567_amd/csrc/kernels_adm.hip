@@ -52,9 +52,10 @@ namespace {
 //     row sum below 2^31 given that bound and |Y|max, and the phase runs again
 //     with a smaller scale whenever an estimate taken from the previous iterate
 //     fails, so no sum overflows.
-//     Bound by VALU issue (57% of the kernel at rank 16), then LDS (46%, most of
-//     it the atomics' bank conflicts); with one lane per part and the products
-//     on the vector units VALU issue was 61% at 9% more time.  Samples of a step
+//     VALU issue takes 52% of the kernel's cycles at rank 16, LDS 48% (two thirds
+//     of it bank conflicts of random rows), and large frames move their bytes at
+//     the rate of a large copy (4.65 TB/s); with one lane per part and the
+//     products on the vector units VALU issue was 61% at 9% more time.  Samples of a step
 //     are loaded while the step before is processed, unconditionally (a load
 //     under a lane mask waits for everything in flight).
 //   X system, X update: Inv = (GY + a I)^-1 by FP64 Cholesky, T = R Y^T + a U - L,
