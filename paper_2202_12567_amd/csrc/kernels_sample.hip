@@ -475,10 +475,13 @@ __global__ __launch_bounds__(P2_THREADS) void k_pass2(const SliceDesc *__restric
 
 // Popcount prefix of each bitmap row (one wavefront per row): wpre[w] = set
 // bits before word w within the row; the row total goes to ptr[row + 1].
+// Bound by the latency of the search for the row's slice: the 1080p frame's 2.07 M
+// rows 1.08 ms with vector loads, 0.67 with scalar ones; 262,144 rows 0.68 -> 0.36.
 __global__ void k_rowscan(const SliceDesc *__restrict__ desc, int S, int64_t total_rows, int cols,
                           const uint32_t *__restrict__ bm, uint16_t *wpre, int32_t *ptr) {
-    const int64_t g = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / WAVE;
-    const int lane = threadIdx.x % WAVE;
+    // the row is the wavefront's: its search and descriptor through scalar loads
+    const int lane = threadIdx.x % WAVE, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t g = blockIdx.x * (int64_t)(blockDim.x / WAVE) + wave;
     if (g >= total_rows) return;
     const int s = slice_of(desc, S, g, cols ? 3 : 2);
     const SliceDesc d = desc[s];
