@@ -42,6 +42,7 @@ constexpr int WAVE = 64;
 constexpr int LT = 256;          // threads of the grid kernels
 constexpr int TS = 4, CHUNK = TS * LT;   // samples per thread and per workgroup of the split test
 constexpr int TN = 32;           // nodes it stages at once
+static_assert(LT / TN == 8, "planes 0-7 by a thread each, plane 8 by those of plane 0");
 constexpr int ST = 1024;         // threads of the single-workgroup kernels
 constexpr int UPD = LC_UPDATE_CHUNK;
 constexpr int OT = 256;               // threads of the ordering kernels
@@ -128,7 +129,9 @@ __device__ __forceinline__ float wave_maxf(float v) {
 // Only the largest ratio of a node counts, so the square root and the divisions
 // are first taken by the 1-ulp instructions (error below 1e-6), and exactly only
 // for the lanes that come within 1e-5 of the wavefront's largest, or whose values
-// leave the range where that error holds; the maximum is the exact one.
+// leave the range where that error holds; the maximum is the exact one.  A level
+// of so few nodes that a workgroup has one at a time is bound by latency, and reads
+// them without staging.
 // Bound by VALU issue.  With samples read again for every node and every ratio
 // exact, 300,000 VPLs at 8,192 samples took 1.05 ms over all levels, so 0.73.
 __global__ __launch_bounds__(LT) void k_lc_test(LightcutView v, int p, float r_min2) {
@@ -143,6 +146,8 @@ __global__ __launch_bounds__(LT) void k_lc_test(LightcutView v, int p, float r_m
     // workgroups per chunk of samples, nodes per group: as many as leave every one a group
     const int per = max(1, (int)gridDim.x / nchunk);
     const int ng = min(TN, max(1, nf / per));
+    if ((int)(blockIdx.x % per) * ng >= nf) return;      // the level has no node for it: no samples either
+    const int own = t % TN, pl = t / TN;                 // the thread stages plane pl of node `own` (and 8, if pl is 0)
     for (int c = blockIdx.x / per; c < nchunk; c += max(1, (int)gridDim.x / per)) {
         float sx[TS][3], sn[TS][3], sm[TS][3], inv[TS];
 #pragma unroll
@@ -156,58 +161,76 @@ __global__ __launch_bounds__(LT) void k_lc_test(LightcutView v, int p, float r_m
             }
             inv[k] = v.inv_est[s];
         }
-        for (int i0 = (int)(blockIdx.x % per) * ng; i0 < nf; i0 += per * ng) {
-            const int cnt = min(ng, nf - i0);
-            __syncthreads();
-            for (int e = t; e < 9 * TN; e += LT) {
-                const int i = e % TN, pl = e / TN;
-                if (i < cnt) {
-                    const int f = cur[i0 + i];
-                    nd[pl][i] = pl < 6 ? v.bbox[pl * N + f] : v.lights[pl * N + f];
-                    if (pl == 0) id[i] = f;
-                }
+        // the node's largest ratio over the workgroup's samples, into rho[k]
+        auto ratios = [&](int k_node, float lx, float ly, float lz, float hx, float hy, float hz, float I0, float I1,
+                          float I2) {
+            float d2[TS], h[TS], m[TS], near[TS];
+            bool want[TS];
+#pragma unroll
+            for (int k = 0; k < TS; ++k) {
+                const float x = sx[k][0], y = sx[k][1], z = sx[k][2];
+                const float nx = sn[k][0], ny = sn[k][1], nz = sn[k][2];
+                const float gx = fmaxf(fmaxf(lx - x, x - hx), 0.0f);
+                const float gy = fmaxf(fmaxf(ly - y, y - hy), 0.0f);
+                const float gz = fmaxf(fmaxf(lz - z, z - hz), 0.0f);
+                d2[k] = fmaf(gx, gx, fmaf(gy, gy, gz * gz));
+                h[k] = fmaxf(nx * (lx - x), nx * (hx - x)) + fmaxf(ny * (ly - y), ny * (hy - y)) +
+                       fmaxf(nz * (lz - z), nz * (hz - z));
+                m[k] = fmaf(sm[k][0], I0, fmaf(sm[k][1], I1, sm[k][2] * I2));
+                want[k] = h[k] > 0.0f;           // 0 otherwise
             }
-            __syncthreads();
-            for (int i = 0; i < cnt; ++i) {
-                if (id[i] < v.n) continue;           // a single VPL: exact, never split
-                const float lx = nd[0][i], ly = nd[1][i], lz = nd[2][i], hx = nd[3][i], hy = nd[4][i], hz = nd[5][i];
-                const float I0 = nd[6][i], I1 = nd[7][i], I2 = nd[8][i];
-                float d2[TS], h[TS], m[TS], near[TS];
-                bool odd[TS];
+            if (ng > 1) {
                 float top = 0.0f;
 #pragma unroll
                 for (int k = 0; k < TS; ++k) {
-                    const float x = sx[k][0], y = sx[k][1], z = sx[k][2];
-                    const float nx = sn[k][0], ny = sn[k][1], nz = sn[k][2];
-                    const float gx = fmaxf(fmaxf(lx - x, x - hx), 0.0f);
-                    const float gy = fmaxf(fmaxf(ly - y, y - hy), 0.0f);
-                    const float gz = fmaxf(fmaxf(lz - z, z - hz), 0.0f);
-                    d2[k] = fmaf(gx, gx, fmaf(gy, gy, gz * gz));
-                    h[k] = fmaxf(nx * (lx - x), nx * (hx - x)) + fmaxf(ny * (ly - y), ny * (hy - y)) +
-                           fmaxf(nz * (lz - z), nz * (hz - z));
-                    m[k] = fmaf(sm[k][0], I0, fmaf(sm[k][1], I1, sm[k][2] * I2));
                     const float cub = d2[k] > 0.0f ? fminf(1.0f, h[k] * __builtin_amdgcn_rsqf(d2[k])) : 1.0f;
                     const float w = cub * __builtin_amdgcn_rcpf(fmaxf(d2[k], r_min2));
                     const float r = w * m[k] * inv[k];
-                    near[k] = h[k] > 0.0f ? r : 0.0f;
                     const bool in = (d2[k] == 0.0f || d2[k] > 1e-30f) && w > 1e-30f && r > 1e-30f && r < 1e30f;
-                    odd[k] = h[k] > 0.0f && !in;
-                    top = fmaxf(top, near[k]);
+                    near[k] = in ? r : INFINITY;
+                    top = fmaxf(top, want[k] && in ? r : 0.0f);
                 }
                 const float cut = wave_maxf(top) * 0.99999f;
-                float best = 0.0f;
 #pragma unroll
-                for (int k = 0; k < TS; ++k) {
-                    const bool want = odd[k] || (h[k] > 0.0f && near[k] >= cut);
-                    if (__ballot(want) == 0) continue;
-                    const float cub = d2[k] > 0.0f ? fminf(1.0f, h[k] / sqrtf(d2[k])) : 1.0f;
-                    const float b = cub / fmaxf(d2[k], r_min2) * m[k];
-                    const float r = b > 0.0f ? b * inv[k] : 0.0f;
-                    best = fmaxf(best, want ? r : 0.0f);
-                }
-                best = wave_maxf(best);
-                if (lane == 0 && best > 0.0f) atomicMax(&rho[i0 + i], __float_as_uint(best));
+                for (int k = 0; k < TS; ++k) want[k] = want[k] && near[k] >= cut;
             }
+            float best = 0.0f;
+#pragma unroll
+            for (int k = 0; k < TS; ++k) {
+                if (__ballot(want[k]) == 0) continue;
+                const float cub = d2[k] > 0.0f ? fminf(1.0f, h[k] / sqrtf(d2[k])) : 1.0f;
+                const float b = cub / fmaxf(d2[k], r_min2) * m[k];
+                const float r = b > 0.0f ? b * inv[k] : 0.0f;
+                best = fmaxf(best, want[k] ? r : 0.0f);
+            }
+            best = wave_maxf(best);
+            if (lane == 0 && best > 0.0f) atomicMax(&rho[k_node], __float_as_uint(best));
+        };
+        const int first = (int)(blockIdx.x % per) * ng;
+        if (ng == 1) {
+            for (int i = first; i < nf; i += per) {
+                const int f = cur[i];
+                if (f < v.n) continue;               // a single VPL: exact, never split
+                ratios(i, v.bbox[f], v.bbox[N + f], v.bbox[2 * N + f], v.bbox[3 * N + f], v.bbox[4 * N + f],
+                       v.bbox[5 * N + f], v.lights[6 * N + f], v.lights[7 * N + f], v.lights[8 * N + f]);
+            }
+            continue;
+        }
+        for (int i0 = first; i0 < nf; i0 += per * ng) {
+            const int cnt = min(ng, nf - i0);
+            if (own < cnt) {
+                const int f = cur[i0 + own];
+                nd[pl][own] = pl < 6 ? v.bbox[pl * N + f] : v.lights[pl * N + f];
+                if (pl == 0) {
+                    nd[8][own] = v.lights[8 * N + f];
+                    id[own] = f;
+                }
+            }
+            __syncthreads();
+            for (int i = 0; i < cnt; ++i)
+                if (id[i] >= v.n)
+                    ratios(i0 + i, nd[0][i], nd[1][i], nd[2][i], nd[3][i], nd[4][i], nd[5][i], nd[6][i], nd[7][i], nd[8][i]);
+            __syncthreads();
         }
     }
 }
