@@ -39,9 +39,9 @@ namespace {
 // address (on the host it is only a stand-in for the device symbol): the
 // device address comes from hipGetSymbolAddress, once per device, below.
 // Its limit on a frame leaves out the tables that only save time (core_total);
-// they have STATIC_TABLE_BYTES beside it, of which the Gram parts and the
-// depth-first tree never need more than a quarter of the frame's own size, and
-// the coarsening's top table is left out of a plan where it does not fit.
+// they have STATIC_TABLE_BYTES beside it, of which the depth-first half of the
+// tree never needs more than a quarter of the frame's own size, and the
+// coarsening's top table is left out of a plan where it does not fit.
 constexpr size_t STATIC_TABLE_BYTES = 16u << 20;
 constexpr size_t STATIC_TOTAL_BYTES = VPLMC_STATIC_WORKSPACE_BYTES + STATIC_TABLE_BYTES;
 __device__ __align__(256) unsigned char scratch[STATIC_TOTAL_BYTES];
@@ -600,7 +600,7 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
     // global-memory completion: row and column blocks of every slice, as prefixes
     // per group (the launch grids), and the squared-residual slot of each row block
     plan->gblk.clear();
-    int64_t e2b = 0, gpart = 0;
+    int64_t e2b = 0;
     for (int g = 1; g < 8; g += 2) {
         int64_t blocks = 0;
         for (int32_t sl : plan->groups[g]) blocks += ((int64_t)plan->desc[sl].n + GADM_CB - 1) / GADM_CB;
@@ -621,9 +621,6 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
         plan->g_cols[g] = c;
         plan->ge2_base[g] = e2b;
         e2b += r;
-        plan->gpart_base[g] = gpart;
-        const int64_t q = 4 << (g / 2);
-        if (!plan->als) gpart += (2 * r + c) * q * q;
     }
     plan->tot1 = o1;
     plan->tot2 = o2;
@@ -711,7 +708,6 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
     bool any_global = false;
     for (int g = 1; g < 8; g += 2) any_global = any_global || !plan->groups[g].empty();
     bytes[R_GSYS] = any_global ? (size_t)S * GADM_SYS_BYTES : 0;
-    bytes[R_GPART] = (size_t)gpart * 4;
     bytes[R_GE2] = (size_t)e2b * 8 * (plan->als ? ALS_E2_SLOTS : 1);
     bytes[R_COLW_PREFIX] = oc * 8;
     bytes[R_BITMAP] = obm * 4;
@@ -755,12 +751,12 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
         L.total = off;
     };
     lay_out();
-    // the workspace without the tables that only save time: top table, Gram
-    // parts, depth-first half of the tree, ALS residual slots but one; and with
-    // the two residual sums per part that the completion once kept
+    // the workspace without the tables that only save time: top table, depth-first
+    // half of the tree, ALS residual slots but one; and with the two residual sums
+    // per part that the completion once kept
     size_t core[R_INTERNAL_END];
     std::copy(bytes, bytes + R_INTERNAL_END, core);
-    core[R_TOP] = core[R_TOP_MAP] = core[R_GPART] = 0;
+    core[R_TOP] = core[R_TOP_MAP] = 0;
     if (co) {
         const int64_t ng = co->n_leaves, ns = ng - 1, nodes = 2 * ng - 1;
         core[R_TREE] = (3 * ns + 3 * nodes + plan->height_max + 1) * 4;
@@ -1030,7 +1026,7 @@ int vplmc_render(vplmc_ctx *ctx, const vplmc_plan *plan, const vplmc_points *poi
                         region<int32_t>(ws, plan, R_YP), stats);
     else
         rc = launch_adm(st, &ctx->adm, *plan, ctx->n_cu, desc, ids, ids + S, region<char>(ws, plan, R_GSYS),
-                        region<double>(ws, plan, R_GE2), region<float>(ws, plan, R_GPART), region<int32_t>(ws, plan, R_QUEUE), *params,
+                        region<double>(ws, plan, R_GE2), region<int32_t>(ws, plan, R_QUEUE), *params,
                         row_ptr, csr_col, csr_val, col_ptr, csc_row, csc_val, ell, X, region<float>(ws, plan, R_XNEXT),
                         region<float>(ws, plan, R_XP), region<float>(ws, plan, R_LAMBDA), Y,
                         region<float>(ws, plan, R_YP), region<float>(ws, plan, R_PI), region<float>(ws, plan, R_YT),
@@ -1396,7 +1392,7 @@ int vplmc_stage_adm(vplmc_ctx *ctx, const vplmc_plan *plan, const vplmc_params *
                         region<int32_t>(ws, plan, R_YP), stats);
     else
         rc = launch_adm(st, &ctx->adm, *plan, ctx->n_cu, desc, ids, ids + plan->n_slices, region<char>(ws, plan, R_GSYS),
-                        region<double>(ws, plan, R_GE2), region<float>(ws, plan, R_GPART), region<int32_t>(ws, plan, R_QUEUE), *params,
+                        region<double>(ws, plan, R_GE2), region<int32_t>(ws, plan, R_QUEUE), *params,
                         row_ptr, csr_col, csr_val, col_ptr, csc_row, csc_val, ell, X, region<float>(ws, plan, R_XNEXT),
                         region<float>(ws, plan, R_XP), region<float>(ws, plan, R_LAMBDA), Y,
                         region<float>(ws, plan, R_YP), region<float>(ws, plan, R_PI), region<float>(ws, plan, R_YT),

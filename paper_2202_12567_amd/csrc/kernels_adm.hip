@@ -1020,7 +1020,7 @@ int launch_adm_ell(hipStream_t st, int threads, size_t count, int max_m, const i
 }  // namespace
 
 int launch_adm(hipStream_t st, const AdmStreams *ss, const vplmc_plan &plan, int n_cu, const SliceDesc *desc,
-               const int32_t *ids_dev, const int32_t *gblk_dev, char *gsys, double *ge2, float *gpart,
+               const int32_t *ids_dev, const int32_t *gblk_dev, char *gsys, double *ge2,
                int32_t *queues, const vplmc_params &prm, const int32_t *row_ptr, const int32_t *csr_col,
                const float *csr_val, const int32_t *col_ptr, const int32_t *csc_row, const float *csc_val,
                const EllView &ell, float *X, float *Xn, float *Xp, float *Lam, float *Y, float *Yp, float *Pi,
@@ -1049,14 +1049,14 @@ int launch_adm(hipStream_t st, const AdmStreams *ss, const vplmc_plan &plan, int
         }
     }
     // rank 32 never fits in LDS (group 6 is empty)
-    int rc = launch_gadm_group(sb[3], 32, plan, 7, id[7], gblk_dev, gsys, ge2, gpart, desc, prm, row_ptr, csr_col,
+    int rc = launch_gadm_group(sb[3], 32, plan, 7, id[7], gblk_dev, gsys, ge2, desc, prm, row_ptr, csr_col,
                                csr_val, col_ptr, csc_row, csc_val, X, Xn, Xp, Lam, Y, Yp, Pi, scale, stats);
 #define VPLMC_ADM_PAIR(B, Q, TG)                                                                                      \
     if (!rc)                                                                                                          \
         rc = launch_adm_ell<Q>(sb[B], thr, plan.groups[2 * B].size(), plan.group_max_m[2 * B], id[2 * B], qp(2 * B), \
                                n_cu, desc, prm, col_ptr, ell, X, Xp, Lam, Y, Yp, Pi, Yt, red, e2part, scale, stats); \
     if (!rc)                                                                                                          \
-        rc = launch_gadm_group(sb[B], Q, plan, 2 * B + 1, id[2 * B + 1], gblk_dev, gsys, ge2, gpart, desc, prm, row_ptr,  \
+        rc = launch_gadm_group(sb[B], Q, plan, 2 * B + 1, id[2 * B + 1], gblk_dev, gsys, ge2, desc, prm, row_ptr,  \
                                csr_col, csr_val, col_ptr, csc_row, csc_val, X, Xn, Xp, Lam, Y, Yp, Pi, scale, stats);
     VPLMC_ADM_PAIR(2, 16, 512)
     VPLMC_ADM_PAIR(1, 8, 512)

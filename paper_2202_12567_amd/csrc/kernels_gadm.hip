@@ -5,31 +5,18 @@
 // waits for another):
 //   init    (workgroup per slice)  scale, initial factors, GY, X system
 //   rows    (per 64-row block)     residuals of the row's samples, R_i Y^T,
-//                                  X+_i = X_i F + T_i Inv, U, Lambda (q/4 lanes per row),
-//                                  the block's part of GX = X+^T X+ and C = X+^T X
-//   ysys    (workgroup per slice)  residual norm and the stop test, GX and C from
-//                                  their parts, Y system
-//   cols    (per column block)     residuals again from X and Y, X+^T R_j,
-//                                  Y+_j = F Y_j + Inv T_j, V, Pi (q/4 lanes per column),
-//                                  the block's part of GY = Y+^T Y+
-//   xsys    (workgroup per slice)  GY from its parts, X system for the next iteration
+//                                  X+_i = X_i F + T_i Inv, U, Lambda (q/4 lanes per row)
+//   ysys    (workgroup per slice)  residual norm and the stop test, GX = X+^T X+,
+//                                  C = X+^T X, Y system
+//   cols    (per column block) residuals again from X and Y, X+^T R_j,
+//                                  Y+_j = F Y_j + Inv T_j, V, Pi (q/4 lanes per column)
+//   xsys    (workgroup per slice)  GY = Y+^T Y+, X system for the next iteration
 //   final   (workgroup per slice)  the final X into the X region, statistics
 // The two X buffers alternate by iteration parity.  The q x q systems (the X
 // system in FP64, the Y system's FP32 rounding) and the slice's stop state live in
 // GADM_SYS_BYTES per slice.  The iteration is the one the LDS-resident kernel
 // runs (Appendix A, in the sparse-residual form of kernels_adm.hip); the Grams
 // are sums in a fixed order, so results are bitwise reproducible.
-//
-// Bound by the latency of the dependent gathers (sample index, then the factor
-// rows it names).  Measured on one MI355X, 96 slices of 300-1,024 rows, 512
-// columns, rank 32, 6.5% sampled, per iteration (us): cols 195, rows 62, ysys
-// 97, xsys 84 with 256-column blocks (192 workgroups) and the Grams streamed by
-// the system launches before a workgroup-wide Cholesky inverse; 99, 69, 22, 19
-// with 64-column blocks, Gram parts formed where the rows and columns are
-// written and the inverse by Gauss-Jordan in registers.  32-column blocks took
-// 109 for cols, four wavefronts per SIMD there 112, batches of two or eight
-// samples 122 / 103; Gram accumulators kept through the row passes cost a
-// wavefront per SIMD (rows 82).
 
 #include "adm_common.h"
 
@@ -63,7 +50,6 @@ struct GadmArgs {
     int32_t *stats_all;
     char *gsys;
     double *ge2;                         // the group's first row block slot
-    float *xpart, *ypart;                // Gram parts: 2 Q Q per row block of the group, Q Q per column block
     int32_t cb;                          // columns per column block
 };
 
@@ -144,108 +130,172 @@ __device__ __forceinline__ int block_slice(const int32_t *__restrict__ pre, int 
     return lo;
 }
 
-// ---- Gram parts on the FP32 matrix unit (v_mfma_f32_16x16x4: lane l holds
-// row l / 16 of four, component l % 16; register v of the result is
-// [4 (l / 16) + v][l % 16] of a 16 x 16 tile) ----
-typedef float f4 __attribute__((ext_vector_type(4)));
-template <int Q>
-struct GramTiles {
-    static constexpr int NB = Q <= 16 ? 1 : Q / 16;      // 16-component blocks
-    static constexpr int N = NB * NB;
-};
-// component 16 h + l % 16 of row `row` of rows of stride ld (0 where there is none)
-template <int Q>
-__device__ __forceinline__ float gram_operand(const float *rows, int ld, int row, int h, int lane) {
-    const int c = 16 * h + lane % 16;
-    return c < Q ? rows[row * ld + c] : 0.f;
-}
-// tile (ha, hb) of a Q x Q result into G
-template <int Q>
-__device__ __forceinline__ void gram_tile_store(const f4 &d, int ha, int hb, int lane, float *G) {
+// Cross Gram C = A^T B of two (rows x Q) FP32 matrices into sh.C, streamed
+// through LDS like gram_rows (half a stage each).
+template <int Q, int PCAP, int THREADS>
+__device__ void gram_cross(AdmShared<Q> &sh, const float *__restrict__ A, const float *__restrict__ B, int rows,
+                           float *part, float *stage) {
+    constexpr int P = Q * Q, QB = Q / 4, NB = QB * QB;
+    constexpr int HALF = GADM_STAGE / 2;
+    constexpr int TR = HALF / Q;
+    constexpr int NL = HALF / 4 / THREADS;
+    static_assert(NL >= 1 && NL * 4 * THREADS == HALF, "tile split");
+    const int t = fresh_tid();
+    const int groups = min(THREADS / NB, PCAP / P);
+    const int g = t / NB, blk = t % NB;
+    const int a0 = 4 * (blk / QB), b0 = 4 * (blk % QB);
+    const float4 *A4 = reinterpret_cast<const float4 *>(A);
+    const float4 *B4 = reinterpret_cast<const float4 *>(B);
+    const int64_t tot4 = (int64_t)rows * (Q / 4);
+    const int ntiles = (rows + TR - 1) / TR;
+    float acc[4][4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int a = 16 * ha + 4 * (lane / 16) + v, b = 16 * hb + lane % 16;
-        if (a < Q && b < Q) G[a * Q + b] = d[v];
-    }
-}
-
-// The Q x Q systems of a slice on one workgroup, thread t owning EPT
-// consecutive elements of a row (the first Q Q / EPT threads).
-template <int Q, int THREADS>
-struct SysShape {
-    static constexpr int EPT = Q * Q >= THREADS ? Q * Q / THREADS : 1;
-    static constexpr int NT = Q * Q / EPT;               // threads at work
-    static_assert(EPT <= Q && Q % EPT == 0 && NT <= THREADS, "elements of one row per thread");
-};
-template <int Q>
-struct SysShared {
-    double row[2][Q], col[2][Q];                         // pivot row and column of a step, by parity
-    double Inv[Q * Q];
-    float G[Q * Q], C[Q * Q];
-};
-
-// sum of n parts (stride floats apart) of the thread's elements, in part order, FP64
-template <int EPT>
-__device__ __forceinline__ void sum_parts(const float *__restrict__ part, int64_t stride, int n, int at, float (&g)[EPT]) {
-    double v[EPT];
+    for (int x = 0; x < 4; ++x)
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) v[e] = 0.0;
-#pragma unroll 4
-    for (int b = 0; b < n; ++b)
+        for (int y = 0; y < 4; ++y) acc[x][y] = 0.f;
+    float4 *sa = reinterpret_cast<float4 *>(stage);
+    float4 *sb = reinterpret_cast<float4 *>(stage + HALF);
+    for (int tile = 0; tile < ntiles; ++tile) {
+        float4 ba[NL], bb[NL];
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) v[e] += (double)part[b * stride + at + e];
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) g[e] = (float)v[e];
-}
-
-// 1 / x for normal x: the hardware's estimate and two Newton steps (a step's
-// dependent chain holds this value up, and the exactly rounded division is a
-// chain of some twenty instructions)
-__device__ __forceinline__ double fast_rcp(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
-}
-
-// sh.Inv = (G + shift I)^-1 in FP64 by Gauss-Jordan elimination in place (the
-// matrix is symmetric positive definite, so no pivoting): the elements stay in
-// registers, a step's pivot row and column go through LDS, one barrier per
-// step.  All threads call.
-template <int Q, int THREADS>
-__device__ __forceinline__ void gj_inverse(SysShared<Q> &sh, const float (&g)[SysShape<Q, THREADS>::EPT], double shift) {
-    using S = SysShape<Q, THREADS>;
-    const int t = threadIdx.x;
-    const int i = (t * S::EPT) / Q, k0 = (t * S::EPT) % Q;
-    const bool on = t < S::NT;
-    double a[S::EPT];
-#pragma unroll
-    for (int e = 0; e < S::EPT; ++e) a[e] = (double)g[e] + (i == k0 + e ? shift : 0.0);
-    for (int j = 0; j < Q; ++j) {
-        const int par = j & 1;
-        if (on) {
-            if (i == j) {
-#pragma unroll
-                for (int e = 0; e < S::EPT; ++e) sh.row[par][k0 + e] = a[e];
-            }
-#pragma unroll
-            for (int e = 0; e < S::EPT; ++e)
-                if (k0 + e == j) sh.col[par][i] = a[e];
+        for (int u = 0; u < NL; ++u) {
+            const int64_t idx = (int64_t)tile * (HALF / 4) + u * THREADS + t;
+            ba[u] = idx < tot4 ? A4[idx] : make_float4(0.f, 0.f, 0.f, 0.f);
+            bb[u] = idx < tot4 ? B4[idx] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
         __syncthreads();
-        if (on) {
-            const double p = fast_rcp(sh.row[par][j]);
-            const double f = sh.col[par][i] * p;
 #pragma unroll
-            for (int e = 0; e < S::EPT; ++e) {
-                const int k = k0 + e;
-                if (i == j) a[e] = k == j ? p : a[e] * p;
-                else a[e] = k == j ? -f : fma(-f, sh.row[par][k], a[e]);
+        for (int u = 0; u < NL; ++u) {
+            sa[u * THREADS + t] = ba[u];
+            sb[u * THREADS + t] = bb[u];
+        }
+        __syncthreads();
+        const int rt = min(TR, rows - tile * TR);
+        if (g < groups) {
+            for (int r = g; r < rt; r += groups) {
+                const float4 u = sa[(r * Q + a0) / 4];
+                const float4 v = sb[(r * Q + b0) / 4];
+                const float ua[4] = {u.x, u.y, u.z, u.w}, vb[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) acc[x][y] = fmaf(ua[x], vb[y], acc[x][y]);
             }
         }
     }
-    if (on) {
+    if (g < groups) {
 #pragma unroll
-        for (int e = 0; e < S::EPT; ++e) sh.Inv[i * Q + k0 + e] = a[e];
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) part[g * P + (a0 + x) * Q + b0 + y] = acc[x][y];
+    }
+    __syncthreads();
+    for (int e = t; e < P; e += THREADS) {
+        float v = 0.f;
+        for (int gg = 0; gg < groups; ++gg) v += part[gg * P + e];
+        sh.C[e] = v;
+    }
+    __syncthreads();
+}
+
+// The Grams of ranks 16 and 32 on the FP32 matrix unit, in the summation order of
+// gram_rows and gram_cross: the rows fall into CH chains (row r into chain r % CH),
+// each one fma after the other, and the chains are added in order.  A
+// v_mfma_f32_16x16x1_4b_f32 is one fma on each element of four 16 x 16 tiles, one per 16
+// lanes: lane 16 b + l holds component l of the row of chain b, register 4 b + v of the
+// result is chain b's [4 (l / 16) + v][l % 16].  The completion can amplify rounding
+// by orders of magnitude, so a faster order of the same sums is no option (parts per
+// row block moved ill-conditioned slices by 1e-4).
+typedef float f16v __attribute__((ext_vector_type(16)));
+template <int Q, int THREADS>
+struct GramChains {
+    static constexpr int NW = THREADS / WAVE;
+    static constexpr int PCAP = (NW * Q * Q > 2 * 1024) ? NW * Q * Q : 2 * 1024;
+    static constexpr int CH = THREADS / (Q * Q / 16) < PCAP / (Q * Q) ? THREADS / (Q * Q / 16) : PCAP / (Q * Q);
+    static constexpr int NB = Q / 16, SYM = NB * (NB + 1) / 2, SETS = CH / 4;
+    static constexpr int STEP = 16;             // rows / CH loaded at once
+    static_assert(Q >= 16 && CH % 4 == 0 && (GADM_STAGE / Q) % CH == 0 && (GADM_STAGE / 2 / Q) % CH == 0, "whole chains per tile");
+};
+
+// tile (ha, hb) of A^T B, every chain, into part[chain][Q Q] (and mirrored, for a Gram)
+template <int Q, int THREADS>
+__device__ __forceinline__ void gram_tile(const float *__restrict__ A, const float *__restrict__ B, int rows, int ha, int hb,
+                                          bool mirror, float *part) {
+    using C = GramChains<Q, THREADS>;
+    constexpr int STEP = C::STEP / C::SETS;
+    const int lane = fresh_tid() % WAVE, c = lane % 16, b = lane / 16;
+    f16v acc[C::SETS];
+#pragma unroll
+    for (int u = 0; u < C::SETS; ++u)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[u][v] = 0.f;
+    const float *pa = A + 16 * ha + c, *pb = B + 16 * hb + c;
+    auto load = [&](int r0, float *x, float *y) {
+#pragma unroll
+        for (int u = 0; u < STEP * C::SETS; ++u) {
+            const int r = min(r0 + 4 * u + b, rows - 1);
+            x[u] = pa[(int64_t)r * Q];
+            y[u] = pb[(int64_t)r * Q];
+        }
+    };
+    auto add = [&](int r0, const float *x, const float *y) {
+#pragma unroll
+        for (int u = 0; u < STEP * C::SETS; ++u) {
+            const bool in = r0 + 4 * u + b < rows;
+            acc[u % C::SETS] =
+                __builtin_amdgcn_mfma_f32_16x16x1f32(in ? x[u] : 0.f, in ? y[u] : 0.f, acc[u % C::SETS], 0, 0, 0);
+        }
+    };
+    // two blocks of rows in turn, one in flight while the other is added
+    constexpr int N = 4 * STEP * C::SETS;
+    if (rows > 0) {
+        float xa[STEP * C::SETS], ya[STEP * C::SETS], xb[STEP * C::SETS], yb[STEP * C::SETS];
+        load(0, xa, ya);
+        for (int r0 = 0;; r0 += 2 * N) {
+            load(r0 + N, xb, yb);
+            add(r0, xa, ya);
+            if (r0 + N >= rows) break;
+            load(r0 + 2 * N, xa, ya);
+            add(r0 + N, xb, yb);
+            if (r0 + 2 * N >= rows) break;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < C::SETS; ++u)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            float *p = part + (4 * u + v / 4) * Q * Q;
+            const int i = 16 * ha + 4 * b + v % 4, j = 16 * hb + c;
+            p[i * Q + j] = acc[u][v];
+            if (mirror) p[j * Q + i] = acc[u][v];
+        }
+}
+
+// sh.G = A^T A and, given X, sh.C = A^T X
+template <int Q, int THREADS>
+__device__ void gram_chains(AdmShared<Q> &sh, const float *__restrict__ A, const float *__restrict__ X, int rows, float *part) {
+    using C = GramChains<Q, THREADS>;
+    const int t = fresh_tid(), wave = __builtin_amdgcn_readfirstlane(t / WAVE);
+    const int jobs = C::SYM + (X ? C::NB * C::NB : 0);
+    for (int job = wave; job < jobs; job += C::NW) {
+        if (job < C::SYM) {
+            const int hb = job == 0 ? 0 : 1, ha = job == 2 ? 1 : 0;      // (0, 0), (0, 1), (1, 1)
+            gram_tile<Q, THREADS>(A, A, rows, ha, hb, ha != hb, part);
+        } else {
+            const int k = job - C::SYM;
+            gram_tile<Q, THREADS>(A, X, rows, k / C::NB, k % C::NB, false, part + C::CH * Q * Q);
+        }
+    }
+    __syncthreads();
+    for (int e = t; e < Q * Q; e += THREADS) {
+        float v = 0.f;
+        for (int g = 0; g < C::CH; ++g) v += part[g * Q * Q + e];
+        sh.G[e] = v;
+        if (X) {
+            v = 0.f;
+            for (int g = 0; g < C::CH; ++g) v += part[(C::CH + g) * Q * Q + e];
+            sh.C[e] = v;
+        }
     }
     __syncthreads();
 }
@@ -575,76 +625,56 @@ __global__ __launch_bounds__(THREADS) void k_gadm_rows(GadmArgs a, int it) {
     e2 = wave_sum_d(e2);
     __shared__ double red[NW];
     if (lane == 0) red[wave] = e2;
-    __threadfence_block();
     __syncthreads();
     if (t == 0) {
         double tot = 0.0;
         for (int w = 0; w < NW; ++w) tot += red[w];
         a.ge2[b] = tot;
     }
-    // the block's parts of X+^T X+ and X+^T X from the rows it has just written
-    // (in the caches), the tiles dealt to the wavefronts: accumulators kept
-    // through the rows would cost a wavefront per SIMD
-    using GT = GramTiles<Q>;
-    float *part = a.xpart + (int64_t)b * 2 * Q * Q;
-    for (int tile = wave; tile < 2 * GT::N; tile += NW) {
-        const int which = tile / GT::N, ha = tile % GT::N / GT::NB, hb = tile % GT::NB;
-        const float *A = Xn + (size_t)r_beg * Q, *B = (which ? X : Xn) + (size_t)r_beg * Q;
-        f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-        for (int r0 = 0; r0 < GADM_RB; r0 += 4) {
-            const int r = min(r0 + lane / 16, nloc - 1);
-            const bool in = r0 + lane / 16 < nloc;
-            const float u = gram_operand<Q>(A, Q, r, ha, lane), v = gram_operand<Q>(B, Q, r, hb, lane);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? u : 0.f, in ? v : 0.f, acc, 0, 0, 0);
-        }
-        gram_tile_store<Q>(acc, ha, hb, lane, part + which * Q * Q);
-    }
 }
 
 template <int Q, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_gadm_ysys(GadmArgs a, int it) {
-    using S = SysShape<Q, THREADS>;
-    __shared__ SysShared<Q> sh;
+    constexpr int NW = THREADS / WAVE;
+    __shared__ AdmShared<Q> sh;
+    constexpr int PCAP = (NW * Q * Q > 2 * 1024) ? NW * Q * Q : 2 * 1024;
+    constexpr bool CHAINS = Q >= 16;
+    __shared__ float part[(CHAINS ? 2 : 1) * PCAP];
+    __shared__ __align__(16) float stage[CHAINS ? 4 : GADM_STAGE];
     __shared__ int stop_s;
     const int k = blockIdx.x;
     const int s = __builtin_amdgcn_readfirstlane(a.ids[k]);
     const GSys g = gsys_of(a.gsys, s);
     if (g.state[0]) return;
     const SliceDesc d = a.desc[s];
+    const int m = d.m, qr = d.qr;
     const int t = threadIdx.x;
-    const int rb0 = a.rowp[k], nrb = a.rowp[k + 1] - rb0;
-    if (t < WAVE) {
-        // the squared residuals of the slice's row blocks, in a fixed order
+    if (t == 0) {
+        // the squared residuals of the slice's row blocks, in block order
         double e2 = 0.0;
-        for (int rb = t; rb < nrb; rb += WAVE) e2 += a.ge2[rb0 + rb];
-        e2 = wave_sum_d(e2);
-        if (t == 0) {
-            const double err = sqrt(e2) / g.dstate[0];
-            g.state[2] = __float_as_int((float)err);
-            const bool stop = !(a.mode & 1) && err < (double)a.tol;
-            if (stop) {
-                g.state[0] = 1;
-                g.state[1] = it;
-            }
-            stop_s = stop ? 1 : 0;
+        for (int rb = a.rowp[k]; rb < a.rowp[k + 1]; ++rb) e2 += a.ge2[rb];
+        const double err = sqrt(e2) / g.dstate[0];
+        g.state[2] = __float_as_int((float)err);
+        const bool stop = !(a.mode & 1) && err < (double)a.tol;
+        if (stop) {
+            g.state[0] = 1;
+            g.state[1] = it;
         }
-    }
-    // GX and C from their parts
-    const float *part = a.xpart + (int64_t)rb0 * 2 * Q * Q;
-    float gx[S::EPT], cx[S::EPT];
-    const int at = min(t, S::NT - 1) * S::EPT;
-    sum_parts<S::EPT>(part, 2 * Q * Q, nrb, at, gx);
-    sum_parts<S::EPT>(part + Q * Q, 2 * Q * Q, nrb, at, cx);
-    if (t < S::NT) {
-#pragma unroll
-        for (int e = 0; e < S::EPT; ++e) sh.C[at + e] = cx[e];
+        stop_s = stop ? 1 : 0;
     }
     __syncthreads();
     if (stop_s) return;
+    const float *X = ((it & 1) ? a.Xn_all : a.X_all) + d.off_x;
+    const float *Xn = ((it & 1) ? a.X_all : a.Xn_all) + d.off_x;
+    if constexpr (CHAINS) {
+        gram_chains<Q, THREADS>(sh, Xn, X, m, part);
+    } else {
+        gram_rows<Q, PCAP, THREADS, GADM_STAGE>(sh, Xn, m, part, stage);
+        gram_cross<Q, PCAP, THREADS>(sh, Xn, X, m, part, stage);
+    }
     // the Y system; the column launch reads its FP32 rounding
-    const double beta = (double)a.beta0 * (double)d.m / d.qr;
-    gj_inverse<Q, THREADS>(sh, gx, beta);
+    const double beta = (double)a.beta0 * (double)m / qr;
+    spd_inverse<Q>(sh, beta);
     for (int e = t; e < Q * Q; e += THREADS) {
         const int aa = e / Q, bb = e % Q;   // Ff[a][b] = sum_l Inv[a][l] C[l][b]
         double v = 0.0;
@@ -671,7 +701,6 @@ __global__ __launch_bounds__(THREADS) void k_gadm_cols(GadmArgs a, int it) {
     __shared__ __align__(16) float Ft[Q * Q];    // Ft[l][k] = (Inv C)[k][l]
     __shared__ __align__(16) float It[Q * Q];    // It[l][k] = Inv[k][l]
     __shared__ __align__(16) float stage[NW * G * 6 * Q];   // per column slot: Y_j (3q), T_j (3q)
-    static_assert(NW * G * 6 * Q >= NW * Q * Q, "the wavefronts' Gram parts reuse the slots");
     __shared__ int order[GADM_CB];                          // the block's columns by decreasing count
     static_assert(GADM_CB <= THREADS, "one column of a block per thread in the sort");
     const int b = xcd_item(blockIdx.x, gridDim.x);
@@ -766,8 +795,7 @@ __global__ __launch_bounds__(THREADS) void k_gadm_cols(GadmArgs a, int it) {
         }
     };
     // components k0..k0+3 of Y+_j for the three channels, then U, P and Y
-    // (Y+_j also replaces Y_j in the slot, for the Gram)
-    auto finish_column = [&](int j, float *wst, const float (&pv)[3][4]) {
+    auto finish_column = [&](int j, const float *wst, const float (&pv)[3][4]) {
         float o[3][4];
 #pragma unroll
         for (int c = 0; c < 3; ++c)
@@ -806,26 +834,6 @@ __global__ __launch_bounds__(THREADS) void k_gadm_cols(GadmArgs a, int it) {
             *reinterpret_cast<float4 *>(Yp + w) = make_float4(un[0], un[1], un[2], un[3]);
             *reinterpret_cast<float4 *>(Pi + w) = make_float4(pn[0], pn[1], pn[2], pn[3]);
             *reinterpret_cast<float4 *>(Y + w) = make_float4(o[c][0], o[c][1], o[c][2], o[c][3]);
-            *reinterpret_cast<float4 *>(wst + c * Q + k0) = make_float4(o[c][0], o[c][1], o[c][2], o[c][3]);
-        }
-    };
-    // the wavefront's part of Y+^T Y+: `cols` columns in its slots, three rows each
-    using GT = GramTiles<Q>;
-    f4 gy[GT::N];
-#pragma unroll
-    for (int u = 0; u < GT::N; ++u) gy[u] = f4{0.f, 0.f, 0.f, 0.f};
-    auto gram_slots = [&](const float *base, int cols) {
-        for (int r0 = 0; r0 < 3 * cols; r0 += 4) {
-            const int r = r0 + lane / 16;                 // row r: channel r % 3 of the slot r / 3
-            const float *y = base + (r / 3) * 6 * Q + (r % 3) * Q;
-            float v[GT::NB];
-#pragma unroll
-            for (int h = 0; h < GT::NB; ++h) v[h] = r < 3 * cols ? gram_operand<Q>(y, 0, 0, h, lane) : 0.f;
-#pragma unroll
-            for (int h = 0; h < GT::NB; ++h)
-#pragma unroll
-                for (int k = 0; k < GT::NB; ++k)
-                    gy[h * GT::NB + k] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[h], v[k], gy[h * GT::NB + k], 0, 0, 0);
         }
     };
 
@@ -859,8 +867,6 @@ __global__ __launch_bounds__(THREADS) void k_gadm_cols(GadmArgs a, int it) {
         wave_lds_sync();
         if (slot == 0) finish_column(jh, hst, pv);
         wave_lds_sync();
-        gram_slots(hst, 1);
-        wave_lds_sync();
     }
     // the others side by side, G to a pass; the pass's first is its longest
     for (int pb = n_heavy + wave * G; pb < nloc; pb += NW * G) {
@@ -884,51 +890,29 @@ __global__ __launch_bounds__(THREADS) void k_gadm_cols(GadmArgs a, int it) {
         if (in) stage_column(j, y, acc, wst, pv);
         wave_lds_sync();
         if (in) finish_column(j, wst, pv);
-        wave_lds_sync();
-        gram_slots(stage + wave * G * 6 * Q, min(G, nloc - pb));
         // the next column's stage overwrites this slot
         wave_lds_sync();
-    }
-    // the block's part: the wavefronts' in wavefront order
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < GT::NB; ++h)
-#pragma unroll
-        for (int k = 0; k < GT::NB; ++k) gram_tile_store<Q>(gy[h * GT::NB + k], h, k, lane, stage + wave * Q * Q);
-    __syncthreads();
-    float *part = a.ypart + (int64_t)b * Q * Q;
-    for (int e = t; e < Q * Q; e += THREADS) {
-        float v = 0.f;
-        for (int w = 0; w < NW; ++w) v += stage[w * Q * Q + e];
-        part[e] = v;
     }
 }
 
 template <int Q, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_gadm_xsys(GadmArgs a, int it) {
-    using S = SysShape<Q, THREADS>;
-    __shared__ SysShared<Q> sh;
-    const int k = blockIdx.x;
-    const int s = __builtin_amdgcn_readfirstlane(a.ids[k]);
+    constexpr int NW = THREADS / WAVE;
+    __shared__ AdmShared<Q> sh;
+    constexpr int PCAP = (NW * Q * Q > 2 * 1024) ? NW * Q * Q : 2 * 1024;
+    __shared__ float part[PCAP];
+    constexpr bool CHAINS = Q >= 16;
+    __shared__ __align__(16) float stage[CHAINS ? 4 : GADM_STAGE];
+    const int s = __builtin_amdgcn_readfirstlane(a.ids[blockIdx.x]);
     const GSys g = gsys_of(a.gsys, s);
     if (g.state[0]) return;
     const SliceDesc d = a.desc[s];
-    const int t = threadIdx.x, cb0 = a.colp[k], ncb = a.colp[k + 1] - cb0;
-    float gy[S::EPT];
-    const int at = min(t, S::NT - 1) * S::EPT;
-    sum_parts<S::EPT>(a.ypart + (int64_t)cb0 * Q * Q, Q * Q, ncb, at, gy);
-    if (t < S::NT) {
-#pragma unroll
-        for (int e = 0; e < S::EPT; ++e) sh.G[at + e] = gy[e];
-    }
-    gj_inverse<Q, THREADS>(sh, gy, (double)a.alpha0 * (3.0 * d.n) / d.qr);
-    for (int e = t; e < Q * Q; e += THREADS) {
-        const int aa = e / Q, bb = e % Q;
-        double v = 0.0;
-        for (int l = 0; l < Q; ++l) v += (double)sh.G[aa * Q + l] * sh.Inv[l * Q + bb];
-        g.F[e] = v;
-        g.Inv[e] = sh.Inv[e];
-    }
+    const float *Y = a.Y_all + d.off_y;
+    if constexpr (CHAINS)
+        gram_chains<Q, THREADS>(sh, Y, nullptr, 3 * d.n, part);
+    else
+        gram_rows<Q, PCAP, THREADS, GADM_STAGE>(sh, Y, 3 * d.n, part, stage);
+    gadm_x_system<Q, THREADS>(sh, g, (double)a.alpha0 * (3.0 * d.n) / d.qr);
     (void)it;
 }
 
@@ -957,7 +941,7 @@ __global__ __launch_bounds__(THREADS) void k_gadm_final(GadmArgs a) {
 // init launch, four launches per iteration, a final launch
 template <int Q, int THREADS>
 int launch_gadm(hipStream_t st, const vplmc_plan &plan, int grp, const int32_t *ids, const int32_t *gblk_dev,
-                char *gsys, double *ge2, float *gpart, const SliceDesc *desc, const vplmc_params &prm, const int32_t *row_ptr,
+                char *gsys, double *ge2, const SliceDesc *desc, const vplmc_params &prm, const int32_t *row_ptr,
                 const int32_t *csr_col, const float *csr_val, const int32_t *col_ptr, const int32_t *csc_row,
                 const float *csc_val, float *X, float *Xn, float *Xp, float *Lam, float *Y, float *Yp, float *Pi,
                 float *scale, int32_t *stats) {
@@ -993,8 +977,6 @@ int launch_gadm(hipStream_t st, const vplmc_plan &plan, int grp, const int32_t *
     a.stats_all = stats;
     a.gsys = gsys;
     a.ge2 = ge2 + plan.ge2_base[grp];
-    a.xpart = gpart + plan.gpart_base[grp];
-    a.ypart = a.xpart + (int64_t)plan.g_rows[grp] * 2 * Q * Q;
     a.cb = plan.g_cb[grp];
     const unsigned nr = (unsigned)plan.g_rows[grp], nc = (unsigned)plan.g_cols[grp];
     hipLaunchKernelGGL((k_gadm_init<Q, THREADS>), dim3((unsigned)count), dim3(THREADS), 0, st, a);
@@ -1019,12 +1001,12 @@ int launch_gadm(hipStream_t st, const vplmc_plan &plan, int grp, const int32_t *
 }  // namespace
 
 int launch_gadm_group(hipStream_t st, int q, const vplmc_plan &plan, int grp, const int32_t *ids,
-                      const int32_t *gblk_dev, char *gsys, double *ge2, float *gpart, const SliceDesc *desc,
+                      const int32_t *gblk_dev, char *gsys, double *ge2, const SliceDesc *desc,
                       const vplmc_params &prm, const int32_t *row_ptr, const int32_t *csr_col, const float *csr_val,
                       const int32_t *col_ptr, const int32_t *csc_row, const float *csc_val, float *X, float *Xn,
                       float *Xp, float *Lam, float *Y, float *Yp, float *Pi, float *scale, int32_t *stats) {
 #define VPLMC_GADM(QQ)                                                                                             \
-    return launch_gadm<QQ, 256>(st, plan, grp, ids, gblk_dev, gsys, ge2, gpart, desc, prm, row_ptr, csr_col, csr_val,   \
+    return launch_gadm<QQ, 256>(st, plan, grp, ids, gblk_dev, gsys, ge2, desc, prm, row_ptr, csr_col, csr_val,   \
                                 col_ptr, csc_row, csc_val, X, Xn, Xp, Lam, Y, Yp, Pi, scale, stats)
     switch (q) {
     case 4: VPLMC_GADM(4);

@@ -208,7 +208,6 @@ enum {
     R_COUNTS,        // uint64[4]: shadow rays of the entries, coarsening evaluations and rays, -
     R_GSYS,          // GADM_SYS_BYTES per slice: q x q systems and state of the global-memory completion
     R_GE2,           // double per row block of the global-memory slices: squared residual sums
-    R_GPART,         // float: Gram parts of the row blocks (2 q q) and column blocks (q q) of the global-memory slices
     R_INTERNAL_END
 };
 
@@ -312,7 +311,6 @@ struct vplmc_plan {
     // ints into gblk; the first row block's squared-residual slot at ge2_base[g]
     std::vector<int32_t> gblk;
     int64_t gblk_off[8] = {}, ge2_base[8] = {}, g_rows[8] = {}, g_cols[8] = {};
-    int64_t gpart_base[8] = {};                // first Gram part of the group, in floats
     int32_t g_cb[8] = {};                      // columns per column block
     std::vector<char> upload;                  // descriptor table + ids + gblk, as copied to the workspace
 };
@@ -400,14 +398,14 @@ int launch_sort(hipStream_t st, const vplmc_plan &plan, const SliceDesc *desc, c
                 const int32_t *stats, int32_t *csr_col, float *csr_val, int32_t *csc_row, float *csc_val,
                 const EllView &ell);
 int launch_adm(hipStream_t st, const AdmStreams *ss, const vplmc_plan &plan, int n_cu, const SliceDesc *desc,
-               const int32_t *ids_dev, const int32_t *gblk_dev, char *gsys, double *ge2, float *gpart,
+               const int32_t *ids_dev, const int32_t *gblk_dev, char *gsys, double *ge2,
                int32_t *queues, const vplmc_params &prm, const int32_t *row_ptr, const int32_t *csr_col,
                const float *csr_val, const int32_t *col_ptr, const int32_t *csc_row, const float *csc_val,
                const EllView &ell, float *X, float *Xn, float *Xp, float *Lam, float *Y, float *Yp, float *Pi,
                float *Yt, float *red, double *e2part, float *scale, int32_t *stats);
 // the global-memory completion of plan group grp (rank q = 4, 8, 16 or 32; kernels_gadm.hip)
 int launch_gadm_group(hipStream_t st, int q, const vplmc_plan &plan, int grp, const int32_t *ids,
-                      const int32_t *gblk_dev, char *gsys, double *ge2, float *gpart, const SliceDesc *desc,
+                      const int32_t *gblk_dev, char *gsys, double *ge2, const SliceDesc *desc,
                       const vplmc_params &prm, const int32_t *row_ptr, const int32_t *csr_col, const float *csr_val,
                       const int32_t *col_ptr, const int32_t *csc_row, const float *csc_val, float *X, float *Xn,
                       float *Xp, float *Lam, float *Y, float *Yp, float *Pi, float *scale, int32_t *stats);
