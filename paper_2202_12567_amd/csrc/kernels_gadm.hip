@@ -8,7 +8,7 @@
 //                                  X+_i = X_i F + T_i Inv, U, Lambda (q/4 lanes per row)
 //   ysys    (workgroup per slice)  residual norm and the stop test, GX = X+^T X+,
 //                                  C = X+^T X, Y system
-//   cols    (per column block) residuals again from X and Y, X+^T R_j,
+//   cols    (per column block)     residuals again from X and Y, X+^T R_j,
 //                                  Y+_j = F Y_j + Inv T_j, V, Pi (q/4 lanes per column)
 //   xsys    (workgroup per slice)  GY = Y+^T Y+, X system for the next iteration
 //   final   (workgroup per slice)  the final X into the X region, statistics
@@ -17,6 +17,14 @@
 // GADM_SYS_BYTES per slice.  The iteration is the one the LDS-resident kernel
 // runs (Appendix A, in the sparse-residual form of kernels_adm.hip); the Grams
 // are sums in a fixed order, so results are bitwise reproducible.
+//
+// Bound by the latency of the dependent gathers (sample index, then the factor
+// rows it names) and, per system launch, of a q x q inverse.  96 slices of 300-1,024
+// rows, 512 columns, rank 32, 6.5% sampled, per iteration: cols 195 -> 94 us with
+// 64-column blocks (192 workgroups of 256 columns before), rows 61, ysys 97 -> 67 and xsys
+// 84 -> 61 with the Grams on the matrix unit and the inverse in registers.  32-column
+// blocks took 109 for cols, four wavefronts per SIMD there 112, batches of two or
+// eight samples 122 / 103.
 
 #include "adm_common.h"
 

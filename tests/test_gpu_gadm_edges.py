@@ -3,7 +3,7 @@
 ranks), a column of more samples than a lane group takes and an empty column,
 against the FP64 oracle on the same samples at an odd iteration count (the
 second X buffer).  1e-3 per slice: the per-slice bar of every completion test,
-three orders above the FP32 rounding of the Grams' parts."""
+three orders above the FP32 rounding of the Grams."""
 import types
 
 import numpy as np
