@@ -31,8 +31,9 @@
 // launch from the Y vectors it loads anyway; its sums per workgroup land in
 // slots, which every workgroup of the column launch adds in slot order for
 // the stop test.  The row launch writes the second X buffer, so a slice that
-// stops keeps the X its residual was measured on.  The factors are
-// bit-reproducible (every system is summed in sample order).
+// stops keeps the X its residual was measured on.  Every system is summed in
+// sample order, and a row's place in a slot's sum depends on the counts alone:
+// factors, residuals and iteration counts are bit-reproducible.
 //
 // Bound by the latency of the gathers on the longest columns and by the
 // elimination's dependent FP64 chain.  Measured on one MI355X, 48 slices of
@@ -125,9 +126,16 @@ __device__ __forceinline__ int block_slice(const int32_t *__restrict__ pre, int 
 }
 
 // the items 0 .. n - 1 of a CSR / CSC pointer by decreasing count (counts past
-// ALS_BINS - 1 alike; the order among equals does not matter).  All threads call.
-__device__ void order_by_count(const int32_t *__restrict__ ptr, int n, int32_t *__restrict__ order, int32_t *bins) {
+// ALS_BINS - 1 alike), equal counts in index order: a system's workgroup, and
+// with it the order of the residual's sum, is the same in every run.  A chunk
+// of items at a time, each counting the equal ones before it.  All threads call.
+struct AlsOrder {
+    int32_t bins[ALS_BINS];
+    __align__(16) uint16_t chunk[ALS_INIT_THREADS];
+};
+__device__ void order_by_count(const int32_t *__restrict__ ptr, int n, int32_t *__restrict__ order, AlsOrder &sh) {
     const int t = threadIdx.x;
+    int32_t *bins = sh.bins;
     auto bin = [&](int i) { return ALS_BINS - 1 - min(ptr[i + 1] - ptr[i], ALS_BINS - 1); };
     for (int e = t; e < ALS_BINS; e += ALS_INIT_THREADS) bins[e] = 0;
     __syncthreads();
@@ -149,16 +157,38 @@ __device__ void order_by_count(const int32_t *__restrict__ ptr, int n, int32_t *
             base += c;
         }
     }
-    __syncthreads();
-    for (int i = t; i < n; i += ALS_INIT_THREADS) order[atomicAdd(bins + bin(i), 1)] = i;
-    __syncthreads();
+    for (int i0 = 0; i0 < n; i0 += ALS_INIT_THREADS) {
+        const int i = i0 + t;
+        const int b = i < n ? bin(i) : 0xFFFF;
+        sh.chunk[t] = (uint16_t)b;
+        __syncthreads();
+        int before = 0, equal = 0;
+#pragma unroll 4
+        for (int u = 0; u < ALS_INIT_THREADS; u += 8) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(sh.chunk + u);
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int same = (int)((w[k / 2] >> (k % 2 * 16)) & 0xFFFFu) == b ? 1 : 0;
+                equal += same;
+                before += u + k < t ? same : 0;
+            }
+        }
+        const int at = i < n ? bins[b] + before : 0;
+        __syncthreads();
+        if (i < n) {
+            order[at] = i;
+            if (before + 1 == equal) bins[b] = at + 1;     // the last of its count in the chunk
+        }
+        __syncthreads();
+    }
 }
 
 // scale s0 = mean sampled value, ||P_Omega M|| of M / s0, initial factors as the ADM's
 template <int Q>
 __global__ __launch_bounds__(ALS_INIT_THREADS) void k_als_init(AlsArgs a) {
     __shared__ double red[ALS_INIT_THREADS / WAVE];
-    __shared__ int32_t bins[ALS_BINS];
+    __shared__ AlsOrder ord;
     const int s = __builtin_amdgcn_readfirstlane(a.ids[blockIdx.x]);
     const SliceDesc d = a.desc[s];
     const int m = d.m, n = d.n, qr = d.qr, t = threadIdx.x;
@@ -186,8 +216,8 @@ __global__ __launch_bounds__(ALS_INIT_THREADS) void k_als_init(AlsArgs a) {
         st->s0 = s0;
         a.scale_all[s] = (float)s0;
     }
-    order_by_count(a.row_ptr_all + d.off_row, m, a.rord_all + d.off_x, bins);
-    order_by_count(a.col_ptr_all + d.off_colptr, n, a.cord_all + d.off_y, bins);
+    order_by_count(a.row_ptr_all + d.off_row, m, a.rord_all + d.off_x, ord);
+    order_by_count(a.col_ptr_all + d.off_colptr, n, a.cord_all + d.off_y, ord);
     const float cq = (float)(2.0 / sqrt((double)qr));
     const bool given = (a.mode & 2) != 0;
     for (int e = t; e < m * Q; e += ALS_INIT_THREADS) {
