@@ -427,9 +427,10 @@ __global__ __launch_bounds__(ALS_THREADS) void k_als_rows(AlsArgs a, int it) {
             }
             gram_add3<Q, S::T, 0>(G, yb[u], b);
             rhs = __fadd_rn(rhs, fmaf(mb[2], yb[u][2], fmaf(mb[0], yb[u][0], __fmul_rn(mb[1], yb[u][1]))));
+            const float xu = e0 + u < cnt ? x : 0.f;   // past the end the row's x may be anything
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {            // 0 past the end
-                const float e = mb[c] - tile_sum<S::T>(x * yb[u][c]);
+            for (int c = 0; c < 3; ++c) {
+                const float e = mb[c] - tile_sum<S::T>(xu * yb[u][c]);
                 e2 = fma((double)e, (double)e, e2);
             }
         });

@@ -70,3 +70,20 @@ def test_whole_workspace_repeats():
         ws = w.workspace()
         w.run(ws)
         assert torch.equal(ws, first)
+
+
+@pytest.mark.parametrize("m,n,q", [(33, 20, 4), (150, 90, 16)])
+def test_given_factors_of_a_row_without_samples_are_not_read(m, n, q):
+    """Nor are they by the oracle: the residual is over the samples."""
+    res = []
+    for fill in (0.25, float("nan"), float("inf")):
+        w = Workload([(m, n, q, 0.02)], holes=True, given_init=True, max_iter=1, tol=1e-9)
+        ws = w.workspace()
+        g = torch.Generator().manual_seed(3)
+        for name, count in (("X", m * q), ("Y", 3 * n * q)):
+            api.region_view(w.plan, ws, name, torch.float32)[:count] = torch.rand(count, generator=g).to(DEV)
+        api.region_view(w.plan, ws, "X", torch.float32)[(m - 1) * q:m * q] = fill
+        rad = w.run(ws)
+        res.append((float(w.stats(ws)["resid"][0]), rad))
+    for resid, rad in res:
+        assert np.isfinite(resid) and resid == res[0][0] and torch.equal(rad, res[0][1])
