@@ -16,7 +16,8 @@
 // Two launches per iteration over all slices of a rank bucket (k_als_rows,
 // k_als_cols), after an init launch and before a final one, so that a frame of
 // a few dozen slices fills the chip and the launch boundaries order the
-// half-steps.  A 16-lane row of a wavefront (32 lanes at rank 32) owns one
+// half-steps (with the residual stop also a loop over the iterations, see
+// ALS_LAUNCHED).  A 16-lane row of a wavefront (32 lanes at rank 32) owns one
 // system, lane r holding row r of its Gram: a factor vector is one coalesced
 // load of the tile, and each lane multiplies its own component by every
 // component, broadcast by DPP.  The Gram is summed in FP32 in sample order;
@@ -43,6 +44,7 @@
 // wavefront per four systems, summed in another order) took 16 ms in FP32 and
 // 26 ms in FP64.
 
+#include <algorithm>
 #include <utility>
 
 #include "vplmc_internal.h"
@@ -53,6 +55,19 @@ namespace {
 constexpr int WAVE = 64;
 constexpr int ALS_THREADS = 256;      // of the row and column launches
 constexpr int ALS_NW = ALS_THREADS / WAVE;
+constexpr int ALS_LOOP_THREADS = 512;
+// With the residual stop, the launches after the last slice has stopped still
+// cost 2.7 us each.  So at most ALS_LAUNCHED iterations are launches, and one
+// launch of k_als_loop, a workgroup per slice, does what is left (limit 2,000,
+// stopped after one: 15.0 -> 0.7 ms); the default limit of 100 lies below.
+// Slices so small that a workgroup per slice does well are its from the start:
+// up to ALS_LOOP_EDGE rows and columns (64 x 32, rank 8: 178 us against 680
+// stopped after two iterations, 2.0 ms against 1.6 after 100; 16 of 64 x 64, rank
+// 16: 0.27 / 0.69 and 5.2 / 2.8 ms), twice that where ALS_LOOP_MANY slices fill
+// the chip (400 of 128 x 128, rank 16: 0.54 / 1.57 and 14.9 / 15.9 ms).  Rank 32
+// (64 x 64: 0.56 / 0.72, 27 / 6 ms) and fixed counts stay with the launches.
+constexpr int ALS_LAUNCHED = 128;
+constexpr int ALS_LOOP_EDGE = 64, ALS_LOOP_MANY = 400;
 constexpr int ALS_INIT_THREADS = 512;
 constexpr int ALS_BINS = 1024;        // sample counts told apart by the ordering
 
@@ -350,22 +365,14 @@ __device__ __forceinline__ void tile_solve(const float (&G)[Q], double shift, do
     for (int c = 0; c < NR; ++c) b[c] *= dinv;
 }
 
-// Row half-step: GRP rows of one slice per workgroup.
+// One row per tile of the wavefront: the row at place `at` of the slice's order
+// (none past the last).  Lane 0 of the tile returns its squared residual of the
+// iterate that enters iteration it.
 template <int Q>
-__global__ __launch_bounds__(ALS_THREADS) void k_als_rows(AlsArgs a, int it) {
+__device__ __forceinline__ double als_row(const AlsArgs &a, const SliceDesc &d, float inv_s0, int it, int at) {
     using S = AlsShape<Q>;
     constexpr int U = 8;                             // samples of a block
-    __shared__ double red[ALS_NW];
-    const int blk = blockIdx.x / S::RSUB, sub = blockIdx.x % S::RSUB;
-    const int kk = block_slice(a.rowp, a.count, blk);
-    const int s = __builtin_amdgcn_readfirstlane(a.ids[kk]);
-    const AlsState *st = state_of(a.gsys, s);
-    if (st->done) return;
-    const SliceDesc d = a.desc[s];
-    const int t = threadIdx.x, lane = t % WAVE, r = lane % S::T, g = lane / S::T;
-    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);
-    const int at = (blk - a.rowp[kk]) * GADM_RB + sub * S::GRP + w * S::SYS + g;   // the tile's place in the order
-    const float inv_s0 = (float)(1.0 / st->s0);
+    const int lane = threadIdx.x % WAVE, r = lane % S::T;
     const int32_t *row_ptr = a.row_ptr_all + d.off_row;
     const int32_t *csr_col = a.csr_col_all + d.off_omega;
     const float *csr_val = a.csr_val_all + 3 * d.off_omega;
@@ -438,49 +445,33 @@ __global__ __launch_bounds__(ALS_THREADS) void k_als_rows(AlsArgs a, int it) {
     double b[1] = {(double)rhs};
     tile_solve<Q, 1>(G, in ? (double)a.lam * (double)max(1, 3 * cnt) : 1.0, b, r);
     if (in && comp) Xn[(size_t)i * Q + r] = r < d.qr ? (float)b[0] : 0.f;
-    e2 = block_sum_d<ALS_NW>(r == 0 ? e2 : 0.0, red);
+    return r == 0 ? e2 : 0.0;
+}
+
+// Row half-step: GRP rows of one slice per workgroup.
+template <int Q>
+__global__ __launch_bounds__(ALS_THREADS) void k_als_rows(AlsArgs a, int it) {
+    using S = AlsShape<Q>;
+    __shared__ double red[ALS_NW];
+    const int blk = blockIdx.x / S::RSUB, sub = blockIdx.x % S::RSUB;
+    const int kk = block_slice(a.rowp, a.count, blk);
+    const int s = __builtin_amdgcn_readfirstlane(a.ids[kk]);
+    const AlsState *st = state_of(a.gsys, s);
+    if (st->done) return;
+    const SliceDesc d = a.desc[s];
+    const int t = threadIdx.x, g = t % WAVE / S::T;
+    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);
+    const int at = (blk - a.rowp[kk]) * GADM_RB + sub * S::GRP + w * S::SYS + g;   // the tile's place in the order
+    const double e2 = block_sum_d<ALS_NW>(als_row<Q>(a, d, (float)(1.0 / st->s0), it, at), red);
     if (t == 0) a.e2[blockIdx.x] = e2;
 }
 
-// Column half-step: GRP columns of one slice per workgroup, their three
-// channels sharing a system; first the stop test on the residual slots.
+// One column per tile: the column at place `at`, its three channels sharing a system.
 template <int Q>
-__global__ __launch_bounds__(ALS_THREADS) void k_als_cols(AlsArgs a, int it) {
+__device__ __forceinline__ void als_col(const AlsArgs &a, const SliceDesc &d, float inv_s0, int it, int at) {
     using S = AlsShape<Q>;
     constexpr int U = 16;                            // samples of a block
-    __shared__ double red[ALS_NW];
-    __shared__ int done_s;
-    const int csub = a.cb / S::GRP, blk = blockIdx.x / csub, sub = blockIdx.x % csub;
-    const int kk = block_slice(a.colp, a.count, blk);
-    const int s = __builtin_amdgcn_readfirstlane(a.ids[kk]);
-    AlsState *st = state_of(a.gsys, s);
-    const SliceDesc d = a.desc[s];
-    const int first_at = (blk - a.colp[kk]) * a.cb + sub * S::GRP;
-    if (first_at >= d.n) return;
-    // a slice that stops in this launch is marked by its first workgroup; the
-    // others find the same sum, so it does not matter which they see first
-    const int t = threadIdx.x, lane = t % WAVE, r = lane % S::T, g = lane / S::T;
-    if (t == 0) done_s = __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (done_s) return;
-    if (!(a.mode & 1) || first_at == 0) {
-        double e2 = 0.0;
-        for (int u = a.rowp[kk] * S::RSUB + t; u < a.rowp[kk + 1] * S::RSUB; u += ALS_THREADS) e2 += a.e2[u];
-        e2 = block_sum_d<ALS_NW>(e2, red);
-        const double err = sqrt(e2) / st->norm_m;
-        const bool stop = !(a.mode & 1) && err < (double)a.tol;
-        if (first_at == 0 && t == 0) {
-            st->resid = __float_as_int((float)err);
-            if (stop) {
-                st->iters = it;
-                __hip_atomic_store(&st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        if (stop) return;
-    }
-    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);
-    const int at = first_at + w * S::SYS + g;
-    const float inv_s0 = (float)(1.0 / st->s0);
+    const int lane = threadIdx.x % WAVE, r = lane % S::T;
     const int32_t *col_ptr = a.col_ptr_all + d.off_colptr;
     const int32_t *csc_row = a.csc_row_all + d.off_omega;
     const float *csc_val = a.csc_val_all + 3 * d.off_omega;
@@ -537,6 +528,78 @@ __global__ __launch_bounds__(ALS_THREADS) void k_als_cols(AlsArgs a, int it) {
     }
 }
 
+// Column half-step: GRP columns of one slice per workgroup; first the stop
+// test on the residual slots.
+template <int Q>
+__global__ __launch_bounds__(ALS_THREADS) void k_als_cols(AlsArgs a, int it) {
+    using S = AlsShape<Q>;
+    __shared__ double red[ALS_NW];
+    __shared__ int done_s;
+    const int csub = a.cb / S::GRP, blk = blockIdx.x / csub, sub = blockIdx.x % csub;
+    const int kk = block_slice(a.colp, a.count, blk);
+    const int s = __builtin_amdgcn_readfirstlane(a.ids[kk]);
+    AlsState *st = state_of(a.gsys, s);
+    const SliceDesc d = a.desc[s];
+    const int first_at = (blk - a.colp[kk]) * a.cb + sub * S::GRP;
+    if (first_at >= d.n) return;
+    // a slice that stops in this launch is marked by its first workgroup; the
+    // others find the same sum, so it does not matter which they see first
+    const int t = threadIdx.x, g = t % WAVE / S::T;
+    if (t == 0) done_s = __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (done_s) return;
+    if (!(a.mode & 1) || first_at == 0) {
+        double e2 = 0.0;
+        for (int u = a.rowp[kk] * S::RSUB + t; u < a.rowp[kk + 1] * S::RSUB; u += ALS_THREADS) e2 += a.e2[u];
+        e2 = block_sum_d<ALS_NW>(e2, red);
+        const double err = sqrt(e2) / st->norm_m;
+        const bool stop = !(a.mode & 1) && err < (double)a.tol;
+        if (first_at == 0 && t == 0) {
+            st->resid = __float_as_int((float)err);
+            if (stop) {
+                st->iters = it;
+                __hip_atomic_store(&st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (stop) return;
+    }
+    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);
+    als_col<Q>(a, d, (float)(1.0 / st->s0), it, first_at + w * S::SYS + g);
+}
+
+// The iterations from it0 on, one workgroup per slice, until the slice stops.
+template <int Q>
+__global__ __launch_bounds__(ALS_LOOP_THREADS) void k_als_loop(AlsArgs a, int it0) {
+    using S = AlsShape<Q>;
+    constexpr int NW = ALS_LOOP_THREADS / WAVE;
+    __shared__ double red[NW];
+    const int s = __builtin_amdgcn_readfirstlane(a.ids[blockIdx.x]);
+    AlsState *st = state_of(a.gsys, s);
+    if (st->done) return;
+    const SliceDesc d = a.desc[s];
+    const int t = threadIdx.x, g = t % WAVE / S::T;
+    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);
+    const float inv_s0 = (float)(1.0 / st->s0);
+    const double norm_m = st->norm_m;
+    for (int it = it0; it < a.max_iter; ++it) {
+        double e2 = 0.0;
+        for (int r0 = w * S::SYS; r0 < d.m; r0 += NW * S::SYS) e2 += als_row<Q>(a, d, inv_s0, it, r0 + g);
+        e2 = block_sum_d<NW>(e2, red);
+        const double err = sqrt(e2) / norm_m;
+        const bool stop = !(a.mode & 1) && err < (double)a.tol;
+        if (t == 0) {
+            st->resid = __float_as_int((float)err);
+            if (stop) st->iters = it;
+        }
+        if (stop) return;
+        __threadfence_block();           // the new X before its columns read it
+        __syncthreads();
+        for (int c0 = w * S::SYS; c0 < d.n; c0 += NW * S::SYS) als_col<Q>(a, d, inv_s0, it, c0 + g);
+        __threadfence_block();
+        __syncthreads();
+    }
+}
+
 // the final X into the X region, statistics
 template <int Q>
 __global__ __launch_bounds__(ALS_THREADS) void k_als_final(AlsArgs a) {
@@ -576,10 +639,17 @@ int launch_als_q(hipStream_t st, const AlsArgs &args, const vplmc_plan &plan, in
     const unsigned nr = (unsigned)(plan.g_rows[grp] * S::RSUB), nc = (unsigned)(plan.g_cols[grp] * (a.cb / S::GRP));
     hipLaunchKernelGGL(k_als_init<Q>, dim3((unsigned)count), dim3(ALS_INIT_THREADS), 0, st, a);
     VPLMC_HIP(hipGetLastError());
-    for (int it = 0; it < a.max_iter; ++it) {
+    const int edge = (count >= (size_t)ALS_LOOP_MANY ? 2 : 1) * ALS_LOOP_EDGE;
+    const bool small = Q <= 16 && plan.group_max_m[grp] <= edge && plan.group_max_n[grp] <= edge;
+    const int launched = a.mode & 1 ? a.max_iter : small ? 0 : std::min(a.max_iter, ALS_LAUNCHED);
+    for (int it = 0; it < launched; ++it) {
         hipLaunchKernelGGL(k_als_rows<Q>, dim3(nr), dim3(ALS_THREADS), 0, st, a, it);
         VPLMC_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_als_cols<Q>, dim3(nc), dim3(ALS_THREADS), 0, st, a, it);
+        VPLMC_HIP(hipGetLastError());
+    }
+    if (launched < a.max_iter) {
+        hipLaunchKernelGGL(k_als_loop<Q>, dim3((unsigned)count), dim3(ALS_LOOP_THREADS), 0, st, a, launched);
         VPLMC_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_als_final<Q>, dim3((unsigned)count), dim3(ALS_THREADS), 0, st, a);

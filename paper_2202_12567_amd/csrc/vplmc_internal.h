@@ -297,7 +297,7 @@ struct vplmc_plan {
     // slice ids by ADM kernel group: 2 * bucket + variant, bucket = rank 4, 8, 16, 32,
     // variant 0 = X resident in LDS, 1 = X in global memory
     std::vector<int32_t> groups[8];
-    int32_t group_max_m[8] = {};
+    int32_t group_max_m[8] = {}, group_max_n[8] = {};
     vplmc::Layout layout;
     int64_t tot1 = 0, tot2 = 0, tot_omega = 0, tot_col = 0, tot_row = 0, tot_x = 0, tot_y = 0;
     int64_t tot_bm = 0, tot_bmt = 0;

@@ -87,3 +87,62 @@ def test_given_factors_of_a_row_without_samples_are_not_read(m, n, q):
         res.append((float(w.stats(ws)["resid"][0]), rad))
     for resid, rad in res:
         assert np.isfinite(resid) and resid == res[0][0] and torch.equal(rad, res[0][1])
+
+
+SMALL = [(64, 64, 8, 0.02), (40, 30, 4, 0.3), (50, 64, 16, 0.1), (33, 17, 3, 0.15), (64, 20, 12, 0.25)]
+LARGE = [(200, 70, 8, 0.02), (130, 300, 16, 0.25), (70, 260, 4, 0.3), (300, 40, 12, 0.15), (90, 100, 32, 0.1)]
+
+
+@pytest.mark.parametrize("slices,tol,iters", [(SMALL, 0.08, [2, 8, 1, 3, 2]), (LARGE, 0.11, [1, 3, 8, 2, 1])])
+def test_stops_where_the_oracle_does(slices, tol, iters):
+    """Slices that stop after odd, even and no iterations (the oracle's residuals before and after a stop are at least
+    2% off the tolerance; FP32 Grams move them by 1e-5), the launches' tiles of rows and columns crossed."""
+    w = Workload(slices, max_iter=8, tol=tol)
+    ws = w.workspace()
+    rad = w.run(ws).double().cpu().numpy()
+    st, at = w.stats(ws), 0
+    assert [int(k) for k in st["iters"]] == iters
+    for s, (m, n, q, _) in enumerate(slices):
+        ii, jj, v = w.samples[s]
+        want, n_it, err, flags, _ = orender.complete_and_render(
+            m, n, q, ii, jj, v.astype(np.float64), SEED, s,
+            orender.Params(seed=SEED, max_iter=8, fixed_iters=False, tol=tol, method="als", lam=0.01))
+        assert n_it == iters[s]
+        assert abs(float(st["resid"][s]) - err) <= 1e-3 * err
+        assert bool(int(st["flags"][s]) & 2) == (n_it == 8)
+        assert orender.relative_rmse(rad[at:at + m], want) <= 1e-3
+        at += m
+
+
+@pytest.mark.parametrize("slices", [SMALL, LARGE])
+@pytest.mark.parametrize("iters", [5, 131, 160])
+def test_an_unreached_tolerance_gives_the_factors_of_the_fixed_count(slices, iters):
+    """Bit for bit, past the iterations that are launches of their own too."""
+    got = []
+    for prm in (dict(tol=1e-12), dict(fixed_iters=True)):
+        w = Workload(slices, max_iter=iters, **prm)
+        ws = w.workspace()
+        rad = w.run(ws)
+        assert [int(k) for k in w.stats(ws)["iters"]] == [iters] * len(slices)
+        got.append((rad, w.x(ws)))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("slices", [SMALL, LARGE])
+def test_a_high_limit_costs_little_once_every_slice_has_stopped(slices):
+    """Every slice stops before its third iteration; the limit of 3,000 takes no more than five times that of 100 (an
+    empty launch per half-step took thirty times)."""
+    took = []
+    for limit in (100, 3000):
+        w = Workload(slices, max_iter=limit, tol=0.3)
+        ws = w.workspace()
+        times = []
+        for _ in range(7):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            w.run(ws)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t)
+        assert max(int(k) for k in w.stats(ws)["iters"]) < 3
+        took.append(sorted(times)[3])
+    assert took[1] <= 5 * took[0]
