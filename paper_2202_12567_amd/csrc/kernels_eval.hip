@@ -185,13 +185,16 @@ __device__ __forceinline__ float wave_min(float v) {
 // every sphere that any of the segments meets and the answer is that of the
 // traversal.  It pays where the segments of a wavefront are alike: rows of one
 // slice against one light or the lights below one tree node.  Returns 1
-// (occluded), 0 (not), or -1 for every lane if the list overflows.  All 64
-// lanes call.
+// (occluded), 0 (not), or -1 for every lane if the list overflows or a segment
+// starts beyond any box.  All 64 lanes call.
 constexpr int SHAFT_CAP = 128;
 // The tests of the groups are linear in their number; a traversal is not.  8,192
 // points against 4,096 lights and fine spheres, lists / traversal of the same
 // wavefronts: 1,024 groups 8.1 / 7.9 ms, 2,048 groups 10.2 / 10.1 ms.
 constexpr int SHAFT_MAX_GROUPS = 512;
+
+// an origin that the arithmetic on boxes takes (an infinite one would leave every lane of its wavefront an empty shaft)
+__device__ __forceinline__ bool boxed(P3 o) { return fabsf(o.x) < 1e18f && fabsf(o.y) < 1e18f && fabsf(o.z) < 1e18f; }
 
 // the spheres near the shaft between the boxes A and B (wave-uniform) listed in
 // `list`; their number, which may exceed the SHAFT_CAP that are listed
@@ -283,6 +286,7 @@ __device__ __forceinline__ bool list_occluded(const float4 *list, int count, boo
 
 __device__ int occluded_shaft(const Bvh &b, float4 *list, bool want, P3 o, P3 y) {
     if (b.n_groups == 0 || __ballot(want) == 0) return 0;
+    if (__ballot(want && !boxed(o)) != 0) return -1;
     const float of[3] = {o.x, o.y, o.z}, yf[3] = {y.x, y.y, y.z};
     float alo[3], ahi[3], blo[3], bhi[3];
 #pragma unroll
@@ -816,8 +820,7 @@ __global__ __launch_bounds__(BS_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8
         ahi[a] = -wave_min(active ? -of[a] : INFINITY);
     }
     // origins beyond any box, or too many groups: the traversal for every light
-    const bool boxed = fabsf(o.x) < 1e18f && fabsf(o.y) < 1e18f && fabsf(o.z) < 1e18f;
-    const bool shaft = bvh.n_groups <= SHAFT_MAX_GROUPS && __ballot(active && !boxed) == 0;
+    const bool shaft = bvh.n_groups <= SHAFT_MAX_GROUPS && __ballot(active && !boxed(o)) == 0;
     int over = 0;                          // lists that overflowed, less those that did not
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
     const int c1 = min(l.n, (int)(blockIdx.y + 1) * chunk);

@@ -1,0 +1,51 @@
+"""The coarsening's wavefront-shared shadow test against the traversal of the same spheres, bit for bit: more than
+16,384 spheres turn the lists off, so spheres that no segment can meet, far below the scene, give the traversal's
+answer on the same code."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+from paper_2202_12567_amd import api  # noqa: E402
+from scenegen import make_scene  # noqa: E402
+
+SEED = 6
+DEV = torch.device("cuda", 0)
+
+
+def below(sph, count):
+    rng = np.random.default_rng(2)
+    f = np.float32
+    far = dict(cx=rng.uniform(0, 1, count), cy=rng.uniform(0, 1, count), cz=rng.uniform(-11, -10, count),
+               r=np.full(count, 1e-3))
+    return {k: np.concatenate([sph[k], far[k].astype(f)]) for k in ("cx", "cy", "cz", "r")}
+
+
+def merge_errors(sc, spheres, K):
+    prm = api.default_params(seed=SEED, pass1_ppm=0, pass2_ppm=20000, max_iter=2, fixed_iters=True)
+    ctx = api.Context(0)
+    ctx.set_occluders(spheres)
+    ds = api.DeviceScene(sc, DEV)
+    plan = api.Plan(sc, prm, api.Coarsening(K, 128))
+    ws = api.workspace(plan, DEV)
+    api.render(ctx, plan, ds, prm, ws)
+    return api.region_view(plan, ws, "NODE_EPS", torch.int32).clone()
+
+
+@pytest.mark.parametrize("K", [600, 4096])
+@pytest.mark.parametrize("normal", [None, np.inf, -np.inf, 1e30, np.nan])
+def test_equals_the_traversal(K, normal):
+    """With normals that put a shadow segment's origin beyond any box, in one row of every 50."""
+    sc = make_scene("tiny", SEED)
+    if normal is not None:
+        pts = {k: np.array(v) for k, v in sc.points.items()}
+        for k, axis in enumerate(("nx", "ny", "nz")):
+            pts[axis][sc.pt_ids[k * 17::50]] = normal
+        sc = dataclasses.replace(sc, points=pts)
+    lists, walk = (merge_errors(sc, below(sc.spheres, extra), K) for extra in (0, 17000))
+    assert int((lists != 0).sum()) > 500
+    assert torch.equal(lists, walk)
