@@ -197,7 +197,7 @@ constexpr int SHAFT_MAX_GROUPS = 512;
 __device__ __forceinline__ bool boxed(P3 o) { return fabsf(o.x) < 1e18f && fabsf(o.y) < 1e18f && fabsf(o.z) < 1e18f; }
 
 // the spheres near the shaft between the boxes A and B (wave-uniform) listed in
-// `list`; their number, which may exceed the SHAFT_CAP that are listed
+// `list`; their number, or one above SHAFT_CAP if there are more than that
 __device__ __forceinline__ int shaft_list(const Bvh &b, float4 *list, float (&alo)[3], float (&ahi)[3],
                                           const float (&blo)[3], const float (&bhi)[3]) {
     const int lane = threadIdx.x & 63;
@@ -259,6 +259,7 @@ __device__ __forceinline__ int shaft_list(const Bvh &b, float4 *list, float (&al
             const int at = count + __popcll(hits & ((1ull << lane) - 1));
             if (hit && at < SHAFT_CAP) list[at] = sp;
             count += __popcll(hits);
+            if (count > SHAFT_CAP) return count;
         }
     }
     return count;
@@ -284,9 +285,26 @@ __device__ __forceinline__ bool list_occluded(const float4 *list, int count, boo
     return want && occ;
 }
 
-__device__ int occluded_shaft(const Bvh &b, float4 *list, bool want, P3 o, P3 y) {
+// Whether a wavefront lists at all: after a list that overflowed it traverses the
+// BVH for the next 1, 2, 4, ... SHAFT_BACKOFF segments of each lane, so that
+// dense occluders cost a few failed lists per wavefront instead of one per tree level.
+constexpr int SHAFT_BACKOFF = 64;
+struct ShaftGate {
+    int wait = 0, penalty = 0;
+    __device__ bool open() {
+        if (wait == 0) return true;
+        --wait;
+        return false;
+    }
+    __device__ void listed(bool fits) {
+        penalty = fits ? 0 : min(max(1, 2 * penalty), SHAFT_BACKOFF);
+        wait = penalty;
+    }
+};
+
+__device__ int occluded_shaft(const Bvh &b, float4 *list, ShaftGate &gate, bool want, P3 o, P3 y) {
     if (b.n_groups == 0 || __ballot(want) == 0) return 0;
-    if (__ballot(want && !boxed(o)) != 0) return -1;
+    if (!gate.open() || __ballot(want && !boxed(o)) != 0) return -1;
     const float of[3] = {o.x, o.y, o.z}, yf[3] = {y.x, y.y, y.z};
     float alo[3], ahi[3], blo[3], bhi[3];
 #pragma unroll
@@ -297,20 +315,21 @@ __device__ int occluded_shaft(const Bvh &b, float4 *list, bool want, P3 o, P3 y)
         bhi[k] = -wave_min(want ? -yf[k] : INFINITY);
     }
     const int count = shaft_list(b, list, alo, ahi, blo, bhi);
+    gate.listed(count <= SHAFT_CAP);
     if (count > SHAFT_CAP) return -1;
     return list_occluded(list, count, want, o, y) ? 1 : 0;
 }
 
 // shade_in for a whole wavefront (all 64 lanes call; lanes without `on` get zeros)
 template <int KIND, typename S>
-__device__ __forceinline__ bool shade_wave(const Bvh &bvh, const S *staged, float4 *list, bool on, const PointData &q,
-                                           const Light &L, float r_min2, float eps, float &o0, float &o1, float &o2) {
+__device__ __forceinline__ bool shade_wave(const Bvh &bvh, const S *staged, float4 *list, ShaftGate &gate, bool on,
+                                           const PointData &q, const Light &L, float r_min2, float eps, float &o0, float &o1, float &o2) {
     if constexpr (KIND == 0) {
         o0 = o1 = o2 = 0.f;
         bool ray = false;
         if (on) ray = entry_unoccluded(q, L, r_min2, o0, o1, o2);
         const P3 o = {fmaf(eps, q.n.x, q.x.x), fmaf(eps, q.n.y, q.x.y), fmaf(eps, q.n.z, q.x.z)};
-        int occ = bvh.n_groups <= SHAFT_MAX_GROUPS ? occluded_shaft(bvh, list, ray, o, L.y) : -1;
+        int occ = bvh.n_groups <= SHAFT_MAX_GROUPS ? occluded_shaft(bvh, list, gate, ray, o, L.y) : -1;
         if (occ < 0) occ = ray && occluded_in(BvhGlobal<KIND>{bvh}, bvh.n_nodes, o, sub(L.y, o)) ? 1 : 0;
         if (occ) o0 = o1 = o2 = 0.f;
         return ray;
@@ -458,6 +477,7 @@ __global__ __launch_bounds__(256) void k_coarsen_top(Bvh bvh, vplmc_points pts, 
     const BvhStaged<KIND> staged{stage, bvh.n_nodes};
     __shared__ float4 lists[KIND == 0 ? 256 / 64 * SHAFT_CAP : 1];
     float4 *list = lists + (KIND == 0 ? threadIdx.x / 64 * SHAFT_CAP : 0);
+    ShaftGate gate;
     const int64_t R0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const bool act = R0 < rows;
     const int64_t R = act ? R0 : rows - 1;
@@ -475,7 +495,7 @@ __global__ __launch_bounds__(256) void k_coarsen_top(Bvh bvh, vplmc_points pts, 
     const int k1 = min(tr.n_front, (int)(blockIdx.y + 1) * TOP_LIGHTS);
     for (int k = blockIdx.y * TOP_LIGHTS; k < k1; ++k) {
         float o0, o1, o2;
-        const bool ray = shade_wave<KIND>(bvh, STAGED ? &staged : nullptr, list, act, q,
+        const bool ray = shade_wave<KIND>(bvh, STAGED ? &staged : nullptr, list, gate, act, q,
                                           node_light(lights, N, tr.front[k], true), r_min2, eps, o0, o1, o2);
         if (act) out[(int64_t)k * d.m] = make_float4(o0, o1, o2, ray ? 1.f : 0.f);
     }
@@ -514,6 +534,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const int lane = threadIdx.x & 63;
     __shared__ float4 lists[KIND == 0 ? 256 / 64 * SHAFT_CAP : 1];
     float4 *list = lists + (KIND == 0 ? threadIdx.x / 64 * SHAFT_CAP : 0);
+    ShaftGate gate;
     for (int64_t base = blockIdx.x * (int64_t)blockDim.x + (threadIdx.x - lane); base < total; base += stride) {
         const int64_t g = base + lane < total ? base + lane : total - 1;
         const int sl = (int)(g / K), s = s_first + sl;
@@ -561,7 +582,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             const int other = c == a ? bb : a;
             float o0, o1, o2;
             const int ti = tr.n_front > 1 && on ? tr.tidx[other] : -1;
-            bool ray = shade_wave<KIND>(bvh, STAGED ? &staged : nullptr, list, on && ti < 0, q,
+            bool ray = shade_wave<KIND>(bvh, STAGED ? &staged : nullptr, list, gate, on && ti < 0, q,
                                         node_light(lights, N, other, true), r_min2, eps, o0, o1, o2);
             if (ti >= 0) {                       // in the top of the tree: evaluated by k_coarsen_top
                 const float4 v = top[(int64_t)cs.top_map[ti] * d.m];

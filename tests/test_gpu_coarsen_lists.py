@@ -36,7 +36,7 @@ def merge_errors(sc, spheres, K):
     return api.region_view(plan, ws, "NODE_EPS", torch.int32).clone()
 
 
-@pytest.mark.parametrize("K", [600, 4096])
+@pytest.mark.parametrize("K", [600, 4096, 32768])
 @pytest.mark.parametrize("normal", [None, np.inf, -np.inf, 1e30, np.nan])
 def test_equals_the_traversal(K, normal):
     """With normals that put a shadow segment's origin beyond any box, in one row of every 50."""
@@ -49,3 +49,32 @@ def test_equals_the_traversal(K, normal):
     lists, walk = (merge_errors(sc, below(sc.spheres, extra), K) for extra in (0, 17000))
     assert int((lists != 0).sum()) > 500
     assert torch.equal(lists, walk)
+
+
+def coarsen_ms(sc, spheres, K):
+    prm = api.default_params(seed=SEED, pass1_ppm=0, pass2_ppm=20000, max_iter=2, fixed_iters=True)
+    ctx = api.Context(0)
+    ctx.set_occluders(spheres)
+    ds = api.DeviceScene(sc, DEV)
+    plan = api.Plan(sc, prm, api.Coarsening(K, 128))
+    ws, rad = api.workspace(plan, DEV), torch.empty((sc.m, 3), device=DEV)
+    best = []
+    for _ in range(6):
+        api.profile_begin(ctx, 1)
+        api.render(ctx, plan, ds, prm, ws, rad)
+        torch.cuda.synchronize()
+        best.append(api.profile_end(ctx)[0]["coarsen"])
+    return min(best)
+
+
+@pytest.mark.parametrize("K", [600, 4096, 32768])
+def test_lists_that_overflow_cost_little(K):
+    """Spheres so dense that no wavefront's list holds them: at most half as long again as the same walk without
+    lists (every list tried and then traversed all the same took 1.8 to 2.3 times as long)."""
+    sc = make_scene("tiny", SEED)
+    rng = np.random.default_rng(17)
+    f = np.float32
+    n = 16000
+    dense = dict(cx=rng.uniform(0, 1, n).astype(f), cy=rng.uniform(0, 1, n).astype(f),
+                 cz=rng.uniform(0.05, 0.24, n).astype(f), r=rng.uniform(0.005, 0.02, n).astype(f))
+    assert coarsen_ms(sc, dense, K) <= 1.5 * coarsen_ms(sc, below(dense, 1000), K)
