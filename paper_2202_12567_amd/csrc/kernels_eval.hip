@@ -430,10 +430,8 @@ __global__ __launch_bounds__(256) void k_eval_omega(Bvh bvh, vplmc_points pts, c
 }
 
 // Merge errors of the per-slice light coarsening (Sec. 4).  One thread per
-// row draw (slice s, draw r; r < dpre[n_g]), draws in depth-first order of their
-// leaves x (dpre, the prefix of the draw counts in that order), so that the
-// lanes of a wavefront lie below one small subtree; draw k < m' of leaf x: its row
-// is the k-th image of leaf x's keyed permutation of [0, m') (4-round
+// row draw (slice s, draw r; r < kpre[n_g]): draw k < m' of leaf x, its row
+// the k-th image of leaf x's keyed permutation of [0, m') (4-round
 // Feistel, round function Philox(key = (seed, s), ctr = (R, round, TAG_ZETA,
 // x)) & mask, cycle-walked).  Walking from x to the root, the thread carries
 // S(i, rep of the current node) at unit intensity; at each split node f
@@ -457,6 +455,101 @@ __device__ __forceinline__ uint64_t feistel_zeta(uint64_t v, uint64_t seed, uint
 }
 
 
+// the row of draw k of leaf x in slice s of m rows
+__device__ __forceinline__ int draw_row(int64_t k, int32_t rows, uint64_t seed, int s, int x) {
+    const uint64_t m = (uint64_t)rows;
+    int b = m > 1 ? 64 - __clzll((long long)(m - 1)) : 0;
+    b = b < 2 ? 2 : b;
+    const int h = (b + 1) / 2;
+    uint64_t e = feistel_zeta((uint64_t)k, seed, (uint64_t)s, (uint64_t)x, h);
+    while (e >= m) e = feistel_zeta(e, seed, (uint64_t)s, (uint64_t)x, h);
+    return (int)e;
+}
+
+__device__ __forceinline__ void raise_error(float *slot_f, float err) {
+    unsigned int *slot = reinterpret_cast<unsigned int *>(slot_f);
+    const unsigned int bits = __float_as_uint(err);
+    if (__hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < bits) atomicMax(slot, bits);
+}
+
+// whether the lights of the top of the tree are taken from a table: only where
+// at least half of the nominal draws exist (with fewer draws than leaves most
+// quotas round down to none)
+__device__ __forceinline__ bool top_table(const CoarsenTree &tr, const CoarsenSlices &cs, int64_t K) {
+    return tr.n_front > 1 && 2 * cs.kpre[tr.n_leaves] >= K;
+}
+
+// The walk of few draws: every thread its own path to the root, draws in leaf-id
+// order, the occluders staged in LDS where they fit.
+// Six wavefronts per SIMD (80 VGPRs): the walk's latency needs the occupancy;
+// at 83 VGPRs (five) the kernel ran 14% slower on the 1080p frame.
+template <bool STAGED, int KIND>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_coarsen_walk(
+    Bvh bvh, vplmc_points pts, const float *__restrict__ lights, const SliceDesc *__restrict__ desc, int64_t total, int64_t K,
+    const int32_t *__restrict__ pt_ids, CoarsenTree tr, CoarsenSlices cs, uint64_t seed, float r_min2, float eps,
+    unsigned long long *__restrict__ counts) {
+    extern __shared__ float4 stage[];
+    if (STAGED) {
+        const int nn = 2 * bvh.n_nodes, ns = bvh.n_spheres;
+        const float4 *nodes4 = reinterpret_cast<const float4 *>(bvh.nodes);
+        for (int k = threadIdx.x; k < nn + ns; k += blockDim.x) stage[k] = k < nn ? nodes4[k] : bvh.spheres[k - nn];
+        __syncthreads();
+    }
+    const BvhStaged<KIND> staged{stage, bvh.n_nodes};
+    const int ng = tr.n_leaves;
+    const size_t N = (size_t)(2 * ng - 1);
+    const int64_t kt = cs.kpre[ng];
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    uint32_t n_eval = 0, n_ray = 0;
+    for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < total; g += stride) {
+        const int s = (int)(g / K);
+        const int64_t r = g - (int64_t)s * K;
+        if (r >= kt) continue;
+        const SliceDesc d = desc[s];
+        int lo = 0, hi = ng;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (cs.kpre[mid] <= r) lo = mid; else hi = mid;
+        }
+        const int x = lo;
+        const int64_t k = r - cs.kpre[x];
+        if (k >= d.m) continue;
+        const int i = draw_row(k, d.m, seed, s, x);
+        cs.zeta[g] = (uint16_t)i;
+        const PointData q = load_point(pts, pt_ids[d.pt_off + i]);
+        auto entry = [&](int c, float &o0, float &o1, float &o2) {
+            const Light L = node_light(lights, N, c, true);
+            const bool ray = STAGED ? shade_in(staged, bvh.n_nodes, q, L, r_min2, eps, o0, o1, o2)
+                                    : shade<KIND>(bvh, q, L, r_min2, eps, o0, o1, o2);
+            n_eval += 1;
+            n_ray += ray ? 1u : 0u;
+        };
+        float c0, c1, c2;
+        entry(x, c0, c1, c2);
+        float *node_eps = cs.eps + (size_t)s * (ng - 1);
+        int c = x;
+        for (int f = tr.parent[x]; f >= 0; c = f, f = tr.parent[f]) {
+            const int kk = f - ng;
+            const int a = cs.kept[kk], bb = cs.dropped[kk];
+            const bool kept_path = c == a;
+            float o0, o1, o2;
+            entry(kept_path ? bb : a, o0, o1, o2);
+            const float a0 = kept_path ? c0 : o0, a1 = kept_path ? c1 : o1, a2 = kept_path ? c2 : o2;
+            const float b0 = kept_path ? o0 : c0, b1 = kept_path ? o1 : c1, b2 = kept_path ? o2 : c2;
+            const float err = fmaxf(fmaxf(lights[6 * N + bb] * fabsf(b0 - a0), lights[7 * N + bb] * fabsf(b1 - a1)),
+                                    lights[8 * N + bb] * fabsf(b2 - a2));
+            if (err > 0.0f) raise_error(node_eps + kk, err);
+            c0 = a0;
+            c1 = a1;
+            c2 = a2;
+        }
+    }
+    if (counts) {
+        add_count(counts, n_eval);
+        add_count(counts + 1, n_ray);
+    }
+}
+
 // The top of the tree, where the draws below a node outnumber the slice's rows
 // and the walk would evaluate the same (row, light) many times: every row of a
 // run of slices against the lights of the front nodes, once each.  Lanes are
@@ -465,8 +558,9 @@ constexpr int TOP_LIGHTS = 8;    // front nodes per thread
 template <bool STAGED, int KIND>
 __global__ __launch_bounds__(256) void k_coarsen_top(Bvh bvh, vplmc_points pts, const float *__restrict__ lights,
                                                      const SliceDesc *__restrict__ desc, int32_t s_first, int32_t s_end,
-                                                     int64_t row_first, int64_t rows, const int32_t *__restrict__ pt_ids,
-                                                     CoarsenTree tr, CoarsenSlices cs, float r_min2, float eps) {
+                                                     int64_t row_first, int64_t rows, int64_t K,
+                                                     const int32_t *__restrict__ pt_ids, CoarsenTree tr, CoarsenSlices cs,
+                                                     float r_min2, float eps) {
     extern __shared__ float4 stage[];
     if (STAGED) {
         const int nn = 2 * bvh.n_nodes, ns = bvh.n_spheres;
@@ -478,6 +572,7 @@ __global__ __launch_bounds__(256) void k_coarsen_top(Bvh bvh, vplmc_points pts, 
     __shared__ float4 lists[KIND == 0 ? 256 / 64 * SHAFT_CAP : 1];
     float4 *list = lists + (KIND == 0 ? threadIdx.x / 64 * SHAFT_CAP : 0);
     ShaftGate gate;
+    if (!top_table(tr, cs, K)) return;
     const int64_t R0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const bool act = R0 < rows;
     const int64_t R = act ? R0 : rows - 1;
@@ -501,10 +596,13 @@ __global__ __launch_bounds__(256) void k_coarsen_top(Bvh bvh, vplmc_points pts, 
     }
 }
 
-// All lanes of a wavefront are on one tree level at a time (deeper leaves start
-// earlier), so they meet the same node's light as soon as they are below it;
-// their shadow rays share a candidate list (occluded_shaft).  Lights of the top
-// of the tree come from k_coarsen_top's table.  Bound by VALU work (0.81 busy):
+// The walk of many draws: in depth-first order of their leaves (dpre, the prefix
+// of the draw counts in that order), so that the lanes of a wavefront lie below
+// one small subtree, and all lanes on one tree level at a time (deeper leaves start
+// earlier), so that they meet the same node's light as soon as they are below it:
+// their shadow rays share a candidate list (occluded_shaft), and one lane adds
+// the largest of their errors.  Lights of the top of the tree come from
+// k_coarsen_top's table.  Bound by VALU work (0.81 busy):
 // shading a third, shadow tests a third, the draws' permutation a ninth.
 // Measured on one MI355X, 1080p frame (3,069 slices, 32,768 draws, 16,384
 // leaves, 2,048 spheres): 154 ms with draws in leaf-id order, 135 depth-first,
@@ -532,6 +630,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     uint32_t n_eval = 0, n_ray = 0;
     const int lane = threadIdx.x & 63;
+    const bool table = top_table(tr, cs, K);
     __shared__ float4 lists[KIND == 0 ? 256 / 64 * SHAFT_CAP : 1];
     float4 *list = lists + (KIND == 0 ? threadIdx.x / 64 * SHAFT_CAP : 0);
     ShaftGate gate;
@@ -549,16 +648,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
         const int x = tr.dfs[lo];
         const int64_t k = r - cs.dpre[lo];
         const bool act = base + lane < total && r < kt && k < d.m;
-        // row of the draw
-        const uint64_t m = (uint64_t)d.m;
+        if (__ballot(act) == 0) continue;
         int i = 0;
         if (act) {
-            int b = m > 1 ? 64 - __clzll((long long)(m - 1)) : 0;
-            b = b < 2 ? 2 : b;
-            const int h = (b + 1) / 2;
-            uint64_t e = feistel_zeta((uint64_t)k, seed, (uint64_t)s, (uint64_t)x, h);
-            while (e >= m) e = feistel_zeta(e, seed, (uint64_t)s, (uint64_t)x, h);
-            i = (int)e;
+            i = draw_row(k, d.m, seed, s, x);
             cs.zeta[(int64_t)s * K + cs.kpre[x] + k] = (uint16_t)i;
         }
         const PointData q = load_point(pts, pt_ids[d.pt_off + i]);
@@ -581,7 +674,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             const int a = up ? cs.kept[kk] : x, bb = up ? cs.dropped[kk] : x;
             const int other = c == a ? bb : a;
             float o0, o1, o2;
-            const int ti = tr.n_front > 1 && on ? tr.tidx[other] : -1;
+            const int ti = table && on ? tr.tidx[other] : -1;
             bool ray = shade_wave<KIND>(bvh, STAGED ? &staged : nullptr, list, gate, on && ti < 0, q,
                                         node_light(lights, N, other, true), r_min2, eps, o0, o1, o2);
             if (ti >= 0) {                       // in the top of the tree: evaluated by k_coarsen_top
@@ -591,29 +684,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                 o2 = v.z;
                 ray = v.w != 0.f;
             }
-            if (!on) continue;
-            n_eval += 1;
-            n_ray += ray ? 1u : 0u;
-            if (first) {
-                c0 = o0;
-                c1 = o1;
-                c2 = o2;
-                continue;
-            }
+            n_eval += on ? 1u : 0u;
+            n_ray += on && ray ? 1u : 0u;
             const bool kept_path = c == a;
             const float a0 = kept_path ? c0 : o0, a1 = kept_path ? c1 : o1, a2 = kept_path ? c2 : o2;
             const float b0 = kept_path ? o0 : c0, b1 = kept_path ? o1 : c1, b2 = kept_path ? o2 : c2;
-            const float err = fmaxf(fmaxf(lights[6 * N + bb] * fabsf(b0 - a0), lights[7 * N + bb] * fabsf(b1 - a1)),
-                                    lights[8 * N + bb] * fabsf(b2 - a2));
-            if (err > 0.0f) {
-                unsigned int *slot = reinterpret_cast<unsigned int *>(node_eps + kk);
-                const unsigned int bits = __float_as_uint(err);
-                if (__hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < bits) atomicMax(slot, bits);
+            const float e = fmaxf(fmaxf(lights[6 * N + bb] * fabsf(b0 - a0), lights[7 * N + bb] * fabsf(b1 - a1)),
+                                  lights[8 * N + bb] * fabsf(b2 - a2));
+            const float err = up ? e : 0.f;
+            const unsigned long long some = __ballot(err > 0.0f);
+            if (some) {
+                const int lead = __ffsll(some) - 1;
+                const int k1 = __builtin_amdgcn_readlane(kk, lead), s1 = __builtin_amdgcn_readlane(s, lead);
+                // lanes below one node of one slice: their largest only
+                const bool one = __ballot(err > 0.0f && (kk != k1 || s != s1)) == 0;
+                const float top_err = one ? -wave_min(err > 0.0f ? -err : 0.f) : err;
+                if (one ? lane == lead : err > 0.0f) raise_error(node_eps + kk, top_err);
             }
-            c0 = a0;
-            c1 = a1;
-            c2 = a2;
-            c = f;
+            if (on) {
+                c0 = first ? o0 : a0;
+                c1 = first ? o1 : a1;
+                c2 = first ? o2 : a2;
+                c = first ? c : f;
+            }
         }
     }
     if (counts) {
@@ -1009,20 +1102,22 @@ int launch_eval_omega(hipStream_t st, const Bvh &bvh, const vplmc_points &pts, c
 
 template <bool STAGED, int KIND>
 static int coarsen_eps(hipStream_t st, const vplmc_plan &plan, const Bvh &bvh, size_t staged, const vplmc_points &pts,
-                       const float *lights, const SliceDesc *desc, const int32_t *pt_ids, const CoarsenTree &tr,
+                       const float *lights, const SliceDesc *desc, const int32_t *pt_ids, CoarsenTree tr,
                        const CoarsenSlices &cs, const vplmc_params &prm, int n_cu, unsigned long long *counts) {
     const int threads = 256;
     const float r_min2 = prm.r_min * prm.r_min;
-    const size_t runs = plan.n_front > 1 ? plan.top_runs.size() - 1 : 1;
+    if (bvh.n_nodes == 0) tr.n_front = 1;        // without shadow rays an entry costs no more than its look-up
+    const bool table = tr.n_front > 1;
+    const size_t runs = table ? plan.top_runs.size() - 1 : 1;
     for (size_t k = 0; k < runs; ++k) {
-        const int32_t s0 = plan.n_front > 1 ? plan.top_runs[k] : 0, s1 = plan.n_front > 1 ? plan.top_runs[k + 1] : plan.n_slices;
+        const int32_t s0 = table ? plan.top_runs[k] : 0, s1 = table ? plan.top_runs[k + 1] : plan.n_slices;
         const int64_t row0 = plan.desc[s0].off_row - s0;
-        if (plan.n_front > 1) {
+        if (table) {
             const int64_t rows = plan.desc[s1 - 1].off_row - (s1 - 1) + plan.desc[s1 - 1].m - row0;
             hipLaunchKernelGGL((k_coarsen_top<STAGED, KIND>),
-                               dim3(blocks_for(rows, threads), (unsigned)((plan.n_front + TOP_LIGHTS - 1) / TOP_LIGHTS)),
-                               dim3(threads), staged, st, bvh, pts, lights, desc, s0, s1, row0, rows, pt_ids, tr, cs,
-                               r_min2, prm.ray_eps);
+                               dim3(blocks_for(rows, threads), (unsigned)((tr.n_front + TOP_LIGHTS - 1) / TOP_LIGHTS)),
+                               dim3(threads), staged, st, bvh, pts, lights, desc, s0, s1, row0, rows,
+                               (int64_t)plan.pixels, pt_ids, tr, cs, r_min2, prm.ray_eps);
             VPLMC_HIP(hipGetLastError());
         }
         const int64_t total = (int64_t)(s1 - s0) * plan.pixels;
@@ -1035,12 +1130,36 @@ static int coarsen_eps(hipStream_t st, const vplmc_plan &plan, const Bvh &bvh, s
     return VPLMC_OK;
 }
 
+// Draws of a launch (over all slices) from which the level-by-level walk pays:
+// with fewer its longer chain of loads per level costs more than the shared lists
+// save.  Merge-error phase, ms, own walk per thread / level by level: 2.6e5 draws
+// 0.52 / 0.62 (512 spheres, 4,096 leaves) and 0.97 / 0.69 (2,048, 16,384), 5.2e5
+// 0.84 / 0.80 and 1.19 / 0.61, 2.1e6 2.54 / 1.49 and 3.81 / 1.54; triangles 6.6e4
+// 0.84 / 1.07, 1.0e6 4.4 / 4.0.  Dense occluders whose lists overflow lose up to
+// a quarter of it at 1e6 draws (1.06 / 1.40 ms) and nothing at 8e6 (6.3 / 6.2).
+// Without occluders there is nothing to share: 2.1e6 0.81 / 0.95, 8.4e6 2.65 / 2.31.
+constexpr int64_t COARSEN_LEVELS_FROM = 1 << 19;
+constexpr int64_t COARSEN_LEVELS_FROM_NO_OCCLUDERS = 1 << 22;
+
 int launch_coarsen_eps(hipStream_t st, const vplmc_plan &plan, const Bvh &bvh, const vplmc_points &pts,
                        const float *lights, const SliceDesc *desc, const int32_t *pt_ids, const CoarsenTree &tr,
                        const CoarsenSlices &cs, const vplmc_params &prm, int n_cu, unsigned long long *counts) {
     if (plan.n_slices <= 0 || plan.pixels <= 0) return VPLMC_OK;
     const size_t staged = ((size_t)2 * bvh.n_nodes + bvh.n_spheres) * sizeof(float4);
-    const bool stage = bvh.kind == 1 && bvh.n_nodes > 0 && staged <= (size_t)EVAL_LDS_BYTES;   // spheres: occluded_shaft
+    const bool fits = bvh.n_nodes > 0 && staged <= (size_t)EVAL_LDS_BYTES;
+    const int64_t total = (int64_t)plan.n_slices * plan.pixels;
+    if (total < (bvh.n_nodes > 0 ? COARSEN_LEVELS_FROM : COARSEN_LEVELS_FROM_NO_OCCLUDERS)) {
+        const int threads = 256;
+        const int64_t blocks = std::min<int64_t>(blocks_for(total, threads), (int64_t)EVAL_GRID_PER_CU * n_cu);
+        auto walk = bvh.kind == 1 ? (fits ? k_coarsen_walk<true, 1> : k_coarsen_walk<false, 1>)
+                                  : (fits ? k_coarsen_walk<true, 0> : k_coarsen_walk<false, 0>);
+        hipLaunchKernelGGL(walk, dim3((unsigned)blocks), dim3(threads), fits ? staged : 0, st, bvh, pts, lights, desc,
+                           total, (int64_t)plan.pixels, pt_ids, tr, cs, prm.seed, prm.r_min * prm.r_min, prm.ray_eps,
+                           counts);
+        VPLMC_HIP(hipGetLastError());
+        return VPLMC_OK;
+    }
+    const bool stage = bvh.kind == 1 && fits;   // spheres: occluded_shaft
     auto run = stage ? coarsen_eps<true, 1> : (bvh.kind == 1 ? coarsen_eps<false, 1> : coarsen_eps<false, 0>);
     return run(st, plan, bvh, stage ? staged : 0, pts, lights, desc, pt_ids, tr, cs, prm, n_cu, counts);
 }

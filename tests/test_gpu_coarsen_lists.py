@@ -1,6 +1,6 @@
-"""The coarsening's wavefront-shared shadow test against the traversal of the same spheres, bit for bit: more than
-16,384 spheres turn the lists off, so spheres that no segment can meet, far below the scene, give the traversal's
-answer on the same code."""
+"""The coarsening's walks against each other, bit for bit.  More than 16,384 spheres turn the wavefront-shared lists
+off, so spheres that no segment can meet, far below the scene, give the traversal's answer; half the slices are too
+few draws for the level-by-level walk and take the one of a path per thread."""
 import dataclasses
 
 import numpy as np
@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from paper_2202_12567_amd import api  # noqa: E402
-from scenegen import make_scene  # noqa: E402
+from scenegen import make_scene, scene_sample  # noqa: E402
 
 SEED = 6
 DEV = torch.device("cuda", 0)
@@ -49,6 +49,29 @@ def test_equals_the_traversal(K, normal):
     lists, walk = (merge_errors(sc, below(sc.spheres, extra), K) for extra in (0, 17000))
     assert int((lists != 0).sum()) > 500
     assert torch.equal(lists, walk)
+
+
+def occluders(kind):
+    rng = np.random.default_rng(17)
+    n, side, z, r = {"none": (0, (0, 1), (0, 1), (0.1, 0.2)), "own": (0, (0, 1), (0, 1), (0.1, 0.2)),
+                     "65 groups": (2080, (0, 1), (0.12, 0.24), (0.004, 0.02)),
+                     "overflow, staged": (700, (0.35, 0.65), (0.21, 0.24), (0.01, 0.03)),
+                     "overflow": (1600, (0.35, 0.65), (0.21, 0.24), (0.006, 0.018))}[kind]
+    f = np.float32
+    return dict(cx=rng.uniform(*side, n).astype(f), cy=rng.uniform(*side, n).astype(f),
+                cz=rng.uniform(*z, n).astype(f), r=rng.uniform(*r, n).astype(f))
+
+
+@pytest.mark.parametrize("kind,K", [("own", 32768), ("65 groups", 32768), ("overflow, staged", 32768), ("overflow", 32768),
+                                    ("overflow", 70001), ("triangles", 32768), ("none", 262144)])
+def test_levels_equal_the_walk_per_thread(kind, K):
+    """16 slices of 32,768 draws are 2^19, from where the walk goes level by level (2^22 without occluders)."""
+    sc = make_scene("tri" if kind == "triangles" else "tiny", SEED)
+    sph = sc.spheres if kind in ("own", "triangles") else occluders(kind)
+    few = merge_errors(scene_sample(sc, list(range(8))), sph, K)
+    many = merge_errors(sc, sph, K)
+    assert int((few != 0).sum()) > 500
+    assert torch.equal(many[:few.shape[0]], few)
 
 
 def coarsen_ms(sc, spheres, K):
