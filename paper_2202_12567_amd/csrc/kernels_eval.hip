@@ -755,15 +755,25 @@ __global__ __launch_bounds__(256) void k_eval_pairs(Bvh bvh, vplmc_points pts, v
     out[3 * g + 2] = o2;
 }
 
-// Brute-force column sum against triangles: one thread per point and light chunk (grid.y),
+// Brute-force column sum against triangles, or against few spheres: one thread per point and light chunk (grid.y),
 // lights staged through LDS; FP32 entries summed in FP64, chunk partial sums
 // added to the zeroed output with FP64 atomics.  Bound by the shadow rays'
 // traversal, whose latency needs wavefronts: the chunk (BF_MIN_CHUNK to
 // BF_CHUNK lights) is the largest that still gives BF_GRID_PER_CU workgroups
-// per CU.
+// per CU (163,842 triangles, 1,024 points, 512 lights: chunks of 64 5.2 ms, of 16 1.4).
 constexpr int BF_TILE = 256;
-constexpr int BF_CHUNK = 2048, BF_MIN_CHUNK = 64;
+constexpr int BF_CHUNK = 2048, BF_MIN_CHUNK = 16;
 constexpr int BF_GRID_PER_CU = 16;
+// Spheres so few, or spheres times lights so few, that ordering the points and
+// listing the spheres costs more than it saves (a call with one light 23 us here,
+// 50-70 in k_brute_spheres).  us here / there, 1,024 points: 4 spheres 56 / 108
+// (16 lights), 212 / 316 (16,384); 32 spheres 41 / 74 (4), 92 / 117 (16), 364 / 358
+// (16,384); 128 spheres 77 / 85 (4), 230 / 164 (16); 512 spheres 54 / 86 (1), 133 /
+// 133 (4).  8,192 points and 16,384 lights: 8 spheres 1,320 / 1,572, 12 spheres
+// 1,728 / 1,536.
+constexpr int BF_FEW_SPHERES = 8;
+constexpr int64_t BF_FEW_TESTS = 512;
+template <int KIND>
 __global__ __launch_bounds__(256) void k_brute_force(Bvh bvh, vplmc_points pts, vplmc_lights l, int32_t n_out,
                                                      const int32_t *__restrict__ pid, int32_t chunk, float r_min2,
                                                      float eps, double *__restrict__ out) {
@@ -795,7 +805,7 @@ __global__ __launch_bounds__(256) void k_brute_force(Bvh bvh, vplmc_points pts, 
                 const Light L = {{sl[0][k], sl[1][k], sl[2][k]}, {sl[3][k], sl[4][k], sl[5][k]}, sl[6][k], sl[7][k],
                                  sl[8][k]};
                 float o0, o1, o2;
-                shade<1>(bvh, q, L, r_min2, eps, o0, o1, o2);
+                shade<KIND>(bvh, q, L, r_min2, eps, o0, o1, o2);
                 a0 += (double)o0;
                 a1 += (double)o1;
                 a2 += (double)o2;
@@ -827,7 +837,7 @@ __global__ __launch_bounds__(256) void k_brute_force(Bvh bvh, vplmc_points pts, 
 // 16: as 8); each orders its segment again.
 constexpr int BS_SEG = 4096, BS_THREADS = 1024, BS_WAVES = BS_THREADS / 64;
 constexpr int BS_AXIS = 64;                  // Morton cells per axis
-constexpr int BS_GRID_PER_CU = 8;
+constexpr int BS_GRID_PER_CU = 8, BS_MIN_CHUNK = 64;
 
 __device__ __forceinline__ uint32_t spread6(uint32_t x) {        // bit b of x to bit 2 b
     x = (x | (x << 4)) & 0x30Fu;
@@ -1199,15 +1209,16 @@ int launch_brute_force(hipStream_t st, const Bvh &bvh, const vplmc_points &pts, 
     hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)std::min<size_t>((nz + 255) / 256, 65536)), dim3(256), 0, st, out, nz);
     VPLMC_HIP(hipGetLastError());
     if (l.n <= 0) return VPLMC_OK;
-    const bool tri = bvh.kind == 1;
-    const int64_t blocks = tri ? blocks_for(n_out, 256) : bs_blocks(n_out);
-    const int64_t want = (int64_t)(tri ? BF_GRID_PER_CU : BS_GRID_PER_CU) * n_cu;
+    const bool plain = bvh.kind == 1 || bvh.n_spheres <= BF_FEW_SPHERES || (int64_t)bvh.n_spheres * l.n <= BF_FEW_TESTS;
+    const int64_t blocks = plain ? blocks_for(n_out, 256) : bs_blocks(n_out);
+    const int64_t want = (int64_t)(plain ? BF_GRID_PER_CU : BS_GRID_PER_CU) * n_cu;
+    const int32_t smallest = plain ? BF_MIN_CHUNK : BS_MIN_CHUNK;
     int32_t chunk = BF_CHUNK;
     // (grid.y is at most 65,535)
-    while (chunk > BF_MIN_CHUNK && blocks * ((l.n + chunk - 1) / chunk) < want && l.n / (chunk / 2) < 65535) chunk /= 2;
+    while (chunk > smallest && blocks * ((l.n + chunk - 1) / chunk) < want && l.n / (chunk / 2) < 65535) chunk /= 2;
     const unsigned chunks = (unsigned)((l.n + (int64_t)chunk - 1) / chunk);
-    if (tri)
-        hipLaunchKernelGGL(k_brute_force, dim3((unsigned)blocks, chunks), dim3(256), 0, st, bvh, pts, l, n_out,
+    if (plain)
+        hipLaunchKernelGGL((bvh.kind == 1 ? k_brute_force<1> : k_brute_force<0>), dim3((unsigned)blocks, chunks), dim3(256), 0, st, bvh, pts, l, n_out,
                            pid, chunk, prm.r_min * prm.r_min, prm.ray_eps, out);
     else
         hipLaunchKernelGGL(k_brute_spheres, dim3((unsigned)blocks, chunks), dim3(BS_THREADS), 0, st, bvh, pts, l, n_out,
