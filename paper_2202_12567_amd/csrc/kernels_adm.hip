@@ -36,10 +36,11 @@ namespace {
 // ---------------------------------------------------------------------------
 // LDS-resident variant for ranks 4, 8, 16 (two LDS buffers of m (q + 1)
 // words: X_k, and the R Y^T accumulator that then holds T and X+).  The
-// samples are read from the slice's ELL copy, in which one lane walks one
-// part of a column (at most ELL_LMAX samples; the parts of a 64-lane group
-// have nearly equal lengths) and every load of a wavefront covers 64
-// consecutive entries.
+// samples are read from the slice's ELL copy: columns cut into parts (at most
+// ELL_LMAX samples), 64 parts of nearly equal lengths to a group, the k-th
+// entries of a group's parts consecutive.  Phase B's lanes walk a part each, so
+// that every load of a wavefront covers 64 consecutive entries; phase A takes
+// four entries of 16 parts at a time.
 //   phase A, 4 lanes = part of column j, a lane = one of its samples: X_i from
 //     LDS, both products with Y_j (X_i . Y_j and sum_c r_c Y_j^c) on 4 x 4 x 1
 //     FP32 matrix instructions, whose results lie in the sample's own lane and
@@ -441,12 +442,98 @@ __device__ void adm_ell_slice(
             // takes items as they do
             if (wave == NW - 1 && !xsys) spd_solve_wave<Q, true>(sh, alpha, lane);
             xsys = true;
+            // Rank 4 with many samples: an item is a group of 64 parts, a lane walks its
+            // part, its column's Y in registers.  Same sums bit for bit.  At 12
+            // products per sample the matrix form's loads and stores, which take 64
+            // entries from four places, outweigh what it saves; its items of 16 parts
+            // spread few samples better.  Four slices, 100 iterations, ms, matrix form /
+            // by lane: 1,024 x 600 at 15% (92,160 samples) 12.7 / 8.8, 1,024 x 300 at 6.5%
+            // (19,968) 4.58 / 4.37, 256 x 600 (9,984) 3.69 / 4.35.  At rank 8 the same code
+            // gave up to 10% from 50,000 samples on and cost 1-3% below (registers).
+            bool by_lane = false;
+            if constexpr (Q == 4) by_lane = nnz >= 16384 && G >= NW / 2;
+            if constexpr (Q == 4) if (by_lane) {
+                constexpr int U = 4;
+                for (int g = wave == NW - 1 ? next_item(taken_a, lane) : wave; g < G; g = next_item(taken_a, lane)) {
+                    int j, cnt, pc, np;
+                    part_of(g, j, cnt, pc, np);
+                    const int base = grp[g];
+                    const int len = (grp[g + 1] - base) >> 6;
+                    float y[3 * Q];
+#pragma unroll
+                    for (int v = 0; v < 3 * QV; ++v) {
+                        const float4 a = reinterpret_cast<const float4 *>(Y + (size_t)j * 3 * Q)[v];
+                        y[4 * v] = a.x;
+                        y[4 * v + 1] = a.y;
+                        y[4 * v + 2] = a.z;
+                        y[4 * v + 3] = a.w;
+                    }
+                    double es[U] = {0.0, 0.0, 0.0, 0.0};
+                    int in[U];
+                    float mn[U][3];
+                    auto load_block = [&](int k0) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const int e = base + 64 * min(k0 + u, len - 1) + lane;
+                            in[u] = (int)erow[e];
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) mn[u][c] = eval[3 * e + c];
+                        }
+                    };
+                    if (len > 0) load_block(0);
+                    for (int k0 = 0; k0 < len; k0 += U) {
+                        int ib[U];
+                        float mb[U][3];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            ib[u] = in[u];
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) mb[u][c] = mn[u][c];
+                        }
+                        if (k0 + U < len) load_block(k0 + U);
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            if (k0 + u >= cnt) continue;
+                            float x[Q];
+#pragma unroll
+                            for (int v = 0; v < QV; ++v) {
+                                const float4 a4 = *xchunk<Q>(XA, ib[u], v);
+                                x[4 * v] = a4.x;
+                                x[4 * v + 1] = a4.y;
+                                x[4 * v + 2] = a4.z;
+                                x[4 * v + 3] = a4.w;
+                            }
+                            float r[3];
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) {
+                                float d = 0.f;
+#pragma unroll
+                                for (int kk = 0; kk < Q; ++kk) d = fmaf(x[kk], y[c * Q + kk], d);
+                                r[c] = fmaf(mb[u][c], inv_s0, -d);
+                            }
+                            const int e = base + 64 * (k0 + u) + lane;
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) eres[3 * e + c] = r[c];
+                            es[u] += (double)(r[0] * r[0]) + (double)(r[1] * r[1]) + (double)(r[2] * r[2]);
+                            const float rsa = fabsf(r[0]) + fabsf(r[1]) + fabsf(r[2]);
+                            rsm = fmaxf(rsm, rsa);
+                            const float s0r = r[0] * fxs, s1r = r[1] * fxs, s2r = r[2] * fxs;
+                            int32_t *rx = RXI + ib[u] * (Q + 1);
+#pragma unroll
+                            for (int kk = 0; kk < Q; ++kk)
+                                atomicAdd(rx + kk, __float2int_rn(fmaf(s0r, y[kk], fmaf(s1r, y[Q + kk], s2r * y[2 * Q + kk]))));
+                            atomicAdd(reinterpret_cast<uint32_t *>(rx + Q), __float2uint_ru(rsa * fxr));
+                        }
+                    }
+                    if (64 * g + lane < P) e2part[pc] = (es[0] + es[1]) + (es[2] + es[3]);
+                }
+            }
             // An item is 16 parts of one group, 4 lanes per part; lane 4 b + u
             // takes the entries 4 s + u of part b.  Both products of a part with
             // its column's Y are 4 x 4 x 1 matrix instructions whose second operand
             // and result belong to the lane's own entry.
             const int bq = lane >> 2, uq = lane & 3;
-            const int items = (P + 15) >> 4;
+            const int items = by_lane ? 0 : (P + 15) >> 4;
             for (int item = wave == NW - 1 ? next_item(taken_a, lane) : wave; item < items;
                  item = next_item(taken_a, lane)) {
                 const int sp = 16 * item + bq;
