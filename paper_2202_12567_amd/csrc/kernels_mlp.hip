@@ -323,7 +323,9 @@ __device__ __forceinline__ GeluSigmoid gelu_sigmoid(float x) {
     g.q = fmaf(-(g.e - (d - 1.0f)), g.r, fmaf(-d, g.r, 1.0f)) * g.r;
     return g;
 }
-__device__ __forceinline__ float gelu_value(float x, const GeluSigmoid &g) { return fmaf(x, g.r, x * g.q); }
+__device__ __forceinline__ float gelu_value(float x, const GeluSigmoid &g) {
+    return fabsf(g.v) > 80.0f ? x * g.r : fmaf(x, g.r, x * g.q);     // (an infinite x times a correction of either sign)
+}
 __device__ __forceinline__ float gelu_slope(float x, const GeluSigmoid &g) {
     const float du = SQRT_2_OVER_PI * (1.0f + 3.0f * 0.044715f * x * x);
     const float s = g.r + g.q;
