@@ -545,6 +545,13 @@ __global__ __launch_bounds__(64 * TRAIN_BW) void k_train_backward(const float *_
                 a3[v] = d * bf16r(gelu_value(z[v], sg));
                 dz[v] = d * w3s[unit(t, v, half)] * gelu_slope(z[v], sg);
             }
+            if (r0 + TRAIN_ROWS > rows) {          // rows past the end add nothing, whatever the biases give there
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    a3[v] = in ? a3[v] : 0.f;
+                    dz[v] = in ? dz[v] : 0.f;
+                }
+            }
             gw3[t] += half_sums(a3, lane);
             if (in) {
 #pragma unroll
@@ -674,9 +681,10 @@ __global__ __launch_bounds__(256) void k_train_dw2(int64_t rows, int64_t per, co
         float a[NS], b[NS][4];
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
-            a[i] = r0 + 2 * i + half < end ? an[i] : 0.f;
+            const bool in = r0 + 2 * i + half < end;
+            a[i] = in ? an[i] : 0.f;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) b[i][t] = __uint_as_float((uint32_t)bn[i][t] << 16);
+            for (int t = 0; t < 4; ++t) b[i][t] = in ? __uint_as_float((uint32_t)bn[i][t] << 16) : 0.f;
         }
         if (r0 + DW2_ROWS < end) load(r0 + DW2_ROWS);
 #pragma unroll

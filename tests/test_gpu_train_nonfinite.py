@@ -30,3 +30,20 @@ def test_infinite_activation(rows):
                                     np.ones(rows))
     assert np.array_equal(np.isposinf(gw3), np.isinf(b2)) and np.isfinite(gw3[b2 == 1]).all()
     assert np.all(gb2[[3, 100]] == rows) and np.isfinite(gb2).all()
+
+
+@pytest.mark.parametrize("rows", [1, 5, 33, 300])
+def test_rows_past_the_end_add_nothing(rows):
+    """Row counts that fill no tile: an infinite bias of either layer must not meet the 0 of a row past the end."""
+    b1, b2 = np.ones(H), np.ones(H)
+    b1[7] = b2[3] = np.inf
+    W2 = np.full((H, H), 0.01)
+    gw1, gb1, gw2, gb2, gw3, gb3 = gradient(np.zeros((H, K)), np.zeros(H), np.zeros((H, H)), b2, np.ones(H),
+                                            np.ones((rows, K)), np.ones(rows))
+    assert np.array_equal(np.isposinf(gw3), np.isinf(b2)) and np.isfinite(gw3[b2 == 1]).all()
+    # first layer: every z2 is infinite then, every slope of the second layer 1
+    gw1, gb1, gw2, gb2, gw3, gb3 = gradient(np.zeros((H, K)), b1, W2, np.zeros(H), np.ones(H), np.ones((rows, K)),
+                                            np.ones(rows))
+    assert np.isposinf(gw3).all() and np.all(gb2 == rows) and np.all(gb3 == rows)
+    assert np.isposinf(gw2[:, 7]).all() and np.isfinite(np.delete(gw2, 7, 1)).all()
+    assert np.isfinite(gw1).all() and np.isfinite(gb1).all()
