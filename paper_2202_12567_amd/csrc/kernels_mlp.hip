@@ -336,6 +336,11 @@ __device__ __forceinline__ float gelu_slope(float x, const GeluSigmoid &g) {
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {   // operands already representable
     return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xFFFF0000u);
 }
+// what the leading 8 significant bits leave of x (an infinity leaves nothing)
+__device__ __forceinline__ float remainder_bf16(float x) {
+    const float lead = __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
+    return x == lead ? 0.f : x - lead;
+}
 __device__ __forceinline__ float16_t mfma_bf16(const uint4 &a, const uint4 &b, float16_t c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
 }
@@ -570,8 +575,8 @@ __global__ __launch_bounds__(64 * TRAIN_BW) void k_train_backward(const float *_
                     for (int k = 0; k < 4; ++k) {
                         float &x0 = dz[8 * u + 2 * k], &x1 = dz[8 * u + 2 * k + 1];
                         pk[k] = pack_bf16(x0, x1);
-                        x0 -= __uint_as_float(__float_as_uint(x0) & 0xFFFF0000u);
-                        x1 -= __uint_as_float(__float_as_uint(x1) & 0xFFFF0000u);
+                        x0 = remainder_bf16(x0);
+                        x1 = remainder_bf16(x1);
                     }
                     term[c] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
                 }

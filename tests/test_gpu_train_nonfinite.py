@@ -47,3 +47,13 @@ def test_rows_past_the_end_add_nothing(rows):
     assert np.isposinf(gw3).all() and np.all(gb2 == rows) and np.all(gb3 == rows)
     assert np.isposinf(gw2[:, 7]).all() and np.isfinite(np.delete(gw2, 7, 1)).all()
     assert np.isfinite(gw1).all() and np.isfinite(gb1).all()
+
+
+@pytest.mark.parametrize("dy,w3", [(np.inf, 1.0), (-np.inf, 1.0), (3e38, 2.0)])
+def test_infinite_slope_of_the_second_layer(dy, w3):
+    """dz2 infinite (given so, or by overflow) reaches the first layer's gradients as an infinity."""
+    W2 = np.random.default_rng(5).uniform(0.01, 0.02, (H, H))
+    gw1, gb1, gw2, gb2, gw3, _ = gradient(np.zeros((H, K)), np.full(H, 32.0), W2, np.full(H, 1000.0), np.full(H, w3),
+                                          np.ones((1, K)), np.array([dy]))
+    for g in (gw1, gb1, gw2, gb2, gw3):
+        assert np.array_equal(g, np.full(g.shape, np.copysign(np.inf, dy)))
