@@ -602,7 +602,8 @@ def main():
         "sampled_fraction_of_slice_matrices": round(entries / matrix_entries, 5),
         "columns_per_slice": {"min": int(n_s.min()), "mean": round(float(n_s.mean()), 1), "max": int(n_s.max())},
         # shadow rays (sampled entries whose point and light face each other) over
-        # the entry phases' time; the coarsening's unit-intensity evaluations over its phase
+        # the entry phases' time; the entries the coarsening's draws take over its phase (those of the
+        # top of the tree are evaluated once per row and counted for every draw)
         "rays": {"entry_rays_per_frame": tot["rays"],
                  "entry_rays_per_s": round(tot["rays"] / ((phase_ms["eval1"] + phase_ms["eval2"]) * 1e-3), 1),
                  "coarsen_evals_per_frame": tot["coarsen_evals"], "coarsen_rays_per_frame": tot["coarsen_rays"],

@@ -289,6 +289,8 @@ int vplmc_plan_create_coarse(int32_t n_slices, const int32_t *pt_offsets, const 
                              const vplmc_coarsen *coarsen, const vplmc_params *params,
                              vplmc_plan **out /* HOST */);
 int vplmc_plan_destroy(vplmc_plan *plan);
+/* A coarsened frame's workspace includes up to 512 MiB for the lights of the
+ * top of its tree on the rows of its slices. */
 int vplmc_workspace_size(const vplmc_plan *plan, size_t *bytes /* HOST */);
 int vplmc_plan_slice(const vplmc_plan *plan, int32_t s, vplmc_slice_info *out /* HOST */);
 int vplmc_plan_region(const vplmc_plan *plan, int32_t region, size_t *offset /* HOST */,
@@ -347,9 +349,11 @@ int vplmc_read_counts(vplmc_ctx *ctx, const vplmc_plan *plan, const void *worksp
 
 /* Totals of the last frame rendered on this workspace (synchronises), HOST
  * int64[4]: sampled entries (both passes), shadow rays cast for them (entries
- * whose point and light face each other), entries the light coarsening
- * evaluated (unit-intensity lighting of a drawn row by a node's light), and
- * the shadow rays among those. */
+ * whose point and light face each other), entries the light coarsening's
+ * draws take (unit-intensity lighting of a drawn row by a node's light, one
+ * per draw and tree level), and those among them whose point and light face
+ * each other.  Entries of the top of the tree that many draws of a row share
+ * are evaluated once, with one shadow ray, and counted for every draw. */
 int vplmc_read_totals(vplmc_ctx *ctx, const vplmc_plan *plan, const void *workspace, int64_t *out);
 
 /* Counts, on the device, the ids that break the contract of vplmc_render:

@@ -752,9 +752,10 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
         L.total = off;
     };
     lay_out();
-    // the workspace without the tables that only save time: top table, depth-first
-    // half of the tree, ALS residual slots but one; and with the two residual sums
-    // per part that the completion once kept
+    // what the static workspace's limit counts: the workspace without the tables that
+    // only save time (top table, depth-first half of the tree, ALS residual slots but
+    // one), and two residual sums per part where one is kept, so that the limit
+    // admits the same frames whatever the kernels keep beside them
     size_t core[R_INTERNAL_END];
     std::copy(bytes, bytes + R_INTERNAL_END, core);
     core[R_TOP] = core[R_TOP_MAP] = 0;

@@ -36,11 +36,12 @@
 // sample order, and a row's place in a slot's sum depends on the counts alone:
 // factors, residuals and iteration counts are bit-reproducible.
 //
-// Bound by the latency of the gathers on the longest columns and by the
-// elimination's dependent FP64 chain.  Measured on one MI355X, 48 slices of
+// The row launch is bound by VALU issue (0.62 busy: Grams, elimination), the
+// column launch by the gathers and the dependent chain of its longest sums (0.21
+// busy, 0.7 wavefronts per SIMD).  Measured on one MI355X, 48 slices of
 // 200-900 rows, 300 columns, rank 16, 6.5% sampled, 100 iterations: 467 ms
 // with one 512-thread workgroup per slice and the systems in LDS (Cholesky by
-// one wavefront per row), 13.0 ms now; Grams on the matrix unit (a
+// one wavefront per row), 11.8 ms now; Grams on the matrix unit (a
 // wavefront per four systems, summed in another order) took 16 ms in FP32 and
 // 26 ms in FP64.
 

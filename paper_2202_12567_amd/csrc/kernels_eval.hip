@@ -190,7 +190,10 @@ __device__ __forceinline__ float wave_min(float v) {
 constexpr int SHAFT_CAP = 128;
 // The tests of the groups are linear in their number; a traversal is not.  8,192
 // points against 4,096 lights and fine spheres, lists / traversal of the same
-// wavefronts: 1,024 groups 8.1 / 7.9 ms, 2,048 groups 10.2 / 10.1 ms.
+// wavefronts: 1,024 groups 8.1 / 7.9 ms, 2,048 groups 10.2 / 10.1 ms.  Spheres that
+// cover the same part of the scene whatever their number: 128 groups 3.56 / 3.97 ms,
+// 256 4.74 / 4.70, 512 4.82 / 4.75, 1,024 5.09 / 5.00; 512 x 512 coarsened frames
+// 24.8 / 24.9, 26.6 / 26.3, 27.9 / 27.5, 29.4 / 28.9 ms.
 constexpr int SHAFT_MAX_GROUPS = 512;
 
 // an origin that the arithmetic on boxes takes (an infinite one would leave every lane of its wavefront an empty shaft)
@@ -828,9 +831,9 @@ __global__ __launch_bounds__(256) void k_brute_force(Bvh bvh, vplmc_points pts, 
 // whose spheres are listed once (shaft_list).  With fewer runs of 64 points than
 // wavefronts, several wavefronts share a run and split its lights.  FP32 entries
 // summed in FP64, partial sums added to the zeroed output with FP64 atomics.
-// Bound by the latency of listing (a wavefront's list takes several dependent
-// loads), hence 8 wavefronts per SIMD although some registers spill: 5.3 ms
-// against 5.9 without.  8,192 points against 16,384 lights and 512 spheres 14.7 ->
+// Bound by VALU issue (0.80 busy) once the latency of listing (several dependent
+// loads per list) is covered, hence 8 wavefronts per SIMD although some registers
+// spill: 5.3 ms against 5.9 without.  8,192 points against 16,384 lights and 512 spheres 14.7 ->
 // 5.1 ms (with a traversal per ray, points in caller order), 64 points 1.47 ->
 // 0.44 ms, 16 spheres and 4,096 lights 0.84 -> 0.53 ms, 65,536 small spheres 15.4
 // -> 10.1 ms.  BS_GRID_PER_CU workgroups per CU even out the ends (4: 6.0 ms,

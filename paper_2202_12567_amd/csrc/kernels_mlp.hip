@@ -257,16 +257,18 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ P
 // inside a pass.  The 128 x 128 products run on v_mfma_f32_32x32x16_bf16 with
 // FP32 accumulation: forward both operands are bfloat16 anyway; backward
 // dz2 (FP32) enters as three bfloat16 terms that sum to it exactly (its 24
-// significant bits in eights), so every product is exact.  Nothing of the
+// significant bits in eights), so every product is exact (the sums of W2^T dz2
+// alone: relative RMS error 1.14e-7 against 64 bits, a chain of FP32 fmas 2.03e-7).  Nothing of the
 // forward pass is kept: the backward pass recomputes it, which costs less
 // than four 128-vectors of FP32 per row written and read back.  dW2 contracts
 // over rows: the backward kernel leaves dz2 and h1 in the scratch and
 // k_train_dw2 forms it with FP32 MFMA.  Each workgroup adds its partial
 // gradients with FP32 atomics.
 //
-// Bound by the activations' VALU work (a sigmoid per hidden unit and pass).
+// Bound by the activations' VALU work (a sigmoid per hidden unit and pass; VALU
+// 0.73 busy forward, 0.52 backward), dW2 by the matrix unit (0.35 busy) and its loads.
 // Measured on one MI355X, 131,072 rows: forward 0.97 -> 0.053 ms, backward
-// 5.53 -> 0.22 ms (0.146 and 0.075 for dW2), against FP32 VALU kernels that kept the activations in
+// 5.53 -> 0.24 ms (0.161 and 0.076 for dW2), against FP32 VALU kernels that kept the activations in
 // the scratch and added every 32-row block's gradients with 18,000 atomics.
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef float f4_t __attribute__((ext_vector_type(4)));

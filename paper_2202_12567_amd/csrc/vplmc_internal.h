@@ -290,7 +290,8 @@ struct vplmc_plan {
     int32_t n_front = 0;           // front nodes of the top of the tree (1: no table)
     std::vector<int32_t> top_runs; // slice runs whose top-light tables share the region, as boundaries
     double bound = 0.0;
-    std::vector<int32_t> tree;     // left, right, parent, height, min_leaf, order, level_off
+    // left, right, parent, height, min_leaf, order, level_off, dfs, depth, tidx, front, opened nodes
+    std::vector<int32_t> tree;
     int32_t pass1_ppm = 0, pass2_ppm = 0;
     int64_t sum_m = 0, max_m = 0;
     std::vector<vplmc::SliceDesc> desc;
@@ -321,7 +322,11 @@ namespace vplmc {
 constexpr int GADM_RB = 64;
 constexpr int GADM_CB = 256;
 // with too few columns for GADM_CB-column blocks to fill the chip (fewer than
-// GADM_CB_FEW blocks in the rank bucket), blocks are this small
+// GADM_CB_FEW blocks in the rank bucket), blocks are this small.  Rank 32, slices
+// of 150-400 rows, 512 columns, 100 iterations, ms with blocks of 64 / 256
+// columns: 512 blocks of 256 32.4 / 35.1, 1,024 56.9 / 57.3, 2,048 109.3 / 105.1,
+// 4,096 211 / 201 (256 columns: 36.4 / 39.2, 69.3 / 70.3, 134.4 / 131.9, 263 / 255);
+// masked ALS takes the same time with either.
 constexpr int GADM_CB_SMALL = 64;
 constexpr int64_t GADM_CB_FEW = 2048;
 constexpr int ALS_E2_SLOTS = 8;   // masked ALS: squared-residual slots per row block
