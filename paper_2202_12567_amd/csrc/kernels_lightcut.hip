@@ -40,8 +40,12 @@ namespace {
 
 constexpr int WAVE = 64;
 constexpr int LT = 256;          // threads of the grid kernels
-constexpr int TS = 4, CHUNK = TS * LT;   // samples per thread and per workgroup of the split test
 constexpr int TN = 32;           // nodes it stages at once
+// Nodes times workgroups' samples up to which a level of the split test shares nothing
+// between its nodes.  us a call with every level shared / up to 512 / 2,048 tiles without: 1,000
+// VPLs and 8,192 samples 491 / 468 / 457, 30,000 and 8,192 1,120 / 1,095 / 1,089, 300,000 and 8,192
+// 2,879 / 2,838 / 2,826, 30,000 and 1,000 946 / 948 / 953.
+constexpr int64_t LC_FEW_TILES = 2048;
 static_assert(LT / TN == 8, "planes 0-7 by a thread each, plane 8 by those of plane 0");
 constexpr int ST = 1024;         // threads of the single-workgroup kernels
 constexpr int UPD = LC_UPDATE_CHUNK;
@@ -124,8 +128,8 @@ __device__ __forceinline__ float wave_maxf(float v) {
                  fmaxf(__int_as_float(__builtin_amdgcn_readlane(b, 32)), __int_as_float(__builtin_amdgcn_readlane(b, 48))));
 }
 
-// rho of the frontier nodes of the level (parity p).  A workgroup keeps CHUNK
-// samples in registers and takes the frontier's nodes in groups, staged in LDS.
+// rho of the frontier nodes of the level (parity p).  A workgroup keeps TS samples
+// per thread (as many as a call of few samples has) in registers and takes the frontier's nodes in groups, staged in LDS.
 // Only the largest ratio of a node counts, so the square root and the divisions
 // are first taken by the 1-ulp instructions (error below 1e-6), and exactly only
 // for the lanes that come within 1e-5 of the wavefront's largest, or whose values
@@ -133,8 +137,12 @@ __device__ __forceinline__ float wave_maxf(float v) {
 // of so few nodes that a workgroup has one at a time is bound by latency, and reads
 // them without staging.
 // Bound by VALU issue.  With samples read again for every node and every ratio
-// exact, 300,000 VPLs at 8,192 samples took 1.05 ms over all levels, so 0.73.
+// exact, 300,000 VPLs at 8,192 samples took 1.05 ms over all levels, so 0.73, and with
+// k_lc_test_few for the first 9 levels 0.70.  At 256 samples a thread with one sample
+// instead of four (the same one repeated) takes a call of 300,000 VPLs from 1,361 to 1,326 us.
+template <int TS>
 __global__ __launch_bounds__(LT) void k_lc_test(LightcutView v, int p, float r_min2) {
+    constexpr int CHUNK = TS * LT;
     __shared__ float nd[9][TN];
     __shared__ int32_t id[TN];
     const int nf = v.ctl[p];
@@ -232,6 +240,52 @@ __global__ __launch_bounds__(LT) void k_lc_test(LightcutView v, int p, float r_m
                     ratios(i0 + i, nd[0][i], nd[1][i], nd[2][i], nd[3][i], nd[4][i], nd[5][i], nd[6][i], nd[7][i], nd[8][i]);
             __syncthreads();
         }
+    }
+}
+
+// The same for levels of few nodes: a workgroup per node and CHUNK samples, every
+// ratio exact, the launch as small as the level can be.  Such a level is bound by the
+// latency of its loads and by launching workgroups that find no node.
+template <int TS>
+__global__ __launch_bounds__(LT) void k_lc_test_few(LightcutView v, int p, float r_min2) {
+    constexpr int CHUNK = TS * LT;
+    __shared__ float red[LT / WAVE];
+    const int nf = v.ctl[p];
+    const int32_t *cur = v.front + (size_t)p * v.F;
+    uint32_t *rho = v.rho_f + (size_t)p * v.F;
+    const size_t N = 2 * (size_t)v.n - 1, S = v.S;
+    const int t = threadIdx.x, lane = t % WAVE, w = t / WAVE, c = blockIdx.y;
+    for (int i = blockIdx.x; i < nf; i += gridDim.x) {
+        const int f = cur[i];
+        if (f < v.n) continue;                   // a single VPL: exact, never split
+        const float lx = v.bbox[f], ly = v.bbox[N + f], lz = v.bbox[2 * N + f];
+        const float hx = v.bbox[3 * N + f], hy = v.bbox[4 * N + f], hz = v.bbox[5 * N + f];
+        const float I0 = v.lights[6 * N + f], I1 = v.lights[7 * N + f], I2 = v.lights[8 * N + f];
+        float best = 0.0f;
+#pragma unroll
+        for (int k = 0; k < TS; ++k) {           // (a repeated sample changes no maximum; a load under a condition would wait)
+            const int s = min(c * CHUNK + k * LT + t, v.S - 1);
+            const float x = v.samp[s], y = v.samp[S + s], z = v.samp[2 * S + s];
+            const float nx = v.samp[3 * S + s], ny = v.samp[4 * S + s], nz = v.samp[5 * S + s];
+            const float gx = fmaxf(fmaxf(lx - x, x - hx), 0.0f);
+            const float gy = fmaxf(fmaxf(ly - y, y - hy), 0.0f);
+            const float gz = fmaxf(fmaxf(lz - z, z - hz), 0.0f);
+            const float d2 = fmaf(gx, gx, fmaf(gy, gy, gz * gz));
+            const float h = fmaxf(nx * (lx - x), nx * (hx - x)) + fmaxf(ny * (ly - y), ny * (hy - y)) +
+                            fmaxf(nz * (lz - z), nz * (hz - z));
+            const float cub = h > 0.0f ? (d2 > 0.0f ? fminf(1.0f, h / sqrtf(d2)) : 1.0f) : 0.0f;
+            const float m = fmaf(v.samp[6 * S + s], I0, fmaf(v.samp[7 * S + s], I1, v.samp[8 * S + s] * I2));
+            const float b = cub / fmaxf(d2, r_min2) * m, inv = v.inv_est[s];
+            best = fmaxf(best, b > 0.0f ? b * inv : 0.0f);
+        }
+        best = wave_maxf(best);
+        if (lane == 0) red[w] = best;
+        __syncthreads();
+        if (t == 0) {
+            for (int k = 1; k < LT / WAVE; ++k) best = fmaxf(best, red[k]);
+            if (best > 0.0f) atomicMax(&rho[i], __float_as_uint(best));
+        }
+        __syncthreads();
     }
 }
 
@@ -558,12 +612,22 @@ int launch_lightcut(hipStream_t st, const LightcutView &v, const int32_t *level_
     hipLaunchKernelGGL(k_lc_samples, dim3(grid_for(std::max(v.S, 1), LT)), dim3(LT), 0, st, v, pts, r_min2);
     VPLMC_HIP(hipGetLastError());
     const unsigned test_grid = 2048;
+    // samples per thread of the split test: no more than there are
+    const int ts = v.S <= LT ? 1 : v.S <= 2 * LT ? 2 : 4;
+    const auto test = ts == 1 ? k_lc_test<1> : ts == 2 ? k_lc_test<2> : k_lc_test<4>;
+    const auto test_few = ts == 1 ? k_lc_test_few<1> : ts == 2 ? k_lc_test_few<2> : k_lc_test_few<4>;
+    const int64_t nchunk = ((int64_t)v.S + ts * LT - 1) / (ts * LT);
     const int max_splits = v.cap < v.n ? v.cap : v.n;   // splits per level stay below both
     const unsigned upd_chunks = (unsigned)((max_splits + UPD - 1) / UPD);
     for (int lvl = 0; lvl < depth; ++lvl) {
         const int p = lvl & 1;
         if (v.S > 0) {
-            hipLaunchKernelGGL(k_lc_test, dim3(test_grid), dim3(LT), 0, st, v, p, r_min2);
+            // the frontier has at most 2^lvl nodes
+            const int64_t nodes = lvl < 30 ? std::min<int64_t>((int64_t)1 << lvl, v.F) : v.F;
+            if (nodes * nchunk <= LC_FEW_TILES)
+                hipLaunchKernelGGL(test_few, dim3((unsigned)nodes, (unsigned)nchunk), dim3(LT), 0, st, v, p, r_min2);
+            else
+                hipLaunchKernelGGL(test, dim3(test_grid), dim3(LT), 0, st, v, p, r_min2);
             VPLMC_HIP(hipGetLastError());
         }
         hipLaunchKernelGGL(k_lc_select, dim3(1), dim3(ST), 0, st, v, p, eps, rho);
