@@ -182,7 +182,7 @@ __device__ __forceinline__ int next_item(int32_t &taken, int lane) {
     return __builtin_amdgcn_readfirstlane(k);
 }
 
-template <int Q, int THREADS>
+template <int Q, int THREADS, bool LANES>
 __device__ void adm_ell_slice(
     int s, const SliceDesc *__restrict__ desc, uint64_t seed, int32_t max_iter,
     int32_t fixed_iters, float tol, float alpha0, float beta0, float gamma, const int32_t *__restrict__ col_ptr_all,
@@ -442,17 +442,16 @@ __device__ void adm_ell_slice(
             // takes items as they do
             if (wave == NW - 1 && !xsys) spd_solve_wave<Q, true>(sh, alpha, lane);
             xsys = true;
-            // Rank 4 with many samples: an item is a group of 64 parts, a lane walks its
-            // part, its column's Y in registers.  Same sums bit for bit.  At 12
+            // Ranks 4 and 8 with many samples: an item is a group of 64 parts, a lane walks
+            // its part, its column's Y in registers.  Same sums bit for bit.  At 12 or 24
             // products per sample the matrix form's loads and stores, which take 64
             // entries from four places, outweigh what it saves; its items of 16 parts
             // spread few samples better.  Four slices, 100 iterations, ms, matrix form /
-            // by lane: 1,024 x 600 at 15% (92,160 samples) 12.7 / 8.8, 1,024 x 300 at 6.5%
-            // (19,968) 4.58 / 4.37, 256 x 600 (9,984) 3.69 / 4.35.  At rank 8 the same code
-            // gave up to 10% from 50,000 samples on and cost 1-3% below (registers).
+            // by lane: rank 4, 1,024 x 600 at 15% (92,160 samples) 12.7 / 8.8, 1,024 x 300 at
+            // 6.5% (19,968) 4.58 / 4.37, 256 x 600 (9,984) 3.69 / 4.35.  Rank 8: ADM_LANES_FROM.
             bool by_lane = false;
-            if constexpr (Q == 4) by_lane = nnz >= 16384 && G >= NW / 2;
-            if constexpr (Q == 4) if (by_lane) {
+            if constexpr (LANES) by_lane = nnz >= 16384 && G >= NW / 2;
+            if constexpr (LANES) if (by_lane) {
                 constexpr int U = 4;
                 for (int g = wave == NW - 1 ? next_item(taken_a, lane) : wave; g < G; g = next_item(taken_a, lane)) {
                     int j, cnt, pc, np;
@@ -994,7 +993,7 @@ __device__ __forceinline__ bool next_slice(int32_t *queue, int32_t count, int &k
     return k < count;
 }
 
-template <int Q, int THREADS>
+template <int Q, int THREADS, bool LANES>
 __global__ __launch_bounds__(THREADS) void k_adm_ell(
     const SliceDesc *__restrict__ desc, const int32_t *__restrict__ slice_list, int32_t count, int32_t *queue,
     uint64_t seed, int32_t max_iter, int32_t fixed_iters, float tol, float alpha0, float beta0, float gamma,
@@ -1003,7 +1002,7 @@ __global__ __launch_bounds__(THREADS) void k_adm_ell(
     int32_t *stats_all) {
     int k, state = 0;
     while (next_slice(queue, count, k, state)) {
-        adm_ell_slice<Q, THREADS>(__builtin_amdgcn_readfirstlane(slice_list[k]), desc, seed, max_iter, fixed_iters, tol, alpha0, beta0, gamma,
+        adm_ell_slice<Q, THREADS, LANES>(__builtin_amdgcn_readfirstlane(slice_list[k]), desc, seed, max_iter, fixed_iters, tol, alpha0, beta0, gamma,
                                   col_ptr_all, ell, X_all, Xp_all, Lam_all, Y_all, Yp_all,
                                   Pi_all, Yt_all, red_all, e2part_all, scale_all, stats_all);
         __syncthreads();
@@ -1069,13 +1068,21 @@ int adm_grid(K kern, int threads, size_t dyn, int n_cu, bool queue, size_t count
     return VPLMC_OK;
 }
 
-template <int Q, int T>
+// At rank 8 holding both forms costs registers, so slices that take the matrix form
+// lose 1-3%: the kernel with both runs where a bucket's slices have at least this many
+// samples in the mean (not where the counts are capacities only, in coarsened frames).
+// 100 iterations, ms, matrix form / both: 4 slices of 1,900 x 600, 70,000 samples 12.7 /
+// 11.6, 175,000 28.9 / 25.1; 300 of 1,900 x 300, 35,000 21.9 / 20.9; 4 of 256 x 2,000, 29,000
+// 9.98 / 9.56; 300 of 1,900 x 600, 21,000 17.8 / 18.3.
+constexpr int64_t ADM_LANES_FROM = 24576;
+
+template <int Q, int T, bool LANES>
 int launch_adm_ell_t(hipStream_t st, size_t count, int max_m, const int32_t *ids_dev, int32_t *queue, int n_cu,
                      const SliceDesc *desc, const vplmc_params &prm, const int32_t *col_ptr, const EllView &ell,
                      float *X, float *Xp, float *Lam, float *Y, float *Yp,
                      float *Pi, float *Yt, float *red, double *e2part, float *scale, int32_t *stats) {
     const size_t dyn = adm_lds_dynamic_bytes(Q, max_m);
-    auto kern = k_adm_ell<Q, T>;
+    auto kern = k_adm_ell<Q, T, LANES>;
     VPLMC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
     unsigned grid;
@@ -1091,17 +1098,18 @@ int launch_adm_ell_t(hipStream_t st, size_t count, int max_m, const int32_t *ids
 }
 
 template <int Q>
-int launch_adm_ell(hipStream_t st, int threads, size_t count, int max_m, const int32_t *ids_dev, int32_t *queue,
+int launch_adm_ell(hipStream_t st, int threads, bool lanes, size_t count, int max_m, const int32_t *ids_dev, int32_t *queue,
                    int n_cu, const SliceDesc *desc, const vplmc_params &prm, const int32_t *col_ptr,
                    const EllView &ell, float *X, float *Xp, float *Lam,
                    float *Y, float *Yp, float *Pi, float *Yt, float *red, double *e2part, float *scale,
                    int32_t *stats) {
     if (count == 0) return VPLMC_OK;
-    if (threads == 512)
-        return launch_adm_ell_t<Q, 512>(st, count, max_m, ids_dev, queue, n_cu, desc, prm, col_ptr, ell, X, Xp, Lam,
-                                        Y, Yp, Pi, Yt, red, e2part, scale, stats);
-    return launch_adm_ell_t<Q, 1024>(st, count, max_m, ids_dev, queue, n_cu, desc, prm, col_ptr, ell, X, Xp, Lam, Y,
-                                     Yp, Pi, Yt, red, e2part, scale, stats);
+    auto run = threads == 512 ? launch_adm_ell_t<Q, 512, Q == 4> : launch_adm_ell_t<Q, 1024, Q == 4>;
+    if constexpr (Q == 8) {
+        if (lanes) run = threads == 512 ? launch_adm_ell_t<Q, 512, true> : launch_adm_ell_t<Q, 1024, true>;
+    }
+    return run(st, count, max_m, ids_dev, queue, n_cu, desc, prm, col_ptr, ell, X, Xp, Lam, Y, Yp, Pi, Yt, red, e2part,
+               scale, stats);
 }
 
 }  // namespace
@@ -1120,6 +1128,9 @@ int launch_adm(hipStream_t st, const AdmStreams *ss, const vplmc_plan &plan, int
     const bool qm = plan.tune.adm_queue != 0;
     auto qp = [&](int g) { return qm ? queues + g : nullptr; };
     const int thr = plan.tune.adm_threads;
+    auto lanes = [&](int g) {
+        return !plan.coarse && plan.group_samples[g] >= ADM_LANES_FROM * (int64_t)plan.groups[g].size();
+    };
     // The rank buckets touch disjoint slices: with more than one bucket present,
     // ranks 4, 8 and 16 run on streams forked from st while rank 32 (the
     // longest slices) runs on st, so that one bucket's tail of large slices
@@ -1140,8 +1151,8 @@ int launch_adm(hipStream_t st, const AdmStreams *ss, const vplmc_plan &plan, int
                                csr_val, col_ptr, csc_row, csc_val, X, Xn, Xp, Lam, Y, Yp, Pi, scale, stats);
 #define VPLMC_ADM_PAIR(B, Q, TG)                                                                                      \
     if (!rc)                                                                                                          \
-        rc = launch_adm_ell<Q>(sb[B], thr, plan.groups[2 * B].size(), plan.group_max_m[2 * B], id[2 * B], qp(2 * B), \
-                               n_cu, desc, prm, col_ptr, ell, X, Xp, Lam, Y, Yp, Pi, Yt, red, e2part, scale, stats); \
+        rc = launch_adm_ell<Q>(sb[B], thr, lanes(2 * B), plan.groups[2 * B].size(), plan.group_max_m[2 * B], id[2 * B], \
+                               qp(2 * B), n_cu, desc, prm, col_ptr, ell, X, Xp, Lam, Y, Yp, Pi, Yt, red, e2part, scale, stats); \
     if (!rc)                                                                                                          \
         rc = launch_gadm_group(sb[B], Q, plan, 2 * B + 1, id[2 * B + 1], gblk_dev, gsys, ge2, desc, prm, row_ptr,  \
                                csr_col, csr_val, col_ptr, csc_row, csc_val, X, Xn, Xp, Lam, Y, Yp, Pi, scale, stats);
