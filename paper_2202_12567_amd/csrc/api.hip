@@ -586,6 +586,7 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
         plan->group_max_m[grp] = std::max<int32_t>(plan->group_max_m[grp], (int32_t)m);
         plan->group_max_n[grp] = std::max<int32_t>(plan->group_max_n[grp], (int32_t)n);
         plan->group_samples[grp] += N1 + N2;
+        plan->group_rows[grp] += m;
         plan->max_m = std::max<int64_t>(plan->max_m, m);
     }
     // largest slices first in every launch group (longest-processing-time order for

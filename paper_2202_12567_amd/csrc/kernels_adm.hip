@@ -1070,11 +1070,13 @@ int adm_grid(K kern, int threads, size_t dyn, int n_cu, bool queue, size_t count
 
 // At rank 8 holding both forms costs registers, so slices that take the matrix form
 // lose 1-3%: the kernel with both runs where a bucket's slices have at least this many
-// samples in the mean (not where the counts are capacities only, in coarsened frames).
-// 100 iterations, ms, matrix form / both: 4 slices of 1,900 x 600, 70,000 samples 12.7 /
-// 11.6, 175,000 28.9 / 25.1; 300 of 1,900 x 300, 35,000 21.9 / 20.9; 4 of 256 x 2,000, 29,000
-// 9.98 / 9.56; 300 of 1,900 x 600, 21,000 17.8 / 18.3.
-constexpr int64_t ADM_LANES_FROM = 24576;
+// samples and rows in the mean (not where the counts are capacities only, in coarsened
+// frames).  100 iterations, ms, matrix form / both: 4 slices of 1,900 x 600, 70,000 samples
+// 12.7 / 11.6, 175,000 28.9 / 25.1; 300 of 1,900 x 300, 35,000 21.9 / 20.9; 16 of 512 x 1,024,
+// 31,000 7.74 / 7.46; 16 of 512 x 512, 26,000 6.01 / 6.05; 300 of 1,900 x 600, 21,000 17.8 /
+// 18.3; 16 of 256 x 1,024, 26,000 6.94 / 7.18, 52,000 10.4 / 10.8 (fewer rows: more of a
+// wavefront's additions meet).
+constexpr int64_t ADM_LANES_FROM = 28672, ADM_LANES_ROWS = 512;
 
 template <int Q, int T, bool LANES>
 int launch_adm_ell_t(hipStream_t st, size_t count, int max_m, const int32_t *ids_dev, int32_t *queue, int n_cu,
@@ -1129,7 +1131,8 @@ int launch_adm(hipStream_t st, const AdmStreams *ss, const vplmc_plan &plan, int
     auto qp = [&](int g) { return qm ? queues + g : nullptr; };
     const int thr = plan.tune.adm_threads;
     auto lanes = [&](int g) {
-        return !plan.coarse && plan.group_samples[g] >= ADM_LANES_FROM * (int64_t)plan.groups[g].size();
+        const int64_t n = (int64_t)plan.groups[g].size();
+        return !plan.coarse && plan.group_samples[g] >= ADM_LANES_FROM * n && plan.group_rows[g] >= ADM_LANES_ROWS * n;
     };
     // The rank buckets touch disjoint slices: with more than one bucket present,
     // ranks 4, 8 and 16 run on streams forked from st while rank 32 (the

@@ -299,7 +299,7 @@ struct vplmc_plan {
     // variant 0 = X resident in LDS, 1 = X in global memory
     std::vector<int32_t> groups[8];
     int32_t group_max_m[8] = {}, group_max_n[8] = {};
-    int64_t group_samples[8] = {};               // N1 + N2 over its slices
+    int64_t group_samples[8] = {}, group_rows[8] = {};   // N1 + N2 and rows over its slices
     vplmc::Layout layout;
     int64_t tot1 = 0, tot2 = 0, tot_omega = 0, tot_col = 0, tot_row = 0, tot_x = 0, tot_y = 0;
     int64_t tot_bm = 0, tot_bmt = 0;
