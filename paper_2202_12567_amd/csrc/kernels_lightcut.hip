@@ -138,7 +138,7 @@ __device__ __forceinline__ float wave_maxf(float v) {
 // them without staging.
 // Bound by VALU issue.  With samples read again for every node and every ratio
 // exact, 300,000 VPLs at 8,192 samples took 1.05 ms over all levels, so 0.73, and with
-// k_lc_test_few for the first 9 levels 0.70.  At 256 samples a thread with one sample
+// k_lc_test_few for the first 9 levels 0.71.  At 256 samples a thread with one sample
 // instead of four (the same one repeated) takes a call of 300,000 VPLs from 1,361 to 1,326 us.
 template <int TS>
 __global__ __launch_bounds__(LT) void k_lc_test(LightcutView v, int p, float r_min2) {
