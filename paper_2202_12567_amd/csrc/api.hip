@@ -770,7 +770,8 @@ static int plan_build(int32_t n_slices, const int32_t *pt_offsets, const int32_t
     core[R_E2PART] = plan->tot_part * 16;
     plan->core_total = 0;
     for (int r = 0; r < R_INTERNAL_END; ++r) plan->core_total = align256(plan->core_total + core[r]);
-    // a frame that the static workspace takes does so with its tables, or without the top one
+    // a frame that the static workspace takes does so with its tables, or, for every
+    // caller (a plan has one layout), without the top one
     if (plan->core_total <= VPLMC_STATIC_WORKSPACE_BYTES && L.total > STATIC_TOTAL_BYTES && plan->n_front > 1) {
         if ((rc = build_tree(co, mean_rows, 1, plan->tree, plan->height_max, plan->n_front))) {
             delete plan;
